@@ -207,6 +207,9 @@ gsmat_status guarded(F&& f) {
 // -------------------------------------------------------------------------
 void prof_begin(hipStream_t s, int cls);
 void host_sync(hipStream_t s);  // hipStreamSynchronize, timed for instrumentation
+// Waits until *p, a word of host memory that the stream's work writes last,
+// is `want`: looks at it for a short while, then waits for the stream.
+void host_wait_word(const uint32_t* p, uint32_t want, hipStream_t s);
 void host_event_sync(hipEvent_t e);  // hipEventSynchronize, timed likewise
 void prof_end(hipStream_t s, int cls, double bytes);
 bool prof_on(int cls);
@@ -288,6 +291,8 @@ void launch_write_expand(ColSet in, int k, const int64_t* P, const int32_t* star
                          int64_t ntiles, OutSet out, double alg_bytes, hipStream_t s);
 void launch_cartesian(ColSet a, int ka, int64_t na, ColSet b, int kb, int64_t nb, int64_t J0,
                       int64_t J1, OutSet out, hipStream_t s);
+// out's columns = in's, n rows of k columns
+void launch_copy_cols(ColSet in, int k, int64_t n, OutSet out, hipStream_t s);
 // writes kSampleBlocks partial sums per candidate to part[cand * kSampleBlocks + b]
 void launch_sample_fanout(const SampleSet& ss, int64_t* part, hipStream_t s);
 void launch_pack_rows(ColSet cols, int k, int64_t row0, int64_t rows, int32_t* out,

@@ -89,9 +89,11 @@ gsmat_step_info step_pick(const gsmat_query_plan* pl, const StepChoice& c, const
 // (null: pinned host memory) is a device area of at least kStageBytes where
 // kernels leave the small results the host reads.
 constexpr size_t kStageBytes = 4096;
-void run_query(gsmat_store* st, const gsmat_query_plan* pl, int64_t budget_bytes,
+// True: every launch has been waited for.  small unset: no one-launch run of
+// small tables.
+bool run_query(gsmat_store* st, const gsmat_query_plan* pl, int64_t budget_bytes,
                int64_t max_rows, hipStream_t s, gsmat_result* res, DeviceMem* mem = nullptr,
-               void* dev_area = nullptr);
+               void* dev_area = nullptr, bool small = true);
 
 // Runs plan pl (adaptive step choice) from table t0, or from the unit table
 // when t0 is null, and appends the final tables to out instead of adding them

@@ -1,0 +1,77 @@
+// Small joins: a query whose tables stay within a few thousand rows runs all
+// its remaining steps in one workgroup and one launch (small.hip).
+#pragma once
+
+#include "common.hpp"
+
+namespace gsmat {
+
+constexpr int64_t kSmallRows = 4096;        // rows of a table inside the launch
+constexpr int64_t kSmallTab = 4 * kSmallRows * kMaxCols;  // bytes of such a table
+constexpr int64_t kSmallFin = 64 << 10;     // bytes of a final table of its own
+// The work area: two tables, the row starts and lengths of every candidate
+// expansion, and the output offsets of an expansion left to be written.
+constexpr int64_t kSmallStarts = 2 * kSmallTab;
+constexpr int64_t kSmallLens = kSmallStarts + (int64_t)kMaxPats * kSmallRows * 4;
+constexpr int64_t kSmallOffs = kSmallLens + (int64_t)kMaxPats * kSmallRows * 4;
+constexpr int64_t kSmallWork = kSmallOffs + (kSmallRows + 32) * 8;
+
+enum : int32_t { kSmallDone = 1, kSmallMore = 2, kSmallWrite = 3 };
+// where a reported table's columns are: where they were at the start (or in
+// the store), in the final area, in the work area
+enum : int32_t { kAtStart = 0, kAtFin = 1, kAtWork = 2 };
+
+struct SmallPat {
+  int32_t s, p, o;
+};
+struct SmallStep {
+  int8_t kind, tp, orient, var;
+  uint32_t members;
+};
+
+// One query: its plan, the table it starts from (column c holds variable
+// var[c]) and the memory of its tables.
+struct SmallArgs {
+  int32_t np, nsteps, adaptive, k;
+  int32_t si;
+  uint32_t rem;
+  int64_t n;
+  int64_t budget;
+  const PredDesc* dout;
+  const PredDesc* din;
+  OriPtrs out, in;
+  const int32_t* out_src;
+  char* work;       // kSmallWork bytes
+  char* fin;        // kSmallFin bytes
+  SmallPat pats[kMaxPats];
+  SmallStep steps[kMaxPats + 1];
+  LookupRes lk[kMaxPats];       // of the patterns with a constant ...
+  uint32_t lk_valid;            // ... where this bit is set (else looked up)
+  const int32_t* col[kMaxCols];
+  int8_t var[kMaxCols];
+};
+
+// What the host reads when the launch is done: the table reached and the
+// steps' row counts.  kSmallDone: the table is the query's answer (n = 0:
+// none).  kSmallMore: it is the table before step si, which the general path
+// takes on from there.  kSmallWrite: likewise, but step si has been counted:
+// an expansion of pattern tp (orient 0 from its subject) with m rows, its
+// offsets (int64) at kSmallOffs of the work area and its rows' starts at start.
+struct SmallReport {
+  int64_t n;
+  int32_t k, si;
+  uint32_t rem;
+  int32_t status, place, tp, orient;
+  int64_t m;
+  const int32_t* start;
+  const int32_t* col[kMaxCols];
+  int32_t var[kMaxCols];
+  int64_t step_in[kMaxPats + 1], step_out[kMaxPats + 1];
+  uint32_t seq;  // written last
+};
+
+// Runs one query from a.rem / a.si on; rep (host memory the device can write,
+// or device memory) is complete once rep->seq == seq.
+void launch_small(const SmallArgs& a, SmallReport* rep, uint32_t seq, hipStream_t s);
+
+}  // namespace gsmat

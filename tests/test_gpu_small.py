@@ -1,0 +1,89 @@
+"""Queries of few rows, which one launch takes from their first table to their
+answer: at the edges of what the launch holds (rows entering a step, rows of a
+step and of the answer), at the steps it leaves to the general path, and from
+tables the general path has already produced.  Rows against the oracle and, in
+order, against the batched join; step counters against the batched join."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+ROWS = 4096  # rows of a table inside the launch
+
+
+@pytest.fixture(scope="module")
+def G():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_1807_07691_amd as G
+    return G
+
+
+def graph(n, fan, seed):
+    """Vertex 0 has n objects along predicate 0; each of them `fan` objects
+    along predicate 1 (every seventh none); predicate 2 closes a part of the
+    pairs, predicate 3 leads on, 4 marks a part of the objects, 5 is random."""
+    r = np.random.default_rng(seed)
+    V = 2 * n + 40
+    xs = np.arange(1, n + 1)
+    t = [np.stack([np.zeros(n, np.int64), np.zeros(n, np.int64), xs], 1)]
+    src = np.repeat(xs[xs % 7 != 0], fan)
+    dst = r.integers(1, V, len(src))
+    t.append(np.stack([src, np.full(len(src), 1), dst], 1))
+    near = r.random(len(src)) < 0.5
+    t.append(np.stack([src[near], np.full(near.sum(), 2), dst[near]], 1))
+    t.append(np.stack([np.arange(1, V), np.full(V - 1, 3), r.integers(1, V, V - 1)], 1))
+    some = xs[r.random(n) < 0.6]
+    t.append(np.stack([some, np.full(len(some), 4), np.full(len(some), 5)], 1))
+    t.append(np.stack([r.integers(0, V, 3000), np.full(3000, 5), r.integers(0, 9, 3000)], 1))
+    a = np.concatenate(t).astype(np.int32)
+    return a[:, 0].copy(), a[:, 1].copy(), a[:, 2].copy(), V, 6
+
+
+QUERIES = [
+    [[0, 0, -1]],
+    [[0, 0, -1], [-1, 1, -2]],
+    [[0, 0, -1], [-1, 1, -2], [-1, 2, -2]],
+    [[0, 0, -1], [-1, 1, -2], [-2, 3, -3], [-1, 3, -4]],
+    [[0, 0, -1], [-1, 4, 5], [-1, 3, -2]],
+    [[-1, 4, 5], [-1, 1, -2], [-2, 5, 3]],
+    [[-1, 4, 5], [0, 0, -1]],
+    [[0, 0, 1], [1, 3, -1], [-1, 3, -2], [-2, 3, -3]],
+    [[0, 0, -1], [-1, 3, -1]],
+    [[0, 0, -1], [1, 3, -2]],
+]
+
+
+def rows_sorted(a):
+    return a[np.lexsort(a.T[::-1])] if len(a) and a.shape[1] else a
+
+
+@pytest.mark.parametrize("n,fan", [(1, 1), (63, 3), (ROWS - 1, 1), (ROWS, 1), (ROWS + 1, 1),
+                                   (2048, 2), (2341, 2), (700, 7), (683, 24)])
+def test_small_joins(G, n, fan):
+    import oracle as O
+    s, p, o, V, P = graph(n, fan, n + fan)
+    st = G.gsmat_load_triples(s, p, o, V, P)
+    G.gsmat_build_index(st)
+    for mode in (G.PLAN_PAPER, G.PLAN_DEFAULT, G.PLAN_ADAPTIVE):
+        for budget in (0, 40_000):
+            plans, _ = G.gsmat_plan_batch(st, QUERIES, mode)
+            # the batch's rounds, which never take the one-launch path
+            G.gsmat_set_batch_engine(st, G.ENGINE_HOST)
+            batch, _ = G.gsmat_join_batch(st, plans)
+            for q, pl, b in zip(QUERIES, plans, batch):
+                want = O.join(s, p, o, q, int(-np.min(np.array(q)[:, [0, 2]])))
+                r = G.gsmat_join(st, pl, budget)
+                got = G.gsmat_fetch_bindings(r)
+                print(f"[gpu] small n={n} fan={fan} mode={mode} budget={budget} rows={len(got)}",
+                      flush=True)
+                assert np.array_equal(rows_sorted(got), want), (q, mode, budget)
+                gi, bi = G.gsmat_result_info(r), G.gsmat_result_info(b)
+                assert gi["step_rows_out"] == bi["step_rows_out"], (q, mode, budget)
+                assert gi["step_rows_in"] == bi["step_rows_in"], (q, mode, budget)
+                if budget == 0:
+                    assert np.array_equal(got, G.gsmat_fetch_bindings(b)), (q, mode)
+                r.close()
+                b.close()
+                pl.close()
+    st.close()
