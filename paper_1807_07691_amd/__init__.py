@@ -790,8 +790,10 @@ def gsmat_result_info(result):
 
 
 def gsmat_fetch_bindings(result, row_offset=0, max_rows=None, stream=None):
-    info = gsmat_result_info(result)
-    rows, nv = info["rows"], info["n_vars"]
+    c_rows, c_nv = ctypes.c_int64(), ctypes.c_int32()
+    _check(_lib.gsmat_result_info(result.h, ctypes.byref(c_rows), ctypes.byref(c_nv), None, None,
+                                  None))
+    rows, nv = c_rows.value, c_nv.value
     if max_rows is None:
         max_rows = rows
     n = max(0, min(rows - min(row_offset, rows), max_rows))

@@ -52,22 +52,30 @@ void host_sync(hipStream_t s) {
 }
 
 // A kernel's last store reaches host memory several microseconds before the
-// stream's completion is signalled and seen (a lookup and its wait: 16.7 us
-// with hipStreamSynchronize).  The looking ends after 200 us, so a long queue
-// does not hold a core, and a failed or capturing stream is reported by the
-// wait that follows.
-void host_wait_word(const uint32_t* p, uint32_t want, hipStream_t s) {
+// stream's completion is signalled and seen.  The looking ends after 200 us,
+// so a long queue does not hold a core, and a failed or capturing stream is
+// reported by the wait that follows.
+void host_wait_words(const uint32_t* p, int n, uint32_t want, hipStream_t s) {
   HostTimer t(&g_sync_ms, &g_syncs);
   const double t0 = now_ms();
+  int at = 0;
   do {
     for (int i = 0; i < 64; ++i) {
-      if (__atomic_load_n(p, __ATOMIC_ACQUIRE) == want) return;
+      while (at < n && __atomic_load_n(p + at, __ATOMIC_ACQUIRE) == want) ++at;
+      if (at == n) return;
       __builtin_ia32_pause();
     }
   } while (now_ms() - t0 < 0.2);
   GS_HIP(hipStreamSynchronize(s));
-  if (__atomic_load_n(p, __ATOMIC_ACQUIRE) != want)
-    throw StatusFail{GSMAT_EHIP, "internal: a kernel ended without its report"};
+  for (; at < n; ++at)
+    if (__atomic_load_n(p + at, __ATOMIC_ACQUIRE) != want)
+      throw StatusFail{GSMAT_EHIP, "internal: a kernel ended without its report"};
+}
+
+uint32_t next_report() {
+  thread_local uint32_t q = 0;
+  if (++q == 0) ++q;
+  return q;
 }
 
 void host_event_sync(hipEvent_t e) {

@@ -95,27 +95,26 @@ std::vector<LookupRes> lookup_many(const gsmat_store* st, const std::vector<Look
   std::vector<LookupRes> out(req.size());
   if (req.empty()) return out;
   const size_t n = req.size();
-  if (n <= (size_t)kMaxLookups) {  // few requests: passed by value, no upload
+  const int groups = (int)ceil_div((int64_t)n, kBlock);
+  LookupRes* hres =
+      (LookupRes*)pins()[kPinTotals].get(sizeof(LookupRes) * n + sizeof(uint32_t) * groups);
+  uint32_t* words = (uint32_t*)(hres + n);
+  std::fill(words, words + groups, 0u);
+  const uint32_t report = next_report();
+  if (n <= (size_t)kMaxLookups) {  // few requests: passed by value
     LookupBatch b{};
     for (size_t i = 0; i < n; ++i) b.req[i] = req[i];
     b.n = (int32_t)n;
-    LookupRes* hres = (LookupRes*)pins()[kPinTotals].get(sizeof(LookupRes) * n);
-    launch_lookup(b, st->out.d_desc, st->in.d_desc, st->out.ptrs(), st->in.ptrs(), hres, s);
-    host_sync(s);
-    std::memcpy(out.data(), hres, sizeof(LookupRes) * n);
-    return out;
+    launch_lookup(b, st->out.d_desc, st->in.d_desc, st->out.ptrs(), st->in.ptrs(), hres, s, words,
+                  report);
+  } else {
+    // 16 bytes a request, each read once: read where they are
+    LookupReq* hreq = (LookupReq*)pins()[kPinLookup].get(sizeof(LookupReq) * n);
+    std::memcpy(hreq, req.data(), sizeof(LookupReq) * n);
+    launch_lookup_many(hreq, (int32_t)n, st->out.d_desc, st->in.d_desc, st->out.ptrs(),
+                       st->in.ptrs(), hres, words, report, s);
   }
-  Layout L;
-  const size_t o_req = L.add(sizeof(LookupReq) * n);
-  Arena a(st->mem.get(), L.bytes, s);
-  char* dev = (char*)a.p;
-  LookupReq* hreq = (LookupReq*)pins()[kPinLookup].get(sizeof(LookupReq) * n);
-  LookupRes* hres = (LookupRes*)pins()[kPinTotals].get(sizeof(LookupRes) * n);
-  std::memcpy(hreq, req.data(), sizeof(LookupReq) * n);
-  GS_HIP(hipMemcpyAsync(dev + o_req, hreq, sizeof(LookupReq) * n, hipMemcpyHostToDevice, s));
-  launch_lookup_many((const LookupReq*)(dev + o_req), (int32_t)n, st->out.d_desc, st->in.d_desc,
-                     st->out.ptrs(), st->in.ptrs(), hres, s);
-  host_sync(s);
+  host_wait_words(words, groups, report, s);
   std::memcpy(out.data(), hres, sizeof(LookupRes) * n);
   return out;
 }

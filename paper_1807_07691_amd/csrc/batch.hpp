@@ -122,8 +122,11 @@ void run_batch_device_bgp(gsmat_store* st, const gsmat_pattern* pats, const int3
                           std::vector<gsmat_status>& status, std::vector<std::string>& msg,
                           std::vector<std::unique_ptr<gsmat_query_plan>>& fallback);
 
+// req and res may be host memory; each workgroup of kBlock requests writes
+// `report` to its word
 void launch_lookup_many(const LookupReq* req, int32_t n, const PredDesc* dout, const PredDesc* din,
-                        OriPtrs out, OriPtrs in, LookupRes* res, hipStream_t s);
+                        OriPtrs out, OriPtrs in, LookupRes* res, uint32_t* words,
+                        uint32_t report, hipStream_t s);
 // fan-out samples: kSampleBlocks partial sums per candidate to part[c * kSampleBlocks + b]
 void launch_b_sample(const SCand* cands, int64_t nc, int64_t* part, hipStream_t s);
 // count / flag tiles of every task (items in task order) -> tile sums ts[ntiles]

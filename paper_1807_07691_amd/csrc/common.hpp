@@ -207,9 +207,13 @@ gsmat_status guarded(F&& f) {
 // -------------------------------------------------------------------------
 void prof_begin(hipStream_t s, int cls);
 void host_sync(hipStream_t s);  // hipStreamSynchronize, timed for instrumentation
-// Waits until *p, a word of host memory that the stream's work writes last,
-// is `want`: looks at it for a short while, then waits for the stream.
-void host_wait_word(const uint32_t* p, uint32_t want, hipStream_t s);
+// Reports: launches that leave small results in host memory write the
+// launch's number to a word of it last (one word per workgroup).
+// next_report: a number the calling thread's earlier launches did not have.
+uint32_t next_report();
+// Waits until each of the n words is `want`: looks at them for a short while,
+// then waits for the stream.
+void host_wait_words(const uint32_t* p, int n, uint32_t want, hipStream_t s);
 void host_event_sync(hipEvent_t e);  // hipEventSynchronize, timed likewise
 void prof_end(hipStream_t s, int cls, double bytes);
 bool prof_on(int cls);
@@ -226,7 +230,7 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // scan of tile sums in place; the grand total goes to total[0] and, if given,
 // to host_total[0] (pinned host memory, valid after the stream synchronizes)
 void launch_scan_tile_sums(int64_t* tile_sum, int64_t nt, int64_t* total, hipStream_t s,
-                           int64_t* host_total);
+                           int64_t* host_total, uint32_t* word = nullptr, uint32_t report = 0);
 // two tile-sum arrays [nt + 1] scanned together (totals at [nt])
 void launch_scan_tile_sums2(int64_t* ts, int64_t* ts2, int64_t nt, hipStream_t s);
 void launch_scan_add_i32(const int32_t* N, int64_t n, const int64_t* tile_off, int64_t* P,
@@ -271,7 +275,8 @@ void launch_ptr_sentinels(const PredDesc* d, int32_t P, int32_t* ptr, hipStream_
 
 // lookups (planner statistics, constant scans)
 void launch_lookup(const LookupBatch& b, const PredDesc* desc_out, const PredDesc* desc_in,
-                   OriPtrs out, OriPtrs in, LookupRes* res, hipStream_t s);
+                   OriPtrs out, OriPtrs in, LookupRes* res, hipStream_t s,
+                   uint32_t* word = nullptr, uint32_t report = 0);
 
 // join steps
 void launch_count_expand(const int32_t* col, int64_t n, PredView pv, int32_t* N, int32_t* start,
@@ -295,7 +300,11 @@ void launch_cartesian(ColSet a, int ka, int64_t na, ColSet b, int kb, int64_t nb
 void launch_copy_cols(ColSet in, int k, int64_t n, OutSet out, hipStream_t s);
 // writes kSampleBlocks partial sums per candidate to part[cand * kSampleBlocks + b]
 void launch_sample_fanout(const SampleSet& ss, int64_t* part, hipStream_t s);
-void launch_pack_rows(ColSet cols, int k, int64_t row0, int64_t rows, int32_t* out,
-                      hipStream_t s);
+// rows [row0, row0 + rows) of the k columns, row-major, to host memory `out`
+// (16-byte aligned); returns the number of workgroups, each of which writes
+// `report` to its word when its rows are there (at most kPackGroups)
+constexpr int kPackGroups = 256;
+int launch_pack_rows(ColSet cols, int k, int64_t row0, int64_t rows, int32_t* out,
+                     uint32_t* words, uint32_t report, hipStream_t s);
 
 }  // namespace gsmat

@@ -20,6 +20,16 @@ __device__ inline uint32_t mbcnt(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
+// The workgroup's report: every thread's stores to host memory, then the word.
+// Called by all threads; word null: nothing.
+__device__ inline void report_done(uint32_t* word, uint32_t report) {
+  if (!word) return;
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0)
+    __hip_atomic_store(word, report, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 __device__ inline int64_t wave_incl_scan(int64_t v) {
   const int lane = lane_id();
 #pragma unroll

@@ -49,6 +49,7 @@ struct PinnedArea {
   LookupRes res[kMaxLookups];
   int64_t part[kMaxPats * kSampleBlocks];
   SmallReport small;
+  uint32_t word;  // report of the launches that fill the other fields
 };
 
 static_assert(sizeof(PinnedArea) <= kStageBytes, "staged results must fit the staging area");
@@ -63,11 +64,34 @@ PinnedArea* pinned(bool make = true) {
   return a;
 }
 
-// Reports of the calling thread's launches are told apart by their number.
-uint32_t next_seq() {
-  thread_local uint32_t q = 0;
-  if (++q == 0) ++q;
-  return q;
+// Host memory that rows are fetched through: two parts, one filled by the
+// device while the other is copied out.  Per thread, 256 KiB until a fetch
+// needs more, then 8 MiB, given back at the thread's end.
+struct FetchArea {
+  static constexpr size_t kSmall = 128 << 10, kLarge = 4 << 20;  // bytes per part
+  char* p = nullptr;
+  size_t part = 0;
+  uint32_t* words(int i) { return (uint32_t*)(p + 2 * part) + i * kPackGroups; }
+  int32_t* rows(int i) { return (int32_t*)(p + i * part); }
+  void reserve(size_t bytes) {
+    const size_t want = bytes <= kSmall ? kSmall : kLarge;
+    if (part >= want) return;
+    release();
+    const size_t all = 2 * want + 2 * sizeof(uint32_t) * kPackGroups;
+    GS_HIP(hipHostMalloc((void**)&p, all, hipHostMallocDefault));
+    part = want;
+    std::memset(words(0), 0, 2 * sizeof(uint32_t) * kPackGroups);
+  }
+  void release() {
+    if (p) (void)hipHostFree(p);
+    p = nullptr;
+    part = 0;
+  }
+  ~FetchArea() { release(); }
+};
+FetchArea& fetch_area() {
+  thread_local FetchArea a;
+  return a;
 }
 
 struct Exec {
@@ -114,8 +138,9 @@ struct Exec {
       return v;
     }
     PinnedArea* h = pinned();
-    launch_scan_tile_sums(ts, nt, ts + nt, st_, &h->total[0]);
-    host_sync(st_);
+    const uint32_t report = next_report();
+    launch_scan_tile_sums(ts, nt, ts + nt, st_, &h->total[0], &h->word, report);
+    host_wait_words(&h->word, 1, report, st_);
     return h->total[0];
   }
 
@@ -186,8 +211,10 @@ struct Exec {
       return r;
     }
     PinnedArea* h = pinned();
-    launch_lookup(b, st->out.d_desc, st->in.d_desc, st->out.ptrs(), st->in.ptrs(), h->res, s);
-    host_sync(s);
+    const uint32_t report = next_report();
+    launch_lookup(b, st->out.d_desc, st->in.d_desc, st->out.ptrs(), st->in.ptrs(), h->res, s,
+                  &h->word, report);
+    host_wait_words(&h->word, 1, report, s);
     return h->res[0];
   }
 
@@ -438,13 +465,13 @@ struct Exec {
       a.col[c] = t.col[c];
       a.var[c] = (int8_t)t.var[c];
     }
-    const uint32_t seq = next_seq();
+    const uint32_t seq = next_report();
     SmallReport staged;
     const SmallReport* r;
     PinnedArea* h = pinned(!dev_area);
     if (h) {
       launch_small(a, &h->small, seq, s);
-      host_wait_word(&h->small.seq, seq, s);
+      host_wait_words(&h->small.seq, 1, seq, s);
       r = &h->small;
     } else {
       launch_small(a, &dev_area->small, seq, s);
@@ -923,8 +950,10 @@ std::vector<TpStat> pattern_stats(const gsmat_store* st, const gsmat_pattern* pa
     for (size_t i = 0; i < reqs.size(); ++i) b.req[i] = reqs[i];
     b.n = (int32_t)reqs.size();
     PinnedArea* h = pinned();
-    launch_lookup(b, st->out.d_desc, st->in.d_desc, st->out.ptrs(), st->in.ptrs(), h->res, s);
-    host_sync(s);
+    const uint32_t report = next_report();
+    launch_lookup(b, st->out.d_desc, st->in.d_desc, st->out.ptrs(), st->in.ptrs(), h->res, s,
+                  &h->word, report);
+    host_wait_words(&h->word, 1, report, s);
     std::vector<LookupRes> res(h->res, h->res + reqs.size());
     for (int i = 0; i < n; ++i) {
       if (req_of[i] < 0) continue;
@@ -1174,26 +1203,44 @@ extern "C" gsmat_status gsmat_fetch_bindings(const gsmat_result* r, int64_t row_
     if (hi <= lo || nv == 0) return GSMAT_OK;
     if (!host_rows) throw StatusFail{GSMAT_EINVAL, "host_rows is NULL"};
     hipStream_t s = (hipStream_t)stream;
-    DeviceMem* mem = r->st->mem.get();
-    const int64_t stage_rows = std::min<int64_t>(hi - lo, (int64_t)1 << 24);
-    Tmp<int32_t> stage(mem, stage_rows * nv, s);
-    int64_t seg_lo = 0;
-    int64_t written = 0;
-    for (const Segment& seg : r->segs) {
-      const int64_t seg_hi = seg_lo + seg.rows;
-      int64_t a = std::max(lo, seg_lo), b = std::min(hi, seg_hi);
-      while (a < b) {
-        const int64_t c = std::min(b - a, stage_rows);
-        ColSet cs{};
-        for (int v = 0; v < nv; ++v) cs.c[v] = seg.col[v];
-        launch_pack_rows(cs, nv, a - seg_lo, c, stage.p, s);
-        GS_HIP(hipMemcpyAsync(host_rows + written * nv, stage.p, sizeof(int32_t) * c * nv,
-                              hipMemcpyDeviceToHost, s));
-        GS_HIP(hipStreamSynchronize(s));
-        written += c;
-        a += c;
+    FetchArea& fa = fetch_area();
+    fa.reserve(std::min<uint64_t>(sizeof(int32_t) * (uint64_t)(hi - lo) * nv, FetchArea::kLarge));
+    const int64_t part_rows = (int64_t)(fa.part / (sizeof(int32_t) * nv));
+    // pieces of at most part_rows rows of one segment, in row order
+    struct Piece {
+      int64_t rows = 0;
+      int groups = 0;
+      uint32_t report = 0;
+    } pc[2];
+    size_t seg_i = 0;
+    int64_t seg_lo = 0, a = lo;  // the next row to launch
+    auto launch_next = [&](int i) {
+      pc[i].rows = 0;
+      while (a < hi && a >= seg_lo + r->segs[seg_i].rows) seg_lo += r->segs[seg_i++].rows;
+      if (a >= hi) return;
+      const Segment& seg = r->segs[seg_i];
+      ColSet cs{};
+      for (int v = 0; v < nv; ++v) cs.c[v] = seg.col[v];
+      const int64_t c = std::min(std::min(hi, seg_lo + seg.rows) - a, part_rows);
+      pc[i].report = next_report();
+      pc[i].groups =
+          launch_pack_rows(cs, nv, a - seg_lo, c, fa.rows(i), fa.words(i), pc[i].report, s);
+      pc[i].rows = c;
+      a += c;
+    };
+    try {
+      launch_next(0);
+      launch_next(1);
+      int32_t* to = host_rows;
+      for (int i = 0; pc[i].rows > 0; i ^= 1) {
+        host_wait_words(fa.words(i), pc[i].groups, pc[i].report, s);
+        std::memcpy(to, fa.rows(i), sizeof(int32_t) * pc[i].rows * nv);
+        to += pc[i].rows * nv;
+        launch_next(i);
       }
-      seg_lo = seg_hi;
+    } catch (...) {
+      (void)hipStreamSynchronize(s);  // nothing may still write the area
+      throw;
     }
     return GSMAT_OK;
   });

@@ -15,10 +15,11 @@ namespace {
 using namespace dev;
 
 __global__ void k_lookup_many(const LookupReq* __restrict__ req, int32_t n, const PredDesc* dout,
-                              const PredDesc* din, OriPtrs out, OriPtrs in, LookupRes* res) {
+                              const PredDesc* din, OriPtrs out, OriPtrs in, LookupRes* res,
+                              uint32_t* words, uint32_t report) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  res[i] = lookup_one(req[i], dout, din, out, in);
+  if (i < n) res[i] = lookup_one(req[i], dout, din, out, in);
+  report_done(words + blockIdx.x, report);
 }
 
 __global__ __launch_bounds__(kBlock) void k_b_sample(const SCand* __restrict__ c,
@@ -158,11 +159,12 @@ void b_compact(const WTask* t, const GItem* g, int ng, const int64_t* ts, int64_
 }  // namespace
 
 void launch_lookup_many(const LookupReq* req, int32_t n, const PredDesc* dout, const PredDesc* din,
-                        OriPtrs out, OriPtrs in, LookupRes* res, hipStream_t s) {
+                        OriPtrs out, OriPtrs in, LookupRes* res, uint32_t* words,
+                        uint32_t report, hipStream_t s) {
   if (n <= 0) return;
   GS_BLAUNCH(GSMAT_K_OTHER, 32.0 * n,
              hipLaunchKernelGGL(k_lookup_many, dim3((unsigned)ceil_div(n, kBlock)), dim3(kBlock),
-                                0, s, req, n, dout, din, out, in, res));
+                                0, s, req, n, dout, din, out, in, res, words, report));
 }
 
 void launch_b_sample(const SCand* cands, int64_t nc, int64_t* part, hipStream_t s) {
