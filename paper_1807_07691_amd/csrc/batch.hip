@@ -136,6 +136,7 @@ struct BQ {
   LookupRes lk[kMaxPats];  // row lookup of each pattern with a constant
   int64_t tag = 0;         // caller's id (server)
   int64_t est_bytes = 0;   // admission estimate (server)
+  bool tried = false;      // has been in a small batch (server)
   int cand0 = -1;       // first sampled candidate this round
   StepChoice choice;
   // pending task output (intersection result before it is combined)
@@ -997,6 +998,32 @@ struct gsmat_server {
     bt.admit(first);
   }
 
+  // The admitted queries that have not started, in one launch; what it does
+  // not finish takes part in the rounds.
+  void run_fresh() {
+    std::vector<const gsmat_query_plan*> plans;
+    std::vector<size_t> at;
+    for (size_t i = 0; i < bt.q.size() && plans.size() < (size_t)kSmallBatch; ++i) {
+      const BQ& b = bt.q[i];
+      if (b.state != kActive || b.si != 0 || !b.t.unit() || b.tried) continue;
+      plans.push_back(b.pl);
+      at.push_back(i);
+    }
+    if (plans.size() < 4) return;  // a round or two of so few is as fast
+    std::vector<DevQueryOut> out;
+    run_small_batch(st, plans.data(), (int32_t)plans.size(), bt.budget, mem_budget, bt.max_rows, s,
+                    out);
+    for (size_t j = 0; j < at.size(); ++j) {
+      BQ& b = bt.q[at[j]];
+      b.tried = true;
+      if (out[j].state == kDevFallback) continue;
+      b.state = out[j].state == kDevDone ? kDone : kFailed;
+      b.status = out[j].status;
+      b.res.reset(out[j].res);
+      b.t = Table();
+    }
+  }
+
   // Moves finished queries to the done list (queries that left the batch
   // are run alone first).
   void collect() {
@@ -1092,7 +1119,12 @@ extern "C" gsmat_status gsmat_server_step(gsmat_server* sv, int32_t* n_active, i
       // already counted rows of its steps: the queries it carried fail with
       // its status instead of repeating the step in the next round
       const gsmat_status rc = guarded([&]() -> gsmat_status {
-        sv->bt.round();
+        sv->run_fresh();
+        for (const BQ& b : sv->bt.q)
+          if (b.state == kActive) {
+            sv->bt.round();
+            break;
+          }
         return GSMAT_OK;
       });
       if (rc != GSMAT_OK) {
@@ -1139,13 +1171,41 @@ extern "C" void gsmat_server_free(gsmat_server* sv) { delete sv; }
 
 namespace {
 
+// A batch's queries: few of them first in one launch, the others in the
+// device-driven rounds.
+void run_batch_any(gsmat_store* st, const gsmat_query_plan* const* plans, int32_t n,
+                   int64_t budget_bytes, int64_t max_rows, hipStream_t s,
+                   std::vector<DevQueryOut>& out) {
+  if (n > kSmallBatch) {
+    run_batch_device(st, plans, n, budget_bytes, max_rows, s, out);
+    return;
+  }
+  run_small_batch(st, plans, n, budget_bytes, 0, max_rows, s, out);
+  std::vector<const gsmat_query_plan*> rest;
+  std::vector<int32_t> at;
+  for (int32_t i = 0; i < n; ++i)
+    if (out[i].state == kDevFallback) {
+      rest.push_back(plans[i]);
+      at.push_back(i);
+    }
+  if (rest.empty()) return;
+  try {
+    std::vector<DevQueryOut> dq;
+    run_batch_device(st, rest.data(), (int32_t)rest.size(), budget_bytes, max_rows, s, dq);
+    for (size_t j = 0; j < at.size(); ++j) out[at[j]] = dq[j];
+  } catch (...) {
+    for (DevQueryOut& o : out) gsmat_result_free(o.res);
+    throw;
+  }
+}
+
 // gsmat_join_batch with device-driven rounds: the queries that leave the
 // batch run alone afterwards, from the start.
 gsmat_status join_batch_device(gsmat_store* st, const gsmat_query_plan* const* plans,
                                int32_t n_plans, int64_t budget_bytes, int64_t max_rows,
                                hipStream_t s, gsmat_result** out, gsmat_status* status) {
   std::vector<DevQueryOut> dq;
-  run_batch_device(st, plans, n_plans, budget_bytes, max_rows, s, dq);
+  run_batch_any(st, plans, n_plans, budget_bytes, max_rows, s, dq);
   bool alone = false;
   gsmat_status first = GSMAT_OK;
   std::string first_err;
@@ -1205,8 +1265,30 @@ extern "C" gsmat_status gsmat_join_batch_bgp(gsmat_store* st, const gsmat_patter
     std::vector<gsmat_status> prc;
     std::vector<std::string> pmsg;
     std::vector<std::unique_ptr<gsmat_query_plan>> fb;
-    run_batch_device_bgp(st, pats, n_pats, n_queries, mode, budget_bytes, max_rows, s, dq, prc,
-                         pmsg, fb);
+    if (n_queries <= kSmallBatch) {
+      PlanPrep P;
+      plan_prepare(st, pats, n_pats, n_queries, mode, s, &P);
+      fb.resize(n_queries);
+      std::vector<const gsmat_query_plan*> valid;
+      std::vector<int32_t> at;
+      for (int i = 0; i < n_queries; ++i) {
+        if (P.rc[i] != GSMAT_OK) continue;
+        fb[i].reset(new gsmat_query_plan);
+        P.rc[i] = plan_build(st, pats, n_pats, mode, P, i, fb[i].get());
+        if (P.rc[i] != GSMAT_OK) continue;
+        valid.push_back(fb[i].get());
+        at.push_back(i);
+      }
+      std::vector<DevQueryOut> vq;
+      run_batch_any(st, valid.data(), (int32_t)valid.size(), budget_bytes, max_rows, s, vq);
+      dq.assign(n_queries, DevQueryOut{nullptr, kDevFailed, GSMAT_OK});
+      for (size_t j = 0; j < at.size(); ++j) dq[at[j]] = vq[j];
+      prc = P.rc;
+      pmsg = P.msg;
+    } else {
+      run_batch_device_bgp(st, pats, n_pats, n_queries, mode, budget_bytes, max_rows, s, dq, prc,
+                           pmsg, fb);
+    }
     bool alone = false;
     gsmat_status first = GSMAT_OK;
     std::string first_err;

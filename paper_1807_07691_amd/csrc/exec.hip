@@ -17,6 +17,7 @@
 #include <memory>
 #include <mutex>
 
+#include "batch.hpp"
 #include "exec.hpp"
 #include "small.hpp"
 
@@ -48,11 +49,13 @@ struct PinnedArea {
   int64_t total[8];
   LookupRes res[kMaxLookups];
   int64_t part[kMaxPats * kSampleBlocks];
-  SmallReport small;
   uint32_t word;  // report of the launches that fill the other fields
+  // a small join's query and report (host memory only)
+  SmallReport small;
+  SmallArgs query;
 };
 
-static_assert(sizeof(PinnedArea) <= kStageBytes, "staged results must fit the staging area");
+static_assert(offsetof(PinnedArea, small) <= kStageBytes, "staged results must fit the staging area");
 
 // The calling thread's area; with `make` unset, null when it has none yet.
 PinnedArea* pinned(bool make = true) {
@@ -89,9 +92,41 @@ struct FetchArea {
   }
   ~FetchArea() { release(); }
 };
+// Host memory of a batch's queries and reports (at most kSmallBatch of them),
+// per thread.
+struct QueryArea {
+  char* p = nullptr;
+  size_t bytes = 0;
+  char* get(size_t want) {
+    if (want <= bytes) return p;
+    if (p) (void)hipHostFree(p);
+    p = nullptr;
+    bytes = 0;
+    size_t b = 1 << 16;
+    while (b < want) b <<= 1;
+    GS_HIP(hipHostMalloc((void**)&p, b, hipHostMallocDefault));
+    bytes = b;
+    return p;
+  }
+  ~QueryArea() {
+    if (p) (void)hipHostFree(p);
+  }
+};
+QueryArea& query_area() {
+  thread_local QueryArea a;
+  return a;
+}
 FetchArea& fetch_area() {
   thread_local FetchArea a;
   return a;
+}
+
+uint32_t all_of(const gsmat_query_plan* pl) {
+  return pl->pats.size() >= 32 ? 0xFFFFFFFFu : ((1u << pl->pats.size()) - 1);
+}
+
+SmallStore small_store(const gsmat_store* st) {
+  return SmallStore{st->out.d_desc, st->in.d_desc, st->out.ptrs(), st->in.ptrs(), st->out.src};
 }
 
 struct Exec {
@@ -159,6 +194,7 @@ struct Exec {
       mem()->free(t.owned, t.owned_bytes, s);
     }
     t.owned = nullptr;
+    t.keep.reset();
   }
 
   // frees every table still alive (error paths)
@@ -235,6 +271,7 @@ struct Exec {
     }
     seg.owned = t.owned;
     seg.owned_bytes = t.owned_bytes;
+    seg.keep = t.keep;
     if (t.owned) forget(t.owned);
     t.owned = nullptr;
     res->rows += seg.rows;
@@ -412,24 +449,34 @@ struct Exec {
     return false;
   }
 
-  // Takes the table t through the steps from si on in one launch.  True: the
-  // query is finished (its answer, if any, emitted); false: the general path
-  // goes on from si, t and rem, which now tell how far the launch came.
-  bool run_small(int& si, Table& t, uint32_t& rem) {
-    void* work = mem()->alloc(kSmallWork, s);
-    void* fin = work ? mem()->alloc(kSmallFin, s) : nullptr;
-    if (work) live.push_back({work, (size_t)kSmallWork});
-    if (fin) live.push_back({fin, (size_t)kSmallFin});
-    auto drop = [&](void* p, size_t bytes) {
-      if (!p) return;
-      forget(p);
-      mem()->free(p, bytes, s);
-    };
-    if (!fin) {  // no memory for the areas: the general path needs less
-      drop(work, kSmallWork);
-      return false;
-    }
-    SmallArgs a;
+  // Whether a batch tries the whole query in one launch: its first relation
+  // has at most kSmallRows rows, as far as is known without a lookup.
+  bool small_first() const {
+    Table unit;
+    unit.n = 1;
+    if (small_fits(0, unit)) return true;
+    const gsmat_step_info& sp = pl->steps[0];
+    if (sp.kind != GSMAT_STEP_SCAN) return false;
+    const gsmat_pattern& q = pl->pats[sp.tp];
+    if (is_var(q.s) && is_var(q.o)) return q.s != q.o && st->out.desc[q.p].nnz <= kSmallRows;
+    return pl->lk[sp.tp].valid && pl->lk[sp.tp].len <= kSmallRows;
+  }
+
+  // Memory of a small join: one query's own blocks, or parts of what a batch
+  // holds (`hold` set: nothing is freed here).
+  struct SmallMem {
+    void* work = nullptr;
+    size_t work_bytes = 0;
+    void* fin = nullptr;
+    std::shared_ptr<Arena> work_hold, fin_hold;
+  };
+
+  int final_cols(const Table& t) const {
+    return std::min<int>(t.k + (int)pl->pats.size(), kMaxCols);
+  }
+
+  void fill_small(SmallArgs& a, int si, const Table& t, uint32_t rem, const SmallLayout& l,
+                  const SmallMem& sm) const {
     a.np = (int32_t)pl->pats.size();
     a.nsteps = (int32_t)pl->steps.size();
     a.adaptive = adaptive;
@@ -438,13 +485,12 @@ struct Exec {
     a.rem = rem;
     a.n = t.n;
     a.budget = budget;
-    a.dout = st->out.d_desc;
-    a.din = st->in.d_desc;
-    a.out = st->out.ptrs();
-    a.in = st->in.ptrs();
-    a.out_src = st->out.src;
-    a.work = (char*)work;
-    a.fin = (char*)fin;
+    a.work = (char*)sm.work;
+    a.tab = l.tab;
+    a.starts = l.starts;
+    a.lens = l.lens;
+    a.offs = l.offs;
+    a.fin = (char*)sm.fin;
     a.lk_valid = 0;
     const bool known = pl->lk_store == st->uid && pl->lk.size() == pl->pats.size();
     for (int i = 0; i < a.np; ++i) {
@@ -465,39 +511,89 @@ struct Exec {
       a.col[c] = t.col[c];
       a.var[c] = (int8_t)t.var[c];
     }
-    const uint32_t seq = next_report();
-    SmallReport staged;
-    const SmallReport* r;
+  }
+
+  // Takes the table t through the steps from si on in one launch.  True: the
+  // query is finished (its answer, if any, emitted); false: the general path
+  // goes on from si, t and rem, which now tell how far the launch came.
+  bool run_small(int& si, Table& t, uint32_t& rem) {
+    // the calling thread's area exists once it has planned a query
     PinnedArea* h = pinned(!dev_area);
-    if (h) {
-      launch_small(a, &h->small, seq, s);
-      host_wait_words(&h->small.seq, 1, seq, s);
-      r = &h->small;
-    } else {
-      launch_small(a, &dev_area->small, seq, s);
-      stage_back(&staged, &dev_area->small, sizeof(staged));
-      r = &staged;
+    if (!h) return false;
+    const SmallLayout l((int)pl->pats.size(), final_cols(t));
+    SmallMem sm;
+    sm.work_bytes = (size_t)l.bytes;
+    sm.work = mem()->alloc(sm.work_bytes, s);
+    if (!sm.work) return false;  // the general path may need less
+    live.push_back({sm.work, sm.work_bytes});
+    sm.fin = mem()->alloc(kSmallFin, s);
+    if (!sm.fin) {
+      drop(sm.work, sm.work_bytes);
+      return false;
     }
-    for (int i = 0; i < res->n_steps && i <= kMaxPats; ++i) {
-      res->step_in[i] += r->step_in[i];
-      res->step_out[i] += r->step_out[i];
-    }
-    const bool done = r->status == kSmallDone, counted = r->status == kSmallWrite;
-    const int place = r->place;
-    const int tp = r->tp, orient = r->orient;
-    const int64_t m = r->m;
-    const int32_t* const start = r->start;
-    Table o;
-    o.n = r->n;
-    o.k = r->k;
-    for (int c = 0; c < o.k; ++c) {
-      o.col[c] = r->col[c];
-      o.var[c] = r->var[c];
-    }
-    si = r->si;
-    rem = r->rem;
+    live.push_back({sm.fin, (size_t)kSmallFin});
+    fill_small(h->query, si, t, rem, l, sm);
+    const uint32_t seq = next_report();
+    launch_small(small_store(st), &h->query, &h->small, 1, seq, s);
+    host_wait_words(&h->small.seq, 1, seq, s);
     settled = true;
-    if (o.n > 0 && place == kAtWork && done) {
+    const SmallReport r = h->small;  // the area is used again by the steps below
+    return finish_small(r, (int64_t*)((char*)sm.work + l.offs), sm, si, t, rem);
+  }
+
+  void drop(void* p, size_t bytes) {
+    forget(p);
+    mem()->free(p, bytes, s);
+  }
+
+  // The write of an expansion that a small join counted: its task and its
+  // output table.
+  void prepare_write(const SmallReport& r, const int64_t* offs, SmallWriteTask& w, Table& o) {
+    const gsmat_pattern& q = pl->pats[r.tp];
+    int vars[kMaxCols];
+    for (int c = 0; c < r.k; ++c) vars[c] = r.var[c];
+    vars[r.k] = r.orient == 0 ? var_of(q.o) : var_of(q.s);
+    o = alloc_table(r.m, vars, r.k + 1);
+    w.offs = offs;
+    w.start = r.start;
+    w.nbr = r.orient == 0 ? st->out.view(q.p).nbr : st->in.view(q.p).nbr;
+    w.out = (int32_t*)o.owned;
+    w.m = r.m;
+    w.stride = col_stride(r.m);
+    w.n = (int32_t)r.n;
+    w.k = r.k;
+    for (int c = 0; c < r.k; ++c) w.col[c] = r.col[c];
+  }
+  static double write_bytes(const SmallReport& r) {
+    return 4.0 * (double)r.m * (r.k + 2) + (double)r.n * (4.0 * r.k + 12.0);
+  }
+  // Whether the write is one piece within the step budget.
+  bool one_piece(const SmallReport& r) const {
+    return budget <= 0 || r.m <= budget / (4 * (int64_t)(r.k + 1));
+  }
+
+  // Takes over what a small join reports (as run_small); written: the table
+  // of its counted expansion, where that has been written.
+  bool finish_small(const SmallReport& r, const int64_t* offs, const SmallMem& sm, int& si,
+                    Table& t, uint32_t& rem, Table* written = nullptr) {
+    for (int i = 0; i < res->n_steps && i <= kMaxPats; ++i) {
+      res->step_in[i] += r.step_in[i];
+      res->step_out[i] += r.step_out[i];
+    }
+    const bool done = r.status == kSmallDone;
+    const bool own = !sm.work_hold;
+    Table o;
+    o.n = r.n;
+    o.k = r.k;
+    for (int c = 0; c < o.k; ++c) {
+      o.col[c] = r.col[c];
+      o.var[c] = r.var[c];
+    }
+    si = r.si;
+    rem = r.rem;
+    bool keep_work = false, keep_fin = false;
+    if (o.n == 0) {
+    } else if (r.place == kAtWork && done) {
       // the answer leaves the work area for memory of its own size
       Table x = alloc_table(o.n, o.var, o.k);
       ColSet in{};
@@ -509,34 +605,54 @@ struct Exec {
       launch_copy_cols(in, o.k, o.n, out, s);
       settled = false;
       o = x;
-    } else if (o.n > 0 && place == kAtWork) {
-      o.owned = work;
-      o.owned_bytes = kSmallWork;
-    } else if (o.n > 0 && place == kAtFin) {
-      o.owned = fin;
-      o.owned_bytes = kSmallFin;
-    } else if (o.n > 0) {  // t's own columns, or views into the store
+    } else if (r.place == kAtWork) {
+      keep_work = true;
+      o.keep = sm.work_hold;
+      if (own) {
+        o.owned = sm.work;
+        o.owned_bytes = sm.work_bytes;
+      }
+    } else if (r.place == kAtFin) {
+      keep_fin = true;
+      o.keep = sm.fin_hold;
+      if (own) {
+        o.owned = sm.fin;
+        o.owned_bytes = kSmallFin;
+      }
+    } else {  // t's own columns, or views into the store
       o.owned = t.owned;
       o.owned_bytes = t.owned_bytes;
       o.keep = t.keep;
       t.owned = nullptr;
     }
-    if (o.owned != fin) drop(fin, kSmallFin);
-    if (counted) {
-      // the step is counted: its outputs are written as any expansion's
-      release(t);
-      t = o;
-      settled = false;
-      if (si < res->n_steps) res->step_in[si] += t.n;
-      add_out(si, m);
-      expand_write(si, tp, orient, t, rem & ~(1u << tp), (const int64_t*)((char*)work + kSmallOffs),
-                   start, m);
-      if (o.owned != work) drop(work, kSmallWork);
-      return true;
-    }
-    if (o.owned != work) drop(work, kSmallWork);
+    if (own && !keep_fin) drop(sm.fin, kSmallFin);
+    const bool counted = r.status == kSmallWrite;
+    if (own && !keep_work && !counted) drop(sm.work, sm.work_bytes);
     release(t);
     t = o;
+    if (counted) {
+      // the step is counted: its outputs are written as any expansion's
+      settled = false;
+      if (si < res->n_steps) res->step_in[si] += t.n;
+      add_out(si, r.m);
+      const uint32_t next = rem & ~(1u << r.tp);
+      if (written || one_piece(r)) {
+        Table x;
+        if (written) {
+          x = *written;
+        } else {
+          SmallWriteTask w;
+          prepare_write(r, offs, w, x);
+          launch_small_write(&w, 1, r.m, write_bytes(r), s);
+        }
+        run(si + 1, x, next);
+        release(t);
+      } else {
+        expand_write(si, r.tp, r.orient, t, next, offs, r.start, r.m);
+      }
+      if (own && !keep_work) drop(sm.work, sm.work_bytes);
+      return true;
+    }
     if (!done) return false;
     if (t.n > 0) emit(t);
     return true;
@@ -870,14 +986,157 @@ bool run_query(gsmat_store* st, const gsmat_query_plan* pl, int64_t budget_bytes
   Table unit;
   unit.n = 1;
   unit.k = 0;
-  const uint32_t all = pl->pats.size() >= 32 ? 0xFFFFFFFFu : ((1u << pl->pats.size()) - 1);
   try {
-    ex.run(0, unit, all);
+    ex.run(0, unit, all_of(pl));
   } catch (...) {
     ex.release_all();
     throw;
   }
   return ex.settled;
+}
+
+void run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int32_t nq,
+                     int64_t budget, int64_t round_budget, int64_t max_rows, hipStream_t s,
+                     std::vector<DevQueryOut>& out) {
+  out.assign(nq, DevQueryOut{nullptr, kDevFallback, GSMAT_OK});
+  struct One {
+    int q;  // the query
+    std::unique_ptr<gsmat_result> res;
+    std::unique_ptr<Exec> ex;
+    Table t;
+    Exec::SmallMem sm;
+    Table w;            // its counted expansion's table ...
+    bool made = false;  // ... when that is written by the batch's launch
+    bool skip = false;  // left to the rounds
+  };
+  std::vector<One> v;
+  v.reserve(nq);
+  int mp = 1;
+  for (int i = 0; i < nq; ++i) {
+    const gsmat_query_plan* pl = plans[i];
+    One o;
+    o.q = i;
+    o.res.reset(new gsmat_result);
+    o.res->st = st;
+    o.res->stream = s;
+    o.res->n_vars = pl->n_vars;
+    o.res->reset_steps(pl->steps.size());
+    bool absent = false;
+    for (const gsmat_pattern& q : pl->pats)
+      absent |= q.p >= st->P || (!is_var(q.s) && q.s >= st->V) || (!is_var(q.o) && q.o >= st->V);
+    if (absent) {  // matches nothing
+      out[i] = DevQueryOut{o.res.release(), kDevDone, GSMAT_OK};
+      continue;
+    }
+    o.ex.reset(new Exec{st, pl, s, budget, max_rows, o.res.get(), pl->mode == GSMAT_PLAN_ADAPTIVE});
+    o.t.n = 1;
+    o.t.k = 0;
+    if (!o.ex->small_first()) continue;
+    mp = std::max(mp, (int)pl->pats.size());
+    v.push_back(std::move(o));
+  }
+  if (v.empty()) return;
+  const int n = (int)v.size();
+  // a pattern after the first adds one variable at most; sizes in steps, so that
+  // batches of about one size share the allocator's blocks
+  mp = (mp + 7) / 8 * 8;
+  const SmallLayout l(mp, mp + 1);
+  DeviceMem* mem = st->mem.get();
+  std::shared_ptr<Arena> work, fin;
+  try {
+    const size_t slots = (size_t)(n + 63) / 64 * 64;
+    work = std::make_shared<Arena>(mem, (size_t)l.bytes * slots, s);
+    fin = std::make_shared<Arena>(mem, (size_t)kSmallFin * slots, s);
+  } catch (const OomFail&) {
+    return;  // the rounds may need less
+  }
+  SmallReport* reps =
+      (SmallReport*)query_area().get((sizeof(SmallArgs) + sizeof(SmallReport) +
+                                      sizeof(SmallWriteTask)) * (size_t)n);
+  SmallArgs* args = (SmallArgs*)(reps + n);
+  for (int i = 0; i < n; ++i) {
+    One& o = v[i];
+    o.sm.work = (char*)work->p + (size_t)l.bytes * i;
+    o.sm.work_bytes = (size_t)l.bytes;
+    o.sm.fin = (char*)fin->p + (size_t)kSmallFin * i;
+    o.sm.work_hold = work;
+    o.sm.fin_hold = fin;
+    o.ex->fill_small(args[i], 0, o.t, all_of(plans[o.q]), l, o.sm);
+    reps[i].seq = 0;
+  }
+  const uint32_t seq = next_report();
+  launch_small(small_store(st), args, reps, n, seq, s);
+  for (int i = 0; i < n; ++i) host_wait_words(&reps[i].seq, 1, seq, s);
+  // Finished here: what is done, and what only has to be written (10 us of
+  // launches each, no wait).  A query left on the way costs the general path
+  // 50 us to 200 us, the rounds about 600 us for any number of them: up to four
+  // go on alone, more go to the rounds together, from the start.
+  int unfinished = 0;
+  auto left = [&](const SmallReport& r) {
+    return r.status == kSmallMore || (r.status == kSmallWrite && (r.rem & ~(1u << r.tp)) != 0);
+  };
+  for (int i = 0; i < n; ++i) unfinished += left(reps[i]);
+  // every write in one launch
+  int64_t written = 0, most = 0;
+  double alg = 0;
+  int nw = 0;
+  SmallWriteTask* tasks = (SmallWriteTask*)(args + n);
+  try {
+    for (int i = 0; i < n; ++i) {
+      One& o = v[i];
+      const SmallReport& r = reps[i];
+      const int64_t bytes = r.status == kSmallWrite ? 4 * col_stride(r.m) * (r.k + 1)
+                                                    : 4 * col_stride(r.n) * r.k;
+      o.skip = (left(r) && (unfinished > 4 || round_budget > 0)) ||
+               (round_budget > 0 && written + bytes > round_budget);
+      if (o.skip) continue;
+      written += bytes;
+      if (r.status != kSmallWrite || !o.ex->one_piece(r)) continue;
+      try {
+        o.ex->prepare_write(r, (const int64_t*)((char*)o.sm.work + l.offs), tasks[nw], o.w);
+      } catch (const OomFail&) {
+        o.skip = true;
+        continue;
+      }
+      o.made = true;
+      most = std::max(most, r.m);
+      alg += Exec::write_bytes(r);
+      ++nw;
+    }
+    launch_small_write(tasks, nw, most, alg, s);
+  } catch (...) {
+    for (One& o : v) o.ex->release_all();
+    throw;
+  }
+  bool settled = nw == 0;
+  for (int i = 0; i < n; ++i) {
+    One& o = v[i];
+    const SmallReport& r = reps[i];
+    if (o.skip) continue;
+    int si = 0;
+    uint32_t rem = 0;
+    const gsmat_status rc = guarded([&]() -> gsmat_status {
+      try {
+        if (!o.ex->finish_small(r, (const int64_t*)((char*)o.sm.work + l.offs), o.sm, si, o.t, rem,
+                                o.made ? &o.w : nullptr))
+          o.ex->run(si, o.t, rem);
+      } catch (...) {
+        o.ex->release_all();
+        throw;
+      }
+      return GSMAT_OK;
+    });
+    settled &= rc == GSMAT_OK && o.ex->settled;
+    out[o.q] = rc == GSMAT_OK ? DevQueryOut{o.res.release(), kDevDone, GSMAT_OK}
+                              : DevQueryOut{nullptr, kDevFailed, rc};
+  }
+  try {
+    if (!settled) host_sync(s);
+  } catch (...) {
+    for (DevQueryOut& o : out) delete o.res;
+    out.clear();
+    throw;
+  }
 }
 
 void run_collect(gsmat_store* st, const gsmat_query_plan* pl, const Table* t0,
@@ -900,9 +1159,8 @@ void run_collect(gsmat_store* st, const gsmat_query_plan* pl, const Table* t0,
     t.k = 0;
   }
   const size_t first = out->size();
-  const uint32_t all = pl->pats.size() >= 32 ? 0xFFFFFFFFu : ((1u << pl->pats.size()) - 1);
   try {
-    ex.run(0, t, all);
+    ex.run(0, t, all_of(pl));
   } catch (...) {
     ex.release_all();
     for (size_t i = first; i < out->size(); ++i)
@@ -983,6 +1241,7 @@ extern "C" gsmat_status gsmat_plan(const gsmat_store* st, const gsmat_pattern* p
     gsmat_status rc = validate_patterns(pats, n_pats, &nv, &err);
     if (rc != GSMAT_OK) throw StatusFail{rc, err};
     if (!st->built) throw StatusFail{GSMAT_ESTATE, "index not built"};
+    (void)pinned();  // here, not in a join that must not allocate
     std::vector<gsmat_pat_lookup> lk;
     std::vector<TpStat> ts = pattern_stats(st, pats, n_pats, mode, (hipStream_t)stream, &lk);
     std::unique_ptr<gsmat_query_plan> pl(new gsmat_query_plan);

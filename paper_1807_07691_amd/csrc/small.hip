@@ -18,10 +18,12 @@
 // A step that is a Cartesian product or a (?x p ?x) scan, or that enters with
 // more than kSmallRows rows, is left to the general path, which goes on from
 // the table reported.  An expansion of more than kSmallRows rows, or an answer
-// above kSmallFin bytes, is counted here and written by the general path's
-// merge-path write into memory of its exact size: one CU writes about 50 GB/s,
-// the launch and wait cost 15 us.  4096 rows are 16 waves of 4 rows a lane.
+// above kSmallFin bytes, is counted here and written by k_small_write into
+// memory of its exact size: one CU writes about 50 GB/s, the launch and wait
+// cost 15 us.  4096 rows are 16 waves of 4 rows a lane.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "device.hpp"
 #include "small.hpp"
@@ -39,19 +41,24 @@ constexpr int kSChunk = 64 * kSU;   // rows per wave and chunk
 static_assert(kSmallRows == kSW * kSChunk, "one chunk per wave covers a table");
 static_assert(kSmallRows <= kSampleRows, "the candidates' sums must equal their samples");
 
+// What row lookups need of a predicate in one orientation.
+struct SmallPred {
+  const int32_t *keys, *ptr, *nbr, *dense, *dir;
+  int32_t nr, shift;
+};
+
 struct SmallList {
-  PredView pv;
   const int32_t* ids;
   int64_t len;
-  int32_t is_keys;
+  int32_t pred;  // row keys: the pattern (by subject), or kMaxPats + pattern; else -1
 };
 
 struct SmallLds {
-  int32_t P[kSmallRows + 1];  // output offset of every row
-  int32_t rb[kSmallRows];     // member base of every row, less its offset
-  SmallPat pat[kMaxPats];
+  int32_t P[kSmallRows];   // output offset of every row (before: candidates' lengths)
+  int32_t rb[kSmallRows];  // member base of every row, less its offset (before: starts)
+  SmallArgs a;
+  SmallPred pred[2 * kMaxPats];  // of pattern i by subject, by object at kMaxPats + i
   LookupRes lk[kMaxPats];
-  int32_t* dst[kMaxCols];
   const int32_t* col[kMaxCols];
   int32_t var[kMaxCols];
   int32_t col_of[kMaxCols];
@@ -76,7 +83,19 @@ __device__ inline char* s_place(const SmallArgs& A, int64_t bytes, bool last, in
   }
   *place = kAtWork;
   *next_half = half ^ 1;
-  return A.work + (half ^ 1) * kSmallTab;
+  return A.work + (half ^ 1) * A.tab;
+}
+
+__device__ inline PredView s_view(const SmallPred& p) {
+  PredView v{};
+  v.keys = p.keys;
+  v.ptr = p.ptr;
+  v.nbr = p.nbr;
+  v.dense = p.dense;
+  v.dir = p.dir;
+  v.nr = p.nr;
+  v.dir_shift = p.shift;
+  return v;
 }
 
 // Keeps the rows whose flag is set, in order: the wave's rows are
@@ -105,19 +124,37 @@ __device__ inline int s_rank(SmallLds& L, const bool (&keep)[kSU], int (&pos)[kS
   return tot;
 }
 
-__device__ __forceinline__ void small_join(const SmallArgs& A, SmallReport* rep, uint32_t seq,
-                                           SmallLds& L) {
+__global__ __launch_bounds__(kST) void k_small_join(SmallStore S,
+                                                    const SmallArgs* __restrict__ args,
+                                                    SmallReport* reps, uint32_t seq) {
+  __shared__ SmallLds L;
+  SmallReport* const rep = reps + blockIdx.x;
   const int tid = (int)threadIdx.x, lane = lane_id(), wave = wave_id();
+  {  // the query comes over in one trip to host memory
+    static_assert(sizeof(SmallArgs) % 4 == 0 && sizeof(SmallArgs) / 4 <= kST, "one word a thread");
+    const uint32_t* src = (const uint32_t*)(args + blockIdx.x);
+    if (tid < (int)(sizeof(SmallArgs) / 4)) ((uint32_t*)&L.a)[tid] = src[tid];
+  }
+  __syncthreads();
+  const SmallArgs& A = L.a;
   const int np = A.np;
   if (tid < np) {
     const SmallPat q = A.pats[tid];
-    L.pat[tid] = q;
     LookupRes r = A.lk[tid];
     if (!(A.lk_valid >> tid & 1) && (q.s >= 0 || q.o >= 0)) {
       LookupReq lq{q.s >= 0 ? 0 : 1, q.p, q.s >= 0 ? q.s : q.o, q.s >= 0 && q.o >= 0 ? q.o : -1};
-      r = lookup_one(lq, A.dout, A.din, A.out, A.in);
+      r = lookup_one(lq, S.dout, S.din, S.out, S.in);
     }
     L.lk[tid] = r;
+  }
+  // the predicates' descriptors, by two waves while the first looks up
+  if (wave == 1 || wave == 2) {
+    if (lane < np) {
+      const PredView v = wave == 1 ? view_of(S.dout[A.pats[lane].p], S.out)
+                                   : view_of(S.din[A.pats[lane].p], S.in);
+      L.pred[(wave - 1) * kMaxPats + lane] =
+          SmallPred{v.keys, v.ptr, v.nbr, v.dense, v.dir, v.nr, v.dir_shift};
+    }
   }
   if (tid < kMaxPats + 1) L.in[tid] = L.out[tid] = 0;
   if (tid < kMaxCols) {
@@ -143,7 +180,7 @@ __device__ __forceinline__ void small_join(const SmallArgs& A, SmallReport* rep,
   uint64_t bound = 0;
   for (int c = 0; c < k; ++c) bound |= 1ull << L.var[c];
 
-  const SmallPat my = lane < np ? L.pat[lane] : SmallPat{0, 0, 0};
+  const SmallPat my = lane < np ? A.pats[lane] : SmallPat{0, 0, 0};
   for (;;) {
     if (n == 0 || rem == 0) {
       status = kSmallDone;
@@ -178,23 +215,22 @@ __device__ __forceinline__ void small_join(const SmallArgs& A, SmallReport* rep,
       if (kind == GSMAT_STEP_EXPAND) {
         cmask = 1u << tp;
         smask = sp.orient == 0 ? cmask : 0u;
-        const int32_t b = sp.orient == 0 ? L.pat[tp].s : L.pat[tp].o;
+        const int32_t b = sp.orient == 0 ? A.pats[tp].s : A.pats[tp].o;
         if (b >= 0 || !(bound >> (-b - 1) & 1)) break;
       }
     }
 
     if (kind == GSMAT_STEP_SCAN || kind == GSMAT_STEP_CARTESIAN) {
-      const SmallPat q = L.pat[tp];
+      const SmallPat q = A.pats[tp];
       if (!unit || (q.s < 0 && q.s == q.o)) break;
       const LookupRes lk = L.lk[tp];
       __syncthreads();
       if (q.s < 0 && q.o < 0) {
-        const PredDesc d = A.dout[q.p];
-        n = d.nnz;
+        n = S.dout[q.p].nnz;
         k = 2;
         if (tid == 0) {
-          L.col[0] = A.out_src + d.nbr_base;
-          L.col[1] = A.out.nbr + d.nbr_base;
+          L.col[0] = S.out_src + S.dout[q.p].nbr_base;
+          L.col[1] = L.pred[tp].nbr;
           L.var[0] = -q.s - 1;
           L.var[1] = -q.o - 1;
           L.col_of[-q.s - 1] = 0;
@@ -208,8 +244,7 @@ __device__ __forceinline__ void small_join(const SmallArgs& A, SmallReport* rep,
         n = lk.len;
         k = 1;
         if (tid == 0) {
-          L.col[0] = (q.s >= 0 ? A.out.nbr + A.dout[q.p].nbr_base : A.in.nbr + A.din[q.p].nbr_base) +
-                     lk.start;
+          L.col[0] = L.pred[q.s >= 0 ? tp : kMaxPats + tp].nbr + lk.start;
           L.var[0] = v;
           L.col_of[v] = 0;
         }
@@ -234,17 +269,16 @@ __device__ __forceinline__ void small_join(const SmallArgs& A, SmallReport* rep,
       const int nl = (int)__popcll(mm);
       if (nl > kMaxLists || nl < 1) break;
       if (wave == 0 && mem) {
-        SmallList l{};
+        SmallList l;
         const bool subj = my.s == cterm;  // the centre is the subject
         if (subj ? my.o < 0 : my.s < 0) {
-          l.pv = subj ? view_of(A.dout[my.p], A.out) : view_of(A.din[my.p], A.in);
-          l.is_keys = 1;
-          l.len = l.pv.nr;
-          l.ids = l.pv.keys;
+          l.pred = subj ? lane : kMaxPats + lane;
+          l.len = L.pred[l.pred].nr;
+          l.ids = L.pred[l.pred].keys;
         } else {
-          const LookupRes r = L.lk[lane];
-          l.ids = (subj ? A.in.nbr + A.din[my.p].nbr_base : A.out.nbr + A.dout[my.p].nbr_base) + r.start;
-          l.len = r.len;
+          l.pred = -1;
+          l.len = L.lk[lane].len;
+          l.ids = L.pred[subj ? kMaxPats + lane : lane].nbr + L.lk[lane].start;
         }
         L.list[mbcnt(mm)] = l;
       }
@@ -267,8 +301,8 @@ __device__ __forceinline__ void small_join(const SmallArgs& A, SmallReport* rep,
       for (int i = 0; i < nl; ++i) {
         if (i == d) continue;
         int32_t a[kSU], b[kSU];
-        if (L.list[i].is_keys) {
-          const PredView pv = L.list[i].pv;
+        if (L.list[i].pred >= 0) {
+          const PredView pv = s_view(L.pred[L.list[i].pred]);
           row_lookup_n<kSU>(pv, x, keep, a, b);
 #pragma unroll
           for (int u = 0; u < kSU; ++u) keep[u] = keep[u] && b[u] > 0;
@@ -317,7 +351,7 @@ __device__ __forceinline__ void small_join(const SmallArgs& A, SmallReport* rep,
     }
 
     if (kind == GSMAT_STEP_FILTER) {
-      const SmallPat q = L.pat[tp];
+      const SmallPat q = A.pats[tp];
       const uint32_t next = rem & ~(1u << tp);
       int64_t m = n;
       if (q.s >= 0 && q.o >= 0) {
@@ -327,7 +361,7 @@ __device__ __forceinline__ void small_join(const SmallArgs& A, SmallReport* rep,
         if ((q.s < 0 && cs < 0) || (q.o < 0 && co < 0)) break;
         const int32_t* sc = cs >= 0 ? L.col[cs] : nullptr;
         const int32_t* oc = co >= 0 ? L.col[co] : nullptr;
-        const PredView pv = view_of(A.dout[q.p], A.out);
+        const PredView pv = s_view(L.pred[tp]);
         int32_t sv[kSU], ov[kSU], st[kSU], len[kSU], lo[kSU], cnt[kSU];
         bool keep[kSU];
         int pos[kSU];
@@ -379,21 +413,23 @@ __device__ __forceinline__ void small_join(const SmallArgs& A, SmallReport* rep,
 
     if (kind != GSMAT_STEP_EXPAND || k + 1 > kMaxCols) break;
     // every candidate's row extents and output size
-    int32_t* const starts = (int32_t*)(A.work + kSmallStarts);
-    int32_t* const lens = (int32_t*)(A.work + kSmallLens);
     const int nc = __popc(cmask);
+    const int per = (int)((n + kSChunk - 1) / kSChunk);  // chunks of a candidate
+    // kept in LDS when a chunk a wave covers them all
+    const bool in_lds = nc * per <= kSW;
+    const int cstride = in_lds ? per * kSChunk : (int)kSmallRows;
+    int32_t* const starts = in_lds ? L.rb : (int32_t*)(A.work + A.starts);
+    int32_t* const lens = in_lds ? L.P : (int32_t*)(A.work + A.lens);
     if (wave == 0 && (cmask >> (lane & 31) & 1) && lane < 32) L.cand[mbcnt(cmask)] = lane;
     if (tid < kMaxPats) L.tot[tid] = 0;
     __syncthreads();
-    const int per = (int)((n + kSChunk - 1) / kSChunk);
     for (int qi = wave; qi < nc * per; qi += kSW) {
       const int c = qi / per, row0 = (qi - c * per) * kSChunk;
-      const int ct = __builtin_amdgcn_readfirstlane(L.cand[c]);
-      const SmallPat q = L.pat[ct];
+      const int ct = L.cand[c];
+      const SmallPat q = A.pats[ct];
       const bool from_s = smask >> ct & 1;
       const int32_t* col = L.col[L.col_of[from_s ? -q.s - 1 : -q.o - 1]];
-      const int32_t pr = __builtin_amdgcn_readfirstlane(q.p);
-      const PredView pv = from_s ? view_of(A.dout[pr], A.out) : view_of(A.din[pr], A.in);
+      const PredView pv = s_view(L.pred[from_s ? ct : kMaxPats + ct]);
       int32_t v[kSU], st[kSU], len[kSU];
       bool ok[kSU];
 #pragma unroll
@@ -406,9 +442,9 @@ __device__ __forceinline__ void small_join(const SmallArgs& A, SmallReport* rep,
       int64_t loc = 0;
 #pragma unroll
       for (int u = 0; u < kSU; ++u) {
-        const int r = row0 + u * 64 + lane;  // below kSmallRows
-        starts[c * kSmallRows + r] = st[u];
-        lens[c * kSmallRows + r] = len[u];
+        const int r = row0 + u * 64 + lane;  // below per * kSChunk
+        starts[c * cstride + r] = st[u];
+        lens[c * cstride + r] = len[u];
         loc += len[u];
       }
       loc = wave_sum(loc);
@@ -420,7 +456,7 @@ __device__ __forceinline__ void small_join(const SmallArgs& A, SmallReport* rep,
       if (L.tot[c] < L.tot[best]) best = c;
     const int64_t m = (int64_t)L.tot[best];
     tp = L.cand[best];
-    const SmallPat q = L.pat[tp];
+    const SmallPat q = A.pats[tp];
     const bool from_s = smask >> tp & 1;
     const int nv = from_s ? -q.o - 1 : -q.s - 1;
     const uint32_t next = rem & ~(1u << tp);
@@ -435,8 +471,8 @@ __device__ __forceinline__ void small_join(const SmallArgs& A, SmallReport* rep,
       for (int u = 0; u < 4; ++u) {
         const int r = tid * 4 + u;
         const bool ok = r < n;
-        len[u] = ok ? lens[best * kSmallRows + r] : 0;
-        st[u] = ok ? starts[best * kSmallRows + r] : 0;
+        len[u] = ok ? lens[best * cstride + r] : 0;
+        st[u] = ok ? starts[best * cstride + r] : 0;
         sum += len[u];
       }
       const int64_t inc = wave_incl_scan(sum);
@@ -447,11 +483,15 @@ __device__ __forceinline__ void small_join(const SmallArgs& A, SmallReport* rep,
       for (int w = 0; w < kSW; ++w)
         if (w < wave) ex += L.wsum64[w];
       if (leave) {
-        int64_t* const offs = (int64_t*)(A.work + kSmallOffs);
+        int64_t* const offs = (int64_t*)(A.work + A.offs);
+        int32_t* const sts = (int32_t*)(A.work + A.starts);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const int r = tid * 4 + u;
-          if (r < n) offs[r] = ex;
+          if (r < n) {
+            offs[r] = ex;
+            sts[r] = st[u];
+          }
           ex += len[u];
         }
         if (tid == 0) offs[n] = m;
@@ -459,7 +499,7 @@ __device__ __forceinline__ void small_join(const SmallArgs& A, SmallReport* rep,
         left_tp = tp;
         left_orient = from_s ? 0 : 1;
         left_m = m;
-        left_start = starts + best * kSmallRows;
+        left_start = sts;
         break;
       }
 #pragma unroll
@@ -474,7 +514,7 @@ __device__ __forceinline__ void small_join(const SmallArgs& A, SmallReport* rep,
       int pl = place, hf = half;
       int32_t* const o = (int32_t*)s_place(A, 4 * stride * (k + 1), next == 0, half, &pl, &hf);
       __syncthreads();
-      const int32_t* nbr = from_s ? A.out.nbr + A.dout[q.p].nbr_base : A.in.nbr + A.din[q.p].nbr_base;
+      const int32_t* nbr = L.pred[from_s ? tp : kMaxPats + tp].nbr;
       int top = 1;
       while (top * 2 < (int)n) top *= 2;
       for (int j0 = tid; j0 < (int)m; j0 += kST * kSU) {
@@ -557,17 +597,120 @@ __device__ __forceinline__ void small_join(const SmallArgs& A, SmallReport* rep,
   }
 }
 
-__global__ __launch_bounds__(kST) void k_small_join(SmallArgs A, SmallReport* rep, uint32_t seq) {
-  __shared__ SmallLds L;
-  small_join(A, rep, seq, L);
+// The outputs of counted expansions: blockIdx.y is the task, the workgroups of
+// a row stride over its tiles of kTile outputs.  With at most kSmallRows rows
+// the tile's rows are found by two searches of a wave over the offsets (64 at
+// a time, two rounds) and staged in LDS, so no split kernel and no path over
+// the rows comes before the outputs.
+struct SmallWriteLds {
+  SmallWriteTask t;
+  int32_t end[kSmallRows];  // offset of the row after, from the tile's first output
+  int32_t rb[kSmallRows];   // member base, likewise
+  int32_t lim[2];
+};
+
+__global__ __launch_bounds__(kBlock) void k_small_write(SmallWriteTask one,
+                                                        const SmallWriteTask* __restrict__ many) {
+  __shared__ SmallWriteLds L;
+  const int tid = (int)threadIdx.x, lane = lane_id(), wave = wave_id();
+  static_assert(sizeof(SmallWriteTask) % 4 == 0 && sizeof(SmallWriteTask) / 4 <= kBlock,
+                "one word a thread");
+  if (many) {
+    if (tid < (int)(sizeof(SmallWriteTask) / 4))
+      ((uint32_t*)&L.t)[tid] = ((const uint32_t*)(many + blockIdx.y))[tid];
+  } else if (tid == 0) {
+    L.t = one;
+  }
+  __syncthreads();
+  const int n = L.t.n, k = L.t.k;
+  const int64_t m = L.t.m, stride = L.t.stride;
+  const int64_t* const offs = L.t.offs;
+  const int32_t* const nbr = L.t.nbr;
+  for (int64_t j0 = (int64_t)blockIdx.x * kTile; j0 < m; j0 += (int64_t)gridDim.x * kTile) {
+    const int nj = (int)min((int64_t)kTile, m - j0);
+    if (wave < 2) {  // the rows of the tile's first and last output
+      const int64_t j = wave == 0 ? j0 : j0 + nj - 1;
+      int lo = 0, len = n;  // the last row with offs <= j is in [lo, lo + len)
+      while (len > 1) {
+        const int step = (len + 63) / 64;
+        const int i = lo + lane * step;
+        const bool le = i < lo + len && offs[i] <= j;  // lanes' rows ascend: a prefix holds
+        const int c = (int)__popcll(__ballot(le));
+        lo += (c - 1) * step;
+        len = min(step, n - lo);
+      }
+      if (lane == 0) L.lim[wave] = lo;
+    }
+    __syncthreads();
+    const int r0 = L.lim[0], nr = L.lim[1] - r0 + 1;
+    for (int i = tid; i < nr; i += kBlock) {
+      const int64_t e = offs[r0 + i + 1] - j0;
+      L.end[i] = e > kTile ? kTile : (int32_t)e;
+      L.rb[i] = (int32_t)((int64_t)L.t.start[r0 + i] + (j0 - offs[r0 + i]));
+    }
+    __syncthreads();
+    int top = 1;
+    while (top * 2 < nr) top *= 2;
+    constexpr int U = 4;
+    int32_t* const o = L.t.out + j0;
+    for (int q = tid; q < nj; q += kBlock * U) {
+      int r[U], v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) r[u] = 0;
+      // the first row whose end is past the output
+      for (int sft = top; sft > 0; sft >>= 1) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int t = r[u] + sft;
+          if (t < nr && L.end[t - 1] <= q + u * kBlock) r[u] = t;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int j = q + u * kBlock;
+        v[u] = j < nj ? nbr[L.rb[r[u]] + j] : 0;
+      }
+      for (int c = 0; c < k; ++c) {
+        const int32_t* src = L.t.col[c] + r0;
+        int32_t x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = src[r[u]];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (q + u * kBlock < nj)
+            __builtin_nontemporal_store(x[u], &o[c * stride + q + u * kBlock]);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (q + u * kBlock < nj)
+          __builtin_nontemporal_store(v[u], &o[k * stride + q + u * kBlock]);
+    }
+    __syncthreads();  // the next tile reuses the LDS
+  }
 }
 
 }  // namespace
 
-void launch_small(const SmallArgs& a, SmallReport* rep, uint32_t seq, hipStream_t s) {
+void launch_small_write(const SmallWriteTask* tasks, int n, int64_t most, double bytes,
+                        hipStream_t s) {
+  if (n <= 0) return;
+  // enough workgroups to fill the device; few tasks take more each
+  const int64_t cap = std::max<int64_t>(16, 4096 / n);
+  const unsigned gx = (unsigned)std::min<int64_t>(std::max<int64_t>(ceil_div(most, kTile), 1), cap);
+  const bool prof = prof_on(GSMAT_K_WRITE);
+  if (prof) prof_begin(s, GSMAT_K_WRITE);
+  hipLaunchKernelGGL(k_small_write, dim3(gx, (unsigned)n), dim3(kBlock), 0, s, tasks[0],
+                     n > 1 ? tasks : nullptr);
+  GS_HIP(hipGetLastError());
+  if (prof) prof_end(s, GSMAT_K_WRITE, bytes);
+}
+
+void launch_small(const SmallStore& st, const SmallArgs* args, SmallReport* reps, int n,
+                  uint32_t seq, hipStream_t s) {
+  if (n <= 0) return;
   const bool prof = prof_on(GSMAT_K_OTHER);
   if (prof) prof_begin(s, GSMAT_K_OTHER);
-  hipLaunchKernelGGL(k_small_join, dim3(1), dim3(kST), 0, s, a, rep, seq);
+  hipLaunchKernelGGL(k_small_join, dim3((unsigned)n), dim3(kST), 0, s, st, args, reps, seq);
   GS_HIP(hipGetLastError());
   if (prof) prof_end(s, GSMAT_K_OTHER, 0.0);
 }

@@ -7,14 +7,22 @@
 namespace gsmat {
 
 constexpr int64_t kSmallRows = 4096;        // rows of a table inside the launch
-constexpr int64_t kSmallTab = 4 * kSmallRows * kMaxCols;  // bytes of such a table
 constexpr int64_t kSmallFin = 64 << 10;     // bytes of a final table of its own
-// The work area: two tables, the row starts and lengths of every candidate
-// expansion, and the output offsets of an expansion left to be written.
-constexpr int64_t kSmallStarts = 2 * kSmallTab;
-constexpr int64_t kSmallLens = kSmallStarts + (int64_t)kMaxPats * kSmallRows * 4;
-constexpr int64_t kSmallOffs = kSmallLens + (int64_t)kMaxPats * kSmallRows * 4;
-constexpr int64_t kSmallWork = kSmallOffs + (kSmallRows + 32) * 8;
+
+// Offsets in a query's work area: two tables of up to `cols` columns (the
+// first at 0, the second at tab), the row starts and lengths of every
+// candidate expansion, and the output offsets of an expansion left to be
+// written.
+struct SmallLayout {
+  int64_t tab, starts, lens, offs, bytes;
+  SmallLayout(int np, int cols) {
+    tab = 4 * kSmallRows * (cols < 1 ? 1 : cols > kMaxCols ? kMaxCols : cols);
+    starts = 2 * tab;
+    lens = starts + 4 * kSmallRows * np;
+    offs = lens + 4 * kSmallRows * np;
+    bytes = offs + 8 * (kSmallRows + 32);
+  }
+};
 
 enum : int32_t { kSmallDone = 1, kSmallMore = 2, kSmallWrite = 3 };
 // where a reported table's columns are: where they were at the start (or in
@@ -37,11 +45,8 @@ struct SmallArgs {
   uint32_t rem;
   int64_t n;
   int64_t budget;
-  const PredDesc* dout;
-  const PredDesc* din;
-  OriPtrs out, in;
-  const int32_t* out_src;
-  char* work;       // kSmallWork bytes
+  char* work;       // laid out by these (SmallLayout)
+  int64_t tab, starts, lens, offs;
   char* fin;        // kSmallFin bytes
   SmallPat pats[kMaxPats];
   SmallStep steps[kMaxPats + 1];
@@ -56,7 +61,7 @@ struct SmallArgs {
 // none).  kSmallMore: it is the table before step si, which the general path
 // takes on from there.  kSmallWrite: likewise, but step si has been counted:
 // an expansion of pattern tp (orient 0 from its subject) with m rows, its
-// offsets (int64) at kSmallOffs of the work area and its rows' starts at start.
+// offsets (int64) at `offs` of the work area and its rows' starts at start.
 struct SmallReport {
   int64_t n;
   int32_t k, si;
@@ -70,8 +75,36 @@ struct SmallReport {
   uint32_t seq;  // written last
 };
 
-// Runs one query from a.rem / a.si on; rep (host memory the device can write,
-// or device memory) is complete once rep->seq == seq.
-void launch_small(const SmallArgs& a, SmallReport* rep, uint32_t seq, hipStream_t s);
+// The store, alike for every query of a launch.
+struct SmallStore {
+  const PredDesc* dout;
+  const PredDesc* din;
+  OriPtrs out, in;
+  const int32_t* out_src;
+};
+
+// Runs n queries, each from its a.rem / a.si on in a workgroup of its own.
+// args and reps are host memory the device can reach; reps[i] is complete once
+// reps[i].seq == seq.
+void launch_small(const SmallStore& st, const SmallArgs* args, SmallReport* reps, int n,
+                  uint32_t seq, hipStream_t s);
+
+// An expansion counted by a small join: output j < m belongs to the last of
+// the n <= kSmallRows rows whose offset is at most j.  Column c of the output
+// is at out + c * stride.
+struct SmallWriteTask {
+  const int64_t* offs;
+  const int32_t* start;
+  const int32_t* nbr;
+  int32_t* out;
+  int64_t m, stride;
+  int32_t n, k;
+  const int32_t* col[kMaxCols];
+};
+
+// Writes n counted expansions, `most` rows the largest; tasks is host memory
+// the device can reach (n = 1: passed by value).
+void launch_small_write(const SmallWriteTask* tasks, int n, int64_t most, double bytes,
+                        hipStream_t s);
 
 }  // namespace gsmat

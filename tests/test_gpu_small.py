@@ -87,3 +87,54 @@ def test_small_joins(G, n, fan):
                 b.close()
                 pl.close()
     st.close()
+
+
+@pytest.mark.parametrize("n,fan,count", [(63, 3, 10), (ROWS, 1, 10), (ROWS + 1, 2, 60), (700, 7, 512),
+                                         (700, 7, 513), (2341, 2, 30)])
+def test_small_batches(G, n, fan, count):
+    """Batches around the size that first runs in one launch: rows, order and
+    counters as in the host-driven rounds, also where most queries are left to
+    the rounds, and through the server."""
+    s, p, o, V, P = graph(n, fan, n + fan)
+    st = G.gsmat_load_triples(s, p, o, V, P)
+    G.gsmat_build_index(st)
+    queries = [QUERIES[i % len(QUERIES)] for i in range(count)]
+    for mode, budget in ((G.PLAN_ADAPTIVE, 0), (G.PLAN_ADAPTIVE, 40_000), (G.PLAN_DEFAULT, 0),
+                         (G.PLAN_PAPER, 0)):
+        plans, _ = G.gsmat_plan_batch(st, queries, mode)
+        G.gsmat_set_batch_engine(st, G.ENGINE_HOST)
+        want, _ = G.gsmat_join_batch(st, plans[:len(QUERIES)], budget)
+        rows = [G.gsmat_fetch_bindings(r) for r in want]
+        info = [G.gsmat_result_info(r) for r in want]
+        G.gsmat_set_batch_engine(st, G.ENGINE_DEVICE)
+        print(f"[gpu] small batch n={n} count={count} mode={mode} budget={budget}", flush=True)
+        a, _ = G.gsmat_join_batch(st, plans, budget)
+        b, _ = G.gsmat_join_batch_bgp(st, queries, mode, budget)
+        sv = G.gsmat_server_new(st, 0, budget, -1, 4096)
+        for i, pl in enumerate(plans):
+            G.gsmat_server_submit(sv, pl, i)
+        c = {}
+        while len(c) < count:
+            G.gsmat_server_step(sv)
+            for tag, r, status in G.gsmat_server_poll(sv, count):
+                assert status == 0
+                c[tag] = r
+        for i in range(count):
+            w, wi = rows[i % len(QUERIES)], info[i % len(QUERIES)]
+            for r in (a[i], b[i], c[i]):
+                assert np.array_equal(G.gsmat_fetch_bindings(r), w), (i, mode)
+                gi = G.gsmat_result_info(r)
+                assert gi["step_rows_out"] == wi["step_rows_out"], (i, mode)
+                assert gi["step_rows_in"] == wi["step_rows_in"], (i, mode)
+                r.close()
+        sv.close()
+        for x in plans + want:
+            x.close()
+        # a row limit fails only the queries above it
+        lim = sorted(len(w) for w in rows)[len(rows) // 2]
+        res, stat = G.gsmat_join_batch_bgp(st, queries, mode, 0, lim, raise_on_error=False)
+        for i in range(count):
+            assert (stat[i] == G.GSMAT_ETOOBIG) == (len(rows[i % len(QUERIES)]) > lim), (i, mode)
+            if res[i] is not None:
+                res[i].close()
+    st.close()
