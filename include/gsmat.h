@@ -263,6 +263,8 @@ gsmat_status gsmat_join_batch(gsmat_store* st, const gsmat_query_plan* const* pl
  *     task that does not fit the regions waits a round; at the wait the host
  *     adds larger regions and runs the remaining rounds.  The batch's
  *     intermediate tables stay in device memory until its results are freed.
+ *     A batch of at most 512 queries first runs in one launch, a workgroup per
+ *     query, and only the queries whose tables outgrow it take the rounds.
  *   0 host-driven: the host builds every round's tasks and allocations from
  *     sizes read back twice per round (the serving loop always runs so).
  * EINVAL for another value. */
@@ -507,7 +509,8 @@ gsmat_status gsmat_parse_bgp(const gsmat_dict* d, const char* text, size_t len,
  * length of its predicate, capped by the Theorem 1 bound (Sec. 6.2).  Each
  * gsmat_server_step admits what fits and runs one step of every admitted
  * query as one batched round (as in gsmat_join_batch with host-driven
- * rounds), so queries that arrive while others run join them at the next
+ * rounds; four or more that have not started first run in one launch, which
+ * finishes those of few rows), so queries that arrive while others run join them at the next
  * round; when the server holds at most two queries, none started and none
  * waiting, the step instead runs the oldest to completion with the
  * single-query executor (the other waits for the next step; later arrivals
@@ -551,8 +554,8 @@ gsmat_status gsmat_release_pools(void);
 
 /* ---- instrumentation ----------------------------------------------------- */
 
-/* Rounds of the store's last device-driven gsmat_join_batch (at most 64
- * recorded): *n_rounds receives their number and out[8 * i + f] (for i <
+/* Rounds of the store's last device-driven gsmat_join_batch that took any (at
+ * most 64 recorded): *n_rounds receives their number and out[8 * i + f] (for i <
  * cap) round i's f-th figure: tasks counted, count tiles, post tiles
  * (row offsets, compacted rows, filter and intersection compactions), write
  * tiles, split entries, output bytes allocated, candidate expansions
