@@ -239,32 +239,36 @@ void launch_tile_reduce_u32(const uint32_t* x, int64_t n, int64_t* tile_sum, hip
 void launch_scan_add_u32(const uint32_t* x, int64_t n, const int64_t* tile_off, uint32_t* out,
                          hipStream_t s);
 
-// radix sort of 64-bit keys on their low nbits (LSD, 8-bit digits); result in keys
-void radix_sort_u64(uint64_t* keys, uint64_t* tmp, int64_t n, int nbits, DeviceMem& mem,
-                    hipStream_t s);
+// Stable sort of 64-bit keys on their bits [lo_bit, hi_bit) (the bits from
+// hi_bit up are zero); swap_vb > 0: of the keys (p, a, b) turned into (p, b, a),
+// a and b of swap_vb bits.  The result is in keys or tmp: returned.
+uint64_t* radix_sort_u64(uint64_t* keys, uint64_t* tmp, int64_t n, int lo_bit, int hi_bit,
+                         int swap_vb, DeviceMem& mem, hipStream_t s);
 
 // build
 void launch_pack_keys(const int32_t* s, const int32_t* p, const int32_t* o, int64_t n, int vb,
-                      uint64_t* k_by_s, uint64_t* k_by_o, hipStream_t st);
+                      uint64_t* k, hipStream_t st);
 void launch_flag_unique(const uint64_t* k, int64_t n, uint8_t* flags, int64_t* tile_sum,
                         hipStream_t s);
-void launch_flag_row_heads(const uint64_t* k, int64_t n, int vb, uint8_t* flags,
-                           int64_t* tile_sum, hipStream_t s);
 void launch_compact_u64(const uint64_t* in, const uint8_t* flags, int64_t n,
                         const int64_t* tile_off, uint64_t* out, hipStream_t s);
-void launch_compact_index(const uint8_t* flags, int64_t n, const int64_t* tile_off,
-                          int64_t* out_idx, hipStream_t s);
-void launch_split_members(const uint64_t* k, int64_t n, int vb, int32_t* nbr, int32_t* src,
-                          hipStream_t s);
-void launch_pred_heads(const uint64_t* k, const int64_t* row_pos, int64_t R, int vb,
-                       int64_t* pred_first_entry, int64_t* pred_first_row, hipStream_t s);
-void launch_fill_rows(const uint64_t* k, const int64_t* row_pos, int64_t R, int vb,
-                      const int64_t* pred_first_entry, int32_t* keys, int32_t* ptr,
+// rows of sorted distinct keys: tile sums of the row heads and every present
+// predicate's first entry; then (tile sums scanned) the rows and members, and
+// every present predicate's first row
+void launch_row_count(const uint64_t* k, int64_t n, int vb, int64_t* pfe, int64_t* tile_sum,
                       hipStream_t s);
+void launch_row_fill(const uint64_t* k, int64_t n, int vb, const int64_t* pfe,
+                     const int64_t* tile_off, int32_t* nbr, int32_t* src, int32_t* keys,
+                     int32_t* ptr, int64_t* pfr, hipStream_t s);
 void launch_fill_i64(int64_t* p, int64_t n, int64_t v, hipStream_t s);
-void launch_dense_ptr(PredView pv, int64_t V, int32_t* dense, hipStream_t s);
-// dir[b] = first row index with id >= b << shift, for b in [0, nb]
-void launch_row_dir(PredView pv, int32_t shift, int64_t nb, int32_t* dir, hipStream_t s);
+// dense row pointers and bucket directories of every predicate that has them:
+// first[p] is predicate p's first tile of kTile entries (alike for predicates
+// without entries and their successor), tiles their number
+void launch_dense_ptrs(const PredDesc* desc, const int64_t* first, int32_t P, int64_t tiles,
+                       const int32_t* keys, const int32_t* ptr, int64_t V, int32_t* dense,
+                       hipStream_t s);
+void launch_row_dirs(const PredDesc* desc, const int64_t* first, int32_t P, int64_t tiles,
+                     const int32_t* keys, int64_t V, int32_t* dir, hipStream_t s);
 // appends (row id, length) of every row with at least min_len members to
 // out[2 * i], out[2 * i + 1] for i < *count (count must start at 0)
 void launch_long_rows(PredView pv, int32_t min_len, int32_t* out, int32_t* count, int32_t cap,

@@ -187,6 +187,23 @@ __device__ inline int32_t lower_bound_i32(const int32_t* __restrict__ a, int32_t
   return lo;
 }
 
+// The same by a whole wave (alike in every lane): 64 elements are looked at
+// together, so n = 2 million takes 4 dependent loads instead of 21.
+__device__ inline int32_t wave_lower_bound(const int32_t* __restrict__ a, int32_t n, int32_t v) {
+  int32_t lo = 0, len = n;  // the answer is in [lo, lo + len]
+  while (len > 0) {
+    const int32_t step = (int32_t)(((int64_t)len + 63) / 64);
+    const int64_t i = (int64_t)lo + (int64_t)lane_id() * step;
+    const int c = (int)__popcll(__ballot(i < (int64_t)lo + len && a[i] < v));  // a prefix of lanes
+    if (c == 0) return lo;
+    // a[lo + (c - 1) * step] < v, and the next one looked at is not
+    const int32_t end = lo + len;
+    lo += (c - 1) * step + 1;
+    len = min(step - 1, end - lo);
+  }
+  return lo;
+}
+
 // Row of vertex v in one predicate's compressed matrix: (start, len), len 0
 // when v has no entry.
 __device__ inline void row_lookup(const PredView& pv, int32_t v, int32_t& start, int32_t& len) {

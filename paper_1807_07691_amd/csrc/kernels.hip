@@ -9,6 +9,8 @@
 // mbcnt, so output order equals input order.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "common.hpp"
 #include "device.hpp"
 
@@ -78,85 +80,157 @@ __global__ __launch_bounds__(kBlock) void k_tile_reduce_u32(const uint32_t* __re
 }
 
 // ---------------------------------------------------------------- radix sort
-__global__ __launch_bounds__(kBlock) void k_rs_hist(const uint64_t* __restrict__ keys, int64_t n,
-                                                    int shift, uint32_t* __restrict__ hist,
-                                                    int64_t nb) {
-  __shared__ uint32_t h[kWaves][256];
-  for (int i = threadIdx.x; i < kWaves * 256; i += kBlock) (&h[0][0])[i] = 0;
-  __syncthreads();
-  const int64_t tile0 = (int64_t)blockIdx.x * kTile;
-#pragma unroll
-  for (int j = 0; j < kItems; ++j) {
-    const int64_t i = tile0 + (int64_t)j * kBlock + threadIdx.x;
-    if (i < n) atomicAdd(&h[wave_id()][(keys[i] >> shift) & 255], 1u);
-  }
-  __syncthreads();
-  uint32_t c = 0;
-#pragma unroll
-  for (int w = 0; w < kWaves; ++w) c += h[w][threadIdx.x];
-  hist[(int64_t)threadIdx.x * nb + blockIdx.x] = c;
+// LSD radix sort of 64-bit keys, RB-bit digits.  A pass reads every key twice
+// (digit counts, then ranks) and writes it once.  What bounded it was the
+// write: ranks were exchanged through three barriers for every 256 keys and
+// each key went to its place on its own (1.6 TB/s).  A tile is now 4096 keys,
+// ranked by each wave on its own for 1024 keys in a row (no barrier), turned
+// into digit order in LDS and written as one run per digit: of 20 million
+// keys 203 -> 80 us a pass (4.0 TB/s), the counts 56 -> 38 us.
+constexpr int kRsItems = 16;
+constexpr int kRsTile = kBlock * kRsItems;  // keys
+constexpr int kRsWave = 64 * kRsItems;      // keys of a wave, consecutive
+
+// A key (p, a, b) as (p, b, a): vb bits each for a and b.
+__device__ inline uint64_t swap_ends(uint64_t k, int vb) {
+  const uint64_t m = (1ull << vb) - 1;
+  return (k >> (2 * vb) << (2 * vb)) | ((k & m) << vb) | ((k >> vb) & m);
 }
 
+// Digit counts of every tile: hist[digit * nb + tile].  kSwap: of the keys
+// with their ends swapped (as k_rs_scatter).
+template <int RB, bool kSwap>
+__global__ __launch_bounds__(kBlock) void k_rs_hist(const uint64_t* __restrict__ keys, int64_t n,
+                                                    int shift, int vb,
+                                                    uint32_t* __restrict__ hist, int64_t nb) {
+  constexpr int D = 1 << RB;
+  __shared__ uint32_t h[kWaves][D];
+  for (int i = threadIdx.x; i < kWaves * D; i += kBlock) (&h[0][0])[i] = 0;
+  __syncthreads();
+  const int64_t i0 = (int64_t)blockIdx.x * kRsTile + wave_id() * kRsWave + lane_id();
+  uint64_t k[kRsItems];
+#pragma unroll
+  for (int j = 0; j < kRsItems; ++j) k[j] = i0 + j * 64 < n ? keys[i0 + j * 64] : 0;
+#pragma unroll
+  for (int j = 0; j < kRsItems; ++j) {
+    const bool valid = i0 + j * 64 < n;
+    if (kSwap) k[j] = swap_ends(k[j], vb);
+    const uint32_t d = (uint32_t)(k[j] >> shift) & (D - 1);
+    // the high digits of sorted keys are alike in a wave: one add for all
+    const uint64_t live = __ballot(valid);
+    const uint32_t d0 = __builtin_amdgcn_readfirstlane(d);
+    if (__ballot(valid && d == d0) == live) {
+      if (lane_id() == 0 && live) atomicAdd(&h[wave_id()][d0], (uint32_t)__popcll(live));
+    } else if (valid) {
+      atomicAdd(&h[wave_id()][d], 1u);
+    }
+  }
+  __syncthreads();
+  for (int d = threadIdx.x; d < D; d += kBlock) {
+    uint32_t c = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) c += h[w][d];
+    hist[(int64_t)d * nb + blockIdx.x] = c;
+  }
+}
+
+template <int RB, bool kSwap>
 __global__ __launch_bounds__(kBlock) void k_rs_scatter(const uint64_t* __restrict__ in,
                                                        uint64_t* __restrict__ out, int64_t n,
-                                                       int shift,
+                                                       int shift, int vb,
                                                        const uint32_t* __restrict__ offs,
                                                        int64_t nb) {
-  __shared__ uint32_t base[256];
-  __shared__ uint32_t wcnt[kWaves][256];
-  base[threadIdx.x] = offs[(int64_t)threadIdx.x * nb + blockIdx.x];
-#pragma unroll
-  for (int w = 0; w < kWaves; ++w) wcnt[w][threadIdx.x] = 0;
+  constexpr int D = 1 << RB;
+  constexpr int DT = D / kBlock;  // digits per thread
+  static_assert(D % kBlock == 0, "every thread takes the same number of digits");
+  __shared__ uint64_t s[kRsTile];
+  __shared__ uint32_t cnt[kWaves][D];  // keys of the wave so far; then its first place in s
+  __shared__ uint32_t gb[D];           // first place of the digit's run, less its place in s
+  for (int i = threadIdx.x; i < kWaves * D; i += kBlock) (&cnt[0][0])[i] = 0;
   __syncthreads();
-  const int64_t tile0 = (int64_t)blockIdx.x * kTile;
+  const int64_t tile0 = (int64_t)blockIdx.x * kRsTile;
+  const int w = wave_id();
+  const int64_t i0 = tile0 + w * kRsWave + lane_id();
   const uint64_t lt = __lanemask_lt();
-  for (int j = 0; j < kItems; ++j) {
-    const int64_t i = tile0 + (int64_t)j * kBlock + threadIdx.x;
-    const bool valid = i < n;
-    const uint64_t k = valid ? in[i] : 0;
-    const uint32_t d = (uint32_t)(k >> shift) & 255u;
+  uint64_t k[kRsItems];
+  uint32_t rank[kRsItems];
+#pragma unroll
+  for (int j = 0; j < kRsItems; ++j) k[j] = i0 + j * 64 < n ? in[i0 + j * 64] : 0;
+#pragma unroll
+  for (int j = 0; j < kRsItems; ++j) {
+    const bool valid = i0 + j * 64 < n;
+    if (kSwap) k[j] = swap_ends(k[j], vb);
+    const uint32_t d = (uint32_t)(k[j] >> shift) & (D - 1);
     uint64_t peers = __ballot(valid);
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
+    for (int b = 0; b < RB; ++b) {
       const bool bit = (d >> b) & 1u;
       const uint64_t m = __ballot(bit);
       peers &= bit ? m : ~m;
     }
-    const uint32_t rank = (uint32_t)__popcll(peers & lt);
-    if (valid && (peers & lt) == 0) wcnt[wave_id()][d] = (uint32_t)__popcll(peers);
-    __syncthreads();
-    if (valid) {
-      uint32_t pos = base[d] + rank;
-      for (int w = 0; w < wave_id(); ++w) pos += wcnt[w][d];
-      out[pos] = k;
-    }
-    __syncthreads();
-    uint32_t add = 0;
+    const uint32_t before = (uint32_t)__popcll(peers & lt);
+    // the wave's keys of the digit before this round; one lane per digit adds
+    // this round's (the counts are the wave's own: its order is enough)
+    const uint32_t base = cnt[w][d];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (valid && before == 0) cnt[w][d] = base + (uint32_t)__popcll(peers);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    rank[j] = base + before;
+  }
+  __syncthreads();
+  // thread t's digits t * DT ...: their places in the tile, wave by wave
+  {
+    uint32_t c[kWaves][DT];
+    int64_t sum = 0;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      add += wcnt[w][threadIdx.x];
-      wcnt[w][threadIdx.x] = 0;
+    for (int q = 0; q < DT; ++q)
+#pragma unroll
+      for (int x = 0; x < kWaves; ++x) {
+        c[x][q] = cnt[x][threadIdx.x * DT + q];
+        sum += c[x][q];
+      }
+    int64_t tot;
+    uint32_t at = (uint32_t)block_excl_scan(sum, &tot);
+#pragma unroll
+    for (int q = 0; q < DT; ++q) {
+      const int d = threadIdx.x * DT + q;
+      gb[d] = offs[(int64_t)d * nb + blockIdx.x] - at;
+#pragma unroll
+      for (int x = 0; x < kWaves; ++x) {
+        cnt[x][d] = at;
+        at += c[x][q];
+      }
     }
-    base[threadIdx.x] += add;
-    __syncthreads();
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kRsItems; ++j)
+    if (i0 + j * 64 < n) s[cnt[w][(uint32_t)(k[j] >> shift) & (D - 1)] + rank[j]] = k[j];
+  __syncthreads();
+  const int m = (int)min((int64_t)kRsTile, n - tile0);
+#pragma unroll
+  for (int j = 0; j < kRsItems; ++j) {
+    const int i = j * kBlock + threadIdx.x;
+    if (i < m) {
+      const uint64_t x = s[i];
+      out[(uint32_t)(gb[(uint32_t)(x >> shift) & (D - 1)] + (uint32_t)i)] = x;
+    }
   }
 }
 
 // ---------------------------------------------------------------- index build
 __global__ void k_pack_keys(const int32_t* __restrict__ s, const int32_t* __restrict__ p,
                             const int32_t* __restrict__ o, int64_t n, int vb,
-                            uint64_t* __restrict__ ks, uint64_t* __restrict__ ko) {
+                            uint64_t* __restrict__ k) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const uint64_t pp = (uint64_t)(uint32_t)p[i] << (2 * vb);
-    const uint64_t ss = (uint32_t)s[i], oo = (uint32_t)o[i];
-    ks[i] = pp | (ss << vb) | oo;
-    ko[i] = pp | (oo << vb) | ss;
-  }
+       i += (int64_t)gridDim.x * blockDim.x)
+    k[i] = (uint64_t)(uint32_t)p[i] << (2 * vb) | (uint64_t)(uint32_t)s[i] << vb | (uint32_t)o[i];
 }
 
 __global__ __launch_bounds__(kBlock) void k_flag_adjacent(const uint64_t* __restrict__ k,
-                                                          int64_t n, int sh,
+                                                          int64_t n,
                                                           uint8_t* __restrict__ flags,
                                                           int64_t* __restrict__ ts) {
   const int64_t tile0 = (int64_t)blockIdx.x * kTile;
@@ -165,7 +239,7 @@ __global__ __launch_bounds__(kBlock) void k_flag_adjacent(const uint64_t* __rest
   for (int j = 0; j < kItems; ++j) {
     const int64_t i = tile0 + (int64_t)j * kBlock + threadIdx.x;
     if (i < n) {
-      const uint8_t f = (i == 0 || (k[i] >> sh) != (k[i - 1] >> sh)) ? 1 : 0;
+      const uint8_t f = (i == 0 || k[i] != k[i - 1]) ? 1 : 0;
       flags[i] = f;
       loc += f;
     }
@@ -184,51 +258,105 @@ __global__ __launch_bounds__(kBlock) void k_compact_u64(const uint64_t* __restri
       [&](int64_t i, int64_t pos) { out[pos] = in[i]; });
 }
 
-__global__ __launch_bounds__(kBlock) void k_compact_index(const uint8_t* __restrict__ flags,
-                                                          int64_t n,
-                                                          const int64_t* __restrict__ tile_off,
-                                                          int64_t* __restrict__ out) {
-  compact_tile(
-      blockIdx.x, n, tile_off[blockIdx.x], [&](int64_t i) { return flags[i] != 0; },
-      [&](int64_t i, int64_t pos) { out[pos] = i; });
-}
-
-__global__ void k_split_members(const uint64_t* __restrict__ k, int64_t n, int vb,
-                                int32_t* __restrict__ nbr, int32_t* __restrict__ src) {
-  const uint64_t vmask = (vb >= 64) ? ~0ull : ((1ull << vb) - 1);
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const uint64_t x = k[i];
-    nbr[i] = (int32_t)(x & vmask);
-    if (src) src[i] = (int32_t)((x >> vb) & vmask);
+// Rows of one orientation from its sorted distinct keys (p, row, member), in
+// two passes over them.  The first counts every tile's row heads and notes
+// each predicate's first entry; the second writes the member lists and, with
+// the heads' places, the row ids and offsets and each predicate's first row.
+// Each key is read twice and nothing else is kept per key or per row (before:
+// a flag per key, a position per row, five passes).  20 million keys: 216 ->
+// 126 us an orientation.
+__global__ __launch_bounds__(kBlock) void k_row_count(const uint64_t* __restrict__ k, int64_t n,
+                                                      int vb, int64_t* __restrict__ pfe,
+                                                      int64_t* __restrict__ ts) {
+  const int64_t tile0 = (int64_t)blockIdx.x * kTile;
+  uint64_t x[kItems], y[kItems];
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    const int64_t i = tile0 + (int64_t)j * kBlock + threadIdx.x;
+    x[j] = i < n ? k[i] : 0;
+    y[j] = i > 0 && i < n ? k[i - 1] : ~0ull;
   }
-}
-
-__global__ void k_pred_heads(const uint64_t* __restrict__ k, const int64_t* __restrict__ row_pos,
-                             int64_t R, int vb, int64_t* __restrict__ pfe,
-                             int64_t* __restrict__ pfr) {
-  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < R;
-       r += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = row_pos[r];
-    const uint64_t p = k[i] >> (2 * vb);
-    if (r == 0 || p != (k[row_pos[r - 1]] >> (2 * vb))) {
-      pfe[p] = i;
-      pfr[p] = r;
-    }
+  int64_t loc = 0;
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    const int64_t i = tile0 + (int64_t)j * kBlock + threadIdx.x;
+    if (i >= n) continue;
+    if (i == 0 || x[j] >> vb != y[j] >> vb) ++loc;
+    if (i == 0 || x[j] >> (2 * vb) != y[j] >> (2 * vb)) pfe[x[j] >> (2 * vb)] = i;
   }
+  const int64_t t = block_sum(loc);
+  if (threadIdx.x == 0) ts[blockIdx.x] = t;
 }
 
-__global__ void k_fill_rows(const uint64_t* __restrict__ k, const int64_t* __restrict__ row_pos,
-                            int64_t R, int vb, const int64_t* __restrict__ pfe,
-                            int32_t* __restrict__ keys, int32_t* __restrict__ ptr) {
+// Thread t takes the tile's keys 8t .. 8t + 7, so one scan of the heads'
+// counts places them and the members leave in 16-byte stores.
+__global__ __launch_bounds__(kBlock) void k_row_fill(const uint64_t* __restrict__ k, int64_t n,
+                                                     int vb, const int64_t* __restrict__ pfe,
+                                                     const int64_t* __restrict__ ts,
+                                                     int32_t* __restrict__ nbr,
+                                                     int32_t* __restrict__ src,
+                                                     int32_t* __restrict__ keys,
+                                                     int32_t* __restrict__ ptr,
+                                                     int64_t* __restrict__ pfr) {
+  static_assert(kItems == 8, "two 16-byte stores per thread");
   const uint64_t vmask = (1ull << vb) - 1;
-  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < R;
-       r += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = row_pos[r];
-    const uint64_t x = k[i];
-    const int64_t p = (int64_t)(x >> (2 * vb));
-    keys[r] = (int32_t)((x >> vb) & vmask);
-    ptr[r + p] = (int32_t)(i - pfe[p]);
+  const int64_t i0 = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kItems;
+  uint64_t x[kItems];
+  uint64_t prev = ~0ull;
+  const bool full = i0 + kItems <= n;
+  if (full) {
+#pragma unroll
+    for (int j = 0; j < kItems; j += 2) {
+      const ulonglong2 v = *reinterpret_cast<const ulonglong2*>(k + i0 + j);
+      x[j] = v.x;
+      x[j + 1] = v.y;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < kItems; ++j) x[j] = i0 + j < n ? k[i0 + j] : 0;
+  }
+  if (i0 > 0 && i0 < n) prev = k[i0 - 1];
+  uint32_t head = 0, phead = 0;
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    const uint64_t b = j ? x[j ? j - 1 : 0] : prev;
+    const bool first = i0 + j == 0;
+    if (i0 + j < n && (first || x[j] >> vb != b >> vb)) head |= 1u << j;
+    if (i0 + j < n && (first || x[j] >> (2 * vb) != b >> (2 * vb))) phead |= 1u << j;
+  }
+  int64_t tot;
+  int64_t r = ts[blockIdx.x] + block_excl_scan(__popc(head), &tot);
+  if (full) {
+    const int4 a = make_int4((int)(x[0] & vmask), (int)(x[1] & vmask), (int)(x[2] & vmask),
+                             (int)(x[3] & vmask));
+    const int4 b = make_int4((int)(x[4] & vmask), (int)(x[5] & vmask), (int)(x[6] & vmask),
+                             (int)(x[7] & vmask));
+    *reinterpret_cast<int4*>(nbr + i0) = a;
+    *reinterpret_cast<int4*>(nbr + i0 + 4) = b;
+    if (src) {
+      const int4 c = make_int4((int)(x[0] >> vb & vmask), (int)(x[1] >> vb & vmask),
+                               (int)(x[2] >> vb & vmask), (int)(x[3] >> vb & vmask));
+      const int4 d = make_int4((int)(x[4] >> vb & vmask), (int)(x[5] >> vb & vmask),
+                               (int)(x[6] >> vb & vmask), (int)(x[7] >> vb & vmask));
+      *reinterpret_cast<int4*>(src + i0) = c;
+      *reinterpret_cast<int4*>(src + i0 + 4) = d;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < kItems; ++j)
+      if (i0 + j < n) {
+        nbr[i0 + j] = (int32_t)(x[j] & vmask);
+        if (src) src[i0 + j] = (int32_t)(x[j] >> vb & vmask);
+      }
+  }
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    if (!(head >> j & 1)) continue;
+    const int64_t p = (int64_t)(x[j] >> (2 * vb));
+    keys[r] = (int32_t)(x[j] >> vb & vmask);
+    ptr[r + p] = (int32_t)(i0 + j - pfe[p]);
+    if (phead >> j & 1) pfr[p] = r;
+    ++r;
   }
 }
 
@@ -238,19 +366,109 @@ __global__ void k_fill_i64(int64_t* p, int64_t n, int64_t v) {
     p[i] = v;
 }
 
-__global__ void k_dense_ptr(PredView pv, int64_t V, int32_t* __restrict__ dense) {
-  for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v <= V;
-       v += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t r = (v >= (int64_t)INT32_MAX) ? pv.nr : lower_bound_i32(pv.keys, pv.nr, (int32_t)v);
-    dense[v] = pv.ptr[r];
+// Dense row pointers of every predicate that has them, one launch: tile b of
+// the launch is 2048 vertices of the predicate that owns it (first[p] its
+// first tile).  dense[v] is the offset of the first row >= v.  The tile's rows
+// are found by one search and marked in LDS, and a scan of the marks gives
+// every vertex its row, so a pointer costs no search of its own (before: a
+// launch per predicate and 20 dependent loads per pointer).  89 predicates of
+// 2 million vertices: 2.82 -> 0.33 ms (2.2 TB/s written).
+__global__ __launch_bounds__(kBlock) void k_dense_ptrs(const PredDesc* __restrict__ desc,
+                                                       const int64_t* __restrict__ first, int32_t P,
+                                                       const int32_t* __restrict__ keys,
+                                                       const int32_t* __restrict__ ptr, int64_t V,
+                                                       int32_t* __restrict__ dense) {
+  __shared__ int32_t mark[kTile];      // rows with this id; then rows before the vertex
+  __shared__ int32_t off[kTile + 1];   // offsets of the tile's rows
+  __shared__ int32_t lim[2];
+  const int64_t b = blockIdx.x;
+  int lo = 0, hi = P - 1;  // the last predicate with first <= b
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (first[mid] <= b) lo = mid;
+    else hi = mid - 1;
   }
+  const PredDesc d = desc[lo];
+  const int64_t v0 = (b - first[lo]) * kTile;
+  const int nv = (int)min((int64_t)kTile, V + 1 - v0);
+  const int32_t* const pk = keys + d.row_base;
+  const int32_t* const pp = ptr + d.ptr_base;
+  if (wave_id() < 2) {
+    const int64_t v = v0 + wave_id() * (int64_t)nv;
+    const int32_t r = wave_lower_bound(pk, (int32_t)d.nr, (int32_t)min(v, (int64_t)INT32_MAX));
+    if (lane_id() == 0) lim[wave_id()] = r;
+  }
+  for (int i = threadIdx.x; i < kTile; i += kBlock) mark[i] = 0;
+  __syncthreads();
+  const int r0 = lim[0], nr = lim[1] - r0;  // ids in [v0, v0 + nv): at most nv rows
+  for (int i = threadIdx.x; i <= nr; i += kBlock) off[i] = pp[r0 + i];
+  for (int i = threadIdx.x; i < nr; i += kBlock) mark[pk[r0 + i] - v0] = 1;
+  __syncthreads();
+  int32_t m[kItems];
+  int64_t sum = 0;
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    m[j] = mark[threadIdx.x * kItems + j];
+    sum += m[j];
+  }
+  int64_t tot;
+  int32_t ex = (int32_t)block_excl_scan(sum, &tot);
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    mark[threadIdx.x * kItems + j] = ex;
+    ex += m[j];
+  }
+  __syncthreads();
+  int32_t* const o = dense + d.dense_base + v0;
+  for (int i = threadIdx.x; i < nv; i += kBlock) o[i] = off[mark[i]];
 }
 
-__global__ void k_row_dir(PredView pv, int32_t shift, int64_t nb, int32_t* __restrict__ dir) {
-  for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b <= nb;
-       b += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t v = b << shift;
-    dir[b] = v >= (int64_t)INT32_MAX ? pv.nr : lower_bound_i32(pv.keys, pv.nr, (int32_t)v);
+// Bucket directories of the other predicates, one launch (tiles as above, of
+// 2048 buckets): dir[b] is the first row with id >= b << shift, searched among
+// the rows of the tile.
+__global__ __launch_bounds__(kBlock) void k_row_dirs(const PredDesc* __restrict__ desc,
+                                                     const int64_t* __restrict__ first, int32_t P,
+                                                     const int32_t* __restrict__ keys, int64_t V,
+                                                     int32_t* __restrict__ dir) {
+  __shared__ int32_t lim[2];
+  const int64_t b = blockIdx.x;
+  int lo = 0, hi = P - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (first[mid] <= b) lo = mid;
+    else hi = mid - 1;
+  }
+  const PredDesc d = desc[lo];
+  const int64_t b0 = (b - first[lo]) * kTile;
+  const int64_t nb = ((V - 1) >> d.dir_shift) + 2;  // entries
+  const int n = (int)min((int64_t)kTile, nb - b0);
+  const int32_t* const pk = keys + d.row_base;
+  if (wave_id() < 2) {
+    const int64_t v = (b0 + wave_id() * (int64_t)n) << d.dir_shift;
+    const int32_t r = v >= (int64_t)INT32_MAX ? (int32_t)d.nr
+                                              : wave_lower_bound(pk, (int32_t)d.nr, (int32_t)v);
+    if (lane_id() == 0) lim[wave_id()] = r;
+  }
+  __syncthreads();
+  int32_t v[kItems], at[kItems], len[kItems];
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    const int i = j * kBlock + threadIdx.x;
+    const int64_t x = (b0 + i) << d.dir_shift;
+    const bool ok = i < n;
+    at[j] = lim[0];
+    len[j] = ok ? lim[1] - lim[0] : 0;
+    if (ok && x >= (int64_t)INT32_MAX) {
+      at[j] = (int32_t)d.nr;
+      len[j] = 0;
+    }
+    v[j] = (int32_t)min(x, (int64_t)INT32_MAX);
+  }
+  lower_bound_n<kItems>(pk, v, at, len);
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    const int i = j * kBlock + threadIdx.x;
+    if (i < n) dir[d.dir_base + b0 + i] = at[j];
   }
 }
 
@@ -473,62 +691,94 @@ void launch_scan_add_u32(const uint32_t* x, int64_t n, const int64_t* tile_off, 
                                dim3(kBlock), 0, s, x, n, tile_off, out, 0));
 }
 
-void radix_sort_u64(uint64_t* keys, uint64_t* tmp, int64_t n, int nbits, DeviceMem& mem,
-                    hipStream_t s) {
-  if (n <= 1) return;
-  const int64_t nb = ceil_div(n, kTile);
-  const int64_t hn = 256 * nb;
+namespace {
+template <int RB, bool kSwap>
+void radix_pass(const uint64_t* src, uint64_t* dst, int64_t n, int shift, int vb, uint32_t* hist,
+                uint32_t* offs, int64_t* ts, int64_t nb, hipStream_t s) {
+  const int64_t hn = nb << RB;
+  const int64_t ht = ceil_div(hn, kTile);
+  GS_LAUNCH(GSMAT_K_OTHER, 8.0 * n,
+            hipLaunchKernelGGL((k_rs_hist<RB, kSwap>), dim3((unsigned)nb), dim3(kBlock), 0, s, src,
+                               n, shift, vb, hist, nb));
+  launch_tile_reduce_u32(hist, hn, ts, s);
+  launch_scan_tile_sums(ts, ht, ts + ht, s, nullptr);
+  launch_scan_add_u32(hist, hn, ts, offs, s);
+  GS_LAUNCH(GSMAT_K_OTHER, 16.0 * n,
+            hipLaunchKernelGGL((k_rs_scatter<RB, kSwap>), dim3((unsigned)nb), dim3(kBlock), 0, s,
+                               src, dst, n, shift, vb, offs, nb));
+}
+}  // namespace
+
+uint64_t* radix_sort_u64(uint64_t* keys, uint64_t* tmp, int64_t n, int lo_bit, int hi_bit,
+                         int swap_vb, DeviceMem& mem, hipStream_t s) {
+  if (n <= 0) return keys;
+  // 9-bit digits where they save a pass (27 bits: 3 against 4), else 8-bit
+  // ones, whose runs are twice as long
+  const int bits = hi_bit - lo_bit;
+  const int rb = (bits + 8) / 9 < (bits + 7) / 8 ? 9 : 8;
+  const int passes = std::max(1, (bits + rb - 1) / rb);
+  const int64_t nb = ceil_div(n, kRsTile);
+  const int64_t hn = nb << rb;
   const int64_t ht = ceil_div(hn, kTile);
   uint32_t* hist = (uint32_t*)mem.alloc(sizeof(uint32_t) * hn, s);
   uint32_t* offs = (uint32_t*)mem.alloc(sizeof(uint32_t) * hn, s);
   int64_t* ts = (int64_t*)mem.alloc(sizeof(int64_t) * (ht + 1), s);
-  if (!hist || !offs || !ts) {
+  auto done = [&] {
     if (hist) mem.free(hist, sizeof(uint32_t) * hn, s);
     if (offs) mem.free(offs, sizeof(uint32_t) * hn, s);
     if (ts) mem.free(ts, sizeof(int64_t) * (ht + 1), s);
+  };
+  if (!hist || !offs || !ts) {
+    done();
     throw OomFail{sizeof(uint32_t) * (size_t)hn};
   }
   uint64_t* src = keys;
   uint64_t* dst = tmp;
-  const int passes = (nbits + 7) / 8;
-  for (int pass = 0; pass < passes; ++pass) {
-    const int shift = 8 * pass;
-    GS_LAUNCH(GSMAT_K_OTHER, 8.0 * n,
-              hipLaunchKernelGGL(k_rs_hist, dim3((unsigned)nb), dim3(kBlock), 0, s, src, n, shift,
-                                 hist, nb));
-    launch_tile_reduce_u32(hist, hn, ts, s);
-    launch_scan_tile_sums(ts, ht, ts + ht, s, nullptr);
-    launch_scan_add_u32(hist, hn, ts, offs, s);
-    GS_LAUNCH(GSMAT_K_OTHER, 16.0 * n,
-              hipLaunchKernelGGL(k_rs_scatter, dim3((unsigned)nb), dim3(kBlock), 0, s, src, dst,
-                                 n, shift, offs, nb));
-    std::swap(src, dst);
+  try {
+    for (int pass = 0; pass < passes; ++pass) {
+      const int shift = lo_bit + rb * pass;
+      const bool swap = swap_vb > 0 && pass == 0;
+      if (rb == 8 && swap) radix_pass<8, true>(src, dst, n, shift, swap_vb, hist, offs, ts, nb, s);
+      else if (rb == 8) radix_pass<8, false>(src, dst, n, shift, 0, hist, offs, ts, nb, s);
+      else if (swap) radix_pass<9, true>(src, dst, n, shift, swap_vb, hist, offs, ts, nb, s);
+      else radix_pass<9, false>(src, dst, n, shift, 0, hist, offs, ts, nb, s);
+      std::swap(src, dst);
+    }
+  } catch (...) {
+    done();
+    throw;
   }
-  if (src != keys) GS_HIP(hipMemcpyAsync(keys, src, sizeof(uint64_t) * n, hipMemcpyDeviceToDevice, s));
-  mem.free(hist, sizeof(uint32_t) * hn, s);
-  mem.free(offs, sizeof(uint32_t) * hn, s);
-  mem.free(ts, sizeof(int64_t) * (ht + 1), s);
+  done();
+  return src;
 }
 
 void launch_pack_keys(const int32_t* sv, const int32_t* p, const int32_t* o, int64_t n, int vb,
-                      uint64_t* k_by_s, uint64_t* k_by_o, hipStream_t s) {
-  GS_LAUNCH(GSMAT_K_OTHER, 28.0 * n,
+                      uint64_t* k, hipStream_t s) {
+  GS_LAUNCH(GSMAT_K_OTHER, 20.0 * n,
             hipLaunchKernelGGL(k_pack_keys, dim3(grid_for(n)), dim3(kBlock), 0, s, sv, p, o, n,
-                               vb, k_by_s, k_by_o));
+                               vb, k));
 }
 
 void launch_flag_unique(const uint64_t* k, int64_t n, uint8_t* flags, int64_t* tile_sum,
                         hipStream_t s) {
   GS_LAUNCH(GSMAT_K_OTHER, 9.0 * n,
-            hipLaunchKernelGGL(k_flag_adjacent, dim3(tiles_for(n)), dim3(kBlock), 0, s, k, n, 0,
+            hipLaunchKernelGGL(k_flag_adjacent, dim3(tiles_for(n)), dim3(kBlock), 0, s, k, n,
                                flags, tile_sum));
 }
 
-void launch_flag_row_heads(const uint64_t* k, int64_t n, int vb, uint8_t* flags,
-                           int64_t* tile_sum, hipStream_t s) {
-  GS_LAUNCH(GSMAT_K_OTHER, 9.0 * n,
-            hipLaunchKernelGGL(k_flag_adjacent, dim3(tiles_for(n)), dim3(kBlock), 0, s, k, n, vb,
-                               flags, tile_sum));
+void launch_row_count(const uint64_t* k, int64_t n, int vb, int64_t* pfe, int64_t* tile_sum,
+                      hipStream_t s) {
+  GS_LAUNCH(GSMAT_K_OTHER, 8.0 * n,
+            hipLaunchKernelGGL(k_row_count, dim3(tiles_for(n)), dim3(kBlock), 0, s, k, n, vb, pfe,
+                               tile_sum));
+}
+
+void launch_row_fill(const uint64_t* k, int64_t n, int vb, const int64_t* pfe,
+                     const int64_t* tile_off, int32_t* nbr, int32_t* src, int32_t* keys,
+                     int32_t* ptr, int64_t* pfr, hipStream_t s) {
+  GS_LAUNCH(GSMAT_K_OTHER, (src ? 16.0 : 12.0) * n,
+            hipLaunchKernelGGL(k_row_fill, dim3(tiles_for(n)), dim3(kBlock), 0, s, k, n, vb, pfe,
+                               tile_off, nbr, src, keys, ptr, pfr));
 }
 
 void launch_compact_u64(const uint64_t* in, const uint8_t* flags, int64_t n,
@@ -538,50 +788,27 @@ void launch_compact_u64(const uint64_t* in, const uint8_t* flags, int64_t n,
                                n, tile_off, out));
 }
 
-void launch_compact_index(const uint8_t* flags, int64_t n, const int64_t* tile_off,
-                          int64_t* out_idx, hipStream_t s) {
-  GS_LAUNCH(GSMAT_K_COMPACT, 9.0 * n,
-            hipLaunchKernelGGL(k_compact_index, dim3(tiles_for(n)), dim3(kBlock), 0, s, flags, n,
-                               tile_off, out_idx));
-}
-
-void launch_split_members(const uint64_t* k, int64_t n, int vb, int32_t* nbr, int32_t* src,
-                          hipStream_t s) {
-  GS_LAUNCH(GSMAT_K_OTHER, 16.0 * n,
-            hipLaunchKernelGGL(k_split_members, dim3(grid_for(n)), dim3(kBlock), 0, s, k, n, vb,
-                               nbr, src));
-}
-
-void launch_pred_heads(const uint64_t* k, const int64_t* row_pos, int64_t R, int vb,
-                       int64_t* pfe, int64_t* pfr, hipStream_t s) {
-  GS_LAUNCH(GSMAT_K_OTHER, 24.0 * R,
-            hipLaunchKernelGGL(k_pred_heads, dim3(grid_for(R)), dim3(kBlock), 0, s, k, row_pos,
-                               R, vb, pfe, pfr));
-}
-
-void launch_fill_rows(const uint64_t* k, const int64_t* row_pos, int64_t R, int vb,
-                      const int64_t* pfe, int32_t* keys, int32_t* ptr, hipStream_t s) {
-  GS_LAUNCH(GSMAT_K_OTHER, 24.0 * R,
-            hipLaunchKernelGGL(k_fill_rows, dim3(grid_for(R)), dim3(kBlock), 0, s, k, row_pos, R,
-                               vb, pfe, keys, ptr));
-}
-
 void launch_fill_i64(int64_t* p, int64_t n, int64_t v, hipStream_t s) {
   if (n <= 0) return;
   GS_LAUNCH(GSMAT_K_OTHER, 8.0 * n,
             hipLaunchKernelGGL(k_fill_i64, dim3(grid_for(n)), dim3(kBlock), 0, s, p, n, v));
 }
 
-void launch_dense_ptr(PredView pv, int64_t V, int32_t* dense, hipStream_t s) {
-  GS_LAUNCH(GSMAT_K_OTHER, 4.0 * (V + 1),
-            hipLaunchKernelGGL(k_dense_ptr, dim3(grid_for(V + 1)), dim3(kBlock), 0, s, pv, V,
-                               dense));
+void launch_dense_ptrs(const PredDesc* desc, const int64_t* first, int32_t P, int64_t tiles,
+                       const int32_t* keys, const int32_t* ptr, int64_t V, int32_t* dense,
+                       hipStream_t s) {
+  if (tiles <= 0) return;
+  GS_LAUNCH(GSMAT_K_OTHER, 4.0 * kTile * tiles,
+            hipLaunchKernelGGL(k_dense_ptrs, dim3((unsigned)tiles), dim3(kBlock), 0, s, desc, first,
+                               P, keys, ptr, V, dense));
 }
 
-void launch_row_dir(PredView pv, int32_t shift, int64_t nb, int32_t* dir, hipStream_t s) {
-  GS_LAUNCH(GSMAT_K_OTHER, 4.0 * (nb + 1),
-            hipLaunchKernelGGL(k_row_dir, dim3(grid_for(nb + 1)), dim3(kBlock), 0, s, pv, shift, nb,
-                               dir));
+void launch_row_dirs(const PredDesc* desc, const int64_t* first, int32_t P, int64_t tiles,
+                     const int32_t* keys, int64_t V, int32_t* dir, hipStream_t s) {
+  if (tiles <= 0) return;
+  GS_LAUNCH(GSMAT_K_OTHER, 4.0 * kTile * tiles,
+            hipLaunchKernelGGL(k_row_dirs, dim3((unsigned)tiles), dim3(kBlock), 0, s, desc, first, P,
+                               keys, V, dir));
 }
 
 void launch_long_rows(PredView pv, int32_t min_len, int32_t* out, int32_t* count, int32_t cap,

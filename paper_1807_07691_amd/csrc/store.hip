@@ -3,10 +3,11 @@
 //
 // Build pipeline per orientation (all on the device, one stream):
 //   pack (p, row, member) into one 64-bit key -> LSD radix sort -> drop
-//   adjacent duplicates (D is a set, Sec. 3.1) -> flag the first entry of every
-//   (p, row) -> compact their positions -> per-predicate first entry/row ->
-//   row ids + row offsets (the Row / Rpos auxiliary arrays of Sec. 6.3) and
-//   member lists -> optional dense row pointers for heavy predicates.
+//   adjacent duplicates (D is a set, Sec. 3.1; by object: resort the distinct
+//   keys) -> count the first entries of every (p, row) and note each
+//   predicate's -> row ids + row offsets (the Row / Rpos auxiliary arrays of
+//   Sec. 6.3), member lists and each predicate's first row in one pass -> dense
+//   row pointers for heavy predicates, bucket directories for the others.
 #include <algorithm>
 #include <atomic>
 #include <cstring>
@@ -114,28 +115,26 @@ void build_orientation(gsmat_store* st, const uint64_t* keys, int64_t U, Orienta
   DeviceMem* mem = st->mem.get();
   const int32_t P = st->P;
   const int64_t nt = ceil_div(std::max<int64_t>(U, 1), kTile);
-  // rows: first entry of every (p, row)
+  // rows counted; first entry of every predicate
   int64_t R = 0;
-  Tmp<int64_t> row_pos(mem, U, s);
-  {
-    Tmp<uint8_t> flags(mem, U, s);
-    Tmp<int64_t> ts(mem, nt + 1, s);
-    if (U > 0) {
-      launch_flag_row_heads(keys, U, st->vb, flags.p, ts.p, s);
-      launch_scan_tile_sums(ts.p, nt, ts.p + nt, s, nullptr);
-      R = read_i64(ts.p + nt, s);
-      launch_compact_index(flags.p, U, ts.p, row_pos.p, s);
-    }
+  std::vector<int64_t> pfe(P, -1), pfr(P, -1);
+  Tmp<int64_t> ts(mem, nt + 1, s), heads(mem, 2 * (int64_t)P, s);
+  int64_t* const d_pfe = heads.p;
+  int64_t* const d_pfr = heads.p + P;
+  launch_fill_i64(heads.p, 2 * (int64_t)P, -1, s);
+  if (U > 0) {
+    launch_row_count(keys, U, st->vb, d_pfe, ts.p, s);
+    launch_scan_tile_sums(ts.p, nt, ts.p + nt, s, nullptr);
+    R = read_i64(ts.p + nt, s);
   }
-  // first entry and first row of every predicate
-  std::vector<int64_t> pfe(P), pfr(P);
-  {
-    Tmp<int64_t> d_pfe(mem, P, s), d_pfr(mem, P, s);
-    launch_fill_i64(d_pfe.p, P, -1, s);
-    launch_fill_i64(d_pfr.p, P, -1, s);
-    if (R > 0) launch_pred_heads(keys, row_pos.p, R, st->vb, d_pfe.p, d_pfr.p, s);
-    GS_HIP(hipMemcpyAsync(pfe.data(), d_pfe.p, sizeof(int64_t) * P, hipMemcpyDeviceToHost, s));
-    GS_HIP(hipMemcpyAsync(pfr.data(), d_pfr.p, sizeof(int64_t) * P, hipMemcpyDeviceToHost, s));
+  ori.nbr = (int32_t*)st->dalloc(sizeof(int32_t) * (size_t)U, s, true);
+  ori.src = with_src ? (int32_t*)st->dalloc(sizeof(int32_t) * (size_t)U, s, true) : nullptr;
+  ori.keys = (int32_t*)st->dalloc(sizeof(int32_t) * (size_t)R, s, true);
+  ori.ptr = (int32_t*)st->dalloc(sizeof(int32_t) * (size_t)(R + P), s, true);
+  if (U > 0) {
+    launch_row_fill(keys, U, st->vb, d_pfe, ts.p, ori.nbr, ori.src, ori.keys, ori.ptr, d_pfr, s);
+    GS_HIP(hipMemcpyAsync(pfe.data(), d_pfe, sizeof(int64_t) * P, hipMemcpyDeviceToHost, s));
+    GS_HIP(hipMemcpyAsync(pfr.data(), d_pfr, sizeof(int64_t) * P, hipMemcpyDeviceToHost, s));
     GS_HIP(hipStreamSynchronize(s));
   }
   ori.desc.assign(P, PredDesc{});
@@ -182,34 +181,28 @@ void build_orientation(gsmat_store* st, const uint64_t* keys, int64_t U, Orienta
       dir_len += ((V - 1) >> s) + 2;
     }
   }
-  ori.nbr = (int32_t*)st->dalloc(sizeof(int32_t) * (size_t)U, s, true);
-  ori.src = with_src ? (int32_t*)st->dalloc(sizeof(int32_t) * (size_t)U, s, true) : nullptr;
-  ori.keys = (int32_t*)st->dalloc(sizeof(int32_t) * (size_t)R, s, true);
-  ori.ptr = (int32_t*)st->dalloc(sizeof(int32_t) * (size_t)(R + P), s, true);
   ori.dense = dense_len ? (int32_t*)st->dalloc(sizeof(int32_t) * (size_t)dense_len, s, true) : nullptr;
   ori.dense_len = dense_len;
   ori.dir = dir_len ? (int32_t*)st->dalloc(sizeof(int32_t) * (size_t)dir_len, s, true) : nullptr;
   ori.dir_len = dir_len;
   ori.d_desc = (PredDesc*)st->dalloc(sizeof(PredDesc) * (size_t)P, s, true);
   GS_HIP(hipMemcpyAsync(ori.d_desc, ori.desc.data(), sizeof(PredDesc) * P, hipMemcpyHostToDevice, s));
-  if (U > 0) {
-    Tmp<int64_t> d_pfe(mem, P, s);
-    GS_HIP(hipMemcpyAsync(d_pfe.p, pfe.data(), sizeof(int64_t) * P, hipMemcpyHostToDevice, s));
-    launch_fill_rows(keys, row_pos.p, R, st->vb, d_pfe.p, ori.keys, ori.ptr, s);
-    launch_split_members(keys, U, st->vb, ori.nbr, ori.src, s);
-    GS_HIP(hipStreamSynchronize(s));  // d_pfe is a host-copied source
-  }
   launch_ptr_sentinels(ori.d_desc, P, ori.ptr, s);
+  // first tiles of the predicates' dense pointers and directories
+  std::vector<int64_t> first(2 * (size_t)P);
+  int64_t dense_tiles = 0, dir_tiles = 0;
   for (int32_t p = 0; p < P; ++p) {
     const PredDesc& d = ori.desc[p];
-    if (d.dense_base >= 0) launch_dense_ptr(ori.view(p), st->V, ori.dense + d.dense_base, s);
-    if (d.dir_base >= 0) {
-      // the view without its directory: the directory is built from the keys
-      PredView pv = ori.view(p);
-      pv.dir = nullptr;
-      launch_row_dir(pv, d.dir_shift, ((V - 1) >> d.dir_shift) + 1, ori.dir + d.dir_base, s);
-    }
+    first[p] = dense_tiles;
+    first[P + p] = dir_tiles;
+    if (d.dense_base >= 0) dense_tiles += ceil_div(V + 1, kTile);
+    if (d.dir_base >= 0) dir_tiles += ceil_div(((V - 1) >> d.dir_shift) + 2, kTile);
   }
+  Tmp<int64_t> d_first(mem, 2 * (int64_t)P, s);
+  GS_HIP(hipMemcpyAsync(d_first.p, first.data(), sizeof(int64_t) * first.size(),
+                        hipMemcpyHostToDevice, s));
+  launch_dense_ptrs(ori.d_desc, d_first.p, P, dense_tiles, ori.keys, ori.ptr, V, ori.dense, s);
+  launch_row_dirs(ori.d_desc, d_first.p + P, P, dir_tiles, ori.keys, V, ori.dir, s);
   GS_HIP(hipStreamSynchronize(s));
   build_hubs(st, ori, s);
 }
@@ -276,21 +269,18 @@ void build_hubs(gsmat_store* st, Orientation& ori, hipStream_t s) {
   GS_HIP(hipStreamSynchronize(s));
 }
 
-// Sort + deduplicate one key array in place; returns the distinct count.
-int64_t sort_unique(gsmat_store* st, uint64_t* keys, int64_t n, uint64_t* tmp, hipStream_t s) {
+// Keeps the first of equal neighbours of the n sorted keys: into out; their
+// number.
+int64_t unique_keys(gsmat_store* st, const uint64_t* keys, int64_t n, uint64_t* out,
+                    hipStream_t s) {
   DeviceMem* mem = st->mem.get();
-  const int nbits = st->pb + 2 * st->vb;
-  radix_sort_u64(keys, tmp, n, nbits, *mem, s);
   const int64_t nt = ceil_div(std::max<int64_t>(n, 1), kTile);
   Tmp<uint8_t> flags(mem, n, s);
   Tmp<int64_t> ts(mem, nt + 1, s);
   launch_flag_unique(keys, n, flags.p, ts.p, s);
   launch_scan_tile_sums(ts.p, nt, ts.p + nt, s, nullptr);
-  const int64_t U = read_i64(ts.p + nt, s);
-  launch_compact_u64(keys, flags.p, n, ts.p, tmp, s);
-  GS_HIP(hipMemcpyAsync(keys, tmp, sizeof(uint64_t) * (size_t)U, hipMemcpyDeviceToDevice, s));
-  GS_HIP(hipStreamSynchronize(s));
-  return U;
+  launch_compact_u64(keys, flags.p, n, ts.p, out, s);
+  return read_i64(ts.p + nt, s);
 }
 
 }  // namespace
@@ -370,15 +360,25 @@ extern "C" gsmat_status gsmat_build_index(gsmat_store* st, int32_t dense_div, vo
     const int64_t n = st->n_in;
     const size_t raw = sizeof(int32_t) * (size_t)std::max<int64_t>(n, 1);
     {
-      Tmp<uint64_t> ks(mem, n, s), ko(mem, n, s);
-      if (n > 0) launch_pack_keys(st->d_s, st->d_p, st->d_o, n, st->vb, ks.p, ko.p, s);
-      Tmp<uint64_t> tmp(mem, n, s);
-      const int64_t U = n > 0 ? sort_unique(st, ks.p, n, tmp.p, s) : 0;
-      build_orientation(st, ks.p, U, st->out, true, dense_div, s);
-      ks.release();
-      const int64_t U2 = n > 0 ? sort_unique(st, ko.p, n, tmp.p, s) : 0;
-      if (U2 != U) throw StatusFail{GSMAT_EHIP, "orientations disagree on the distinct count"};
-      build_orientation(st, ko.p, U2, st->in, false, dense_div, s);
+      const int vb = st->vb, bits = st->pb + 2 * vb;
+      Tmp<uint64_t> ka(mem, n, s), kb(mem, n, s);
+      uint64_t* k = ka.p;
+      int64_t U = 0;
+      auto other = [&] { return k == ka.p ? kb.p : ka.p; };
+      if (n > 0) {
+        launch_pack_keys(st->d_s, st->d_p, st->d_o, n, vb, k, s);
+        k = radix_sort_u64(k, other(), n, 0, bits, 0, *mem, s);
+        uint64_t* const to = other();
+        U = unique_keys(st, k, n, to, s);
+        k = to;
+      }
+      build_orientation(st, k, U, st->out, true, dense_div, s);
+      // by object: the distinct keys are in (p, s, o) order, so a stable sort of
+      // (p, o, s) on o and p alone leaves s ascending: vb + pb bits instead of
+      // pb + 2 vb (20 million triples: 3 passes instead of 6), and no second
+      // removal of duplicates
+      if (U > 0) k = radix_sort_u64(k, other(), U, vb, bits, vb, *mem, s);
+      build_orientation(st, k, U, st->in, false, dense_div, s);
       st->T = U;
     }
     mem->free(st->d_s, raw, s);
