@@ -200,11 +200,24 @@ def _p(a):
     return a.ctypes.data_as(ctypes.c_void_p)
 
 
+_raw_stream = None  # torch's current stream of a device as an int, once torch has set up its GPU
+
+
 def default_stream():
+    global _raw_stream
+    if _raw_stream is not None:
+        get, device = _raw_stream
+        return get(device())
     try:
         import torch
         if torch.cuda.is_available():
-            return int(torch.cuda.current_stream().cuda_stream)
+            s = int(torch.cuda.current_stream().cuda_stream)
+            get = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+            device = getattr(torch._C, "_cuda_getDevice", None)
+            # without the stream object: 0.3 us instead of 3.7 us a call
+            if get is not None and device is not None and get(device()) == s:
+                _raw_stream = (get, device)
+            return s
     except Exception:  # torch absent or without a GPU: the null stream
         pass
     return 0

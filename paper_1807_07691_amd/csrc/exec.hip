@@ -19,6 +19,7 @@
 
 #include "batch.hpp"
 #include "exec.hpp"
+#include "host_area.hpp"
 #include "small.hpp"
 
 using namespace gsmat;
@@ -67,31 +68,6 @@ PinnedArea* pinned(bool make = true) {
   return a;
 }
 
-// Host memory that rows are fetched through: two parts, one filled by the
-// device while the other is copied out.  Per thread, 256 KiB until a fetch
-// needs more, then 8 MiB, given back at the thread's end.
-struct FetchArea {
-  static constexpr size_t kSmall = 128 << 10, kLarge = 4 << 20;  // bytes per part
-  char* p = nullptr;
-  size_t part = 0;
-  uint32_t* words(int i) { return (uint32_t*)(p + 2 * part) + i * kPackGroups; }
-  int32_t* rows(int i) { return (int32_t*)(p + i * part); }
-  void reserve(size_t bytes) {
-    const size_t want = bytes <= kSmall ? kSmall : kLarge;
-    if (part >= want) return;
-    release();
-    const size_t all = 2 * want + 2 * sizeof(uint32_t) * kPackGroups;
-    GS_HIP(hipHostMalloc((void**)&p, all, hipHostMallocDefault));
-    part = want;
-    std::memset(words(0), 0, 2 * sizeof(uint32_t) * kPackGroups);
-  }
-  void release() {
-    if (p) (void)hipHostFree(p);
-    p = nullptr;
-    part = 0;
-  }
-  ~FetchArea() { release(); }
-};
 // Host memory of a batch's queries and reports (at most kSmallBatch of them),
 // per thread.
 struct QueryArea {
@@ -114,10 +90,6 @@ struct QueryArea {
 };
 QueryArea& query_area() {
   thread_local QueryArea a;
-  return a;
-}
-FetchArea& fetch_area() {
-  thread_local FetchArea a;
   return a;
 }
 
@@ -1491,9 +1463,12 @@ extern "C" gsmat_status gsmat_fetch_bindings(const gsmat_result* r, int64_t row_
       launch_next(0);
       launch_next(1);
       int32_t* to = host_rows;
+      char* const end = (char*)(host_rows + (hi - lo) * nv);
+      char* mapped = (char*)host_rows;
       for (int i = 0; pc[i].rows > 0; i ^= 1) {
+        if ((char*)(to + pc[i].rows * nv) > mapped) mapped = map_ahead(mapped, end);
         host_wait_words(fa.words(i), pc[i].groups, pc[i].report, s);
-        std::memcpy(to, fa.rows(i), sizeof(int32_t) * pc[i].rows * nv);
+        copy_host((char*)to, (const char*)fa.rows(i), sizeof(int32_t) * (int64_t)pc[i].rows * nv);
         to += pc[i].rows * nv;
         launch_next(i);
       }
