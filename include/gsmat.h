@@ -380,6 +380,12 @@ gsmat_status gsmat_result_info(const gsmat_result* r, int64_t* n_rows, int32_t* 
 gsmat_status gsmat_fetch_bindings(const gsmat_result* r, int64_t row_offset, int64_t max_rows,
                                   int32_t* host_rows, int64_t* n_written, void* stream);
 
+/* Every row of n results (NULL entries are skipped): as gsmat_fetch_bindings
+ * of results[i] into host_rows[i], with one launch for as many results as fit
+ * the transfer area. */
+gsmat_status gsmat_fetch_bindings_many(const gsmat_result* const* results, int32_t n,
+                                       int32_t* const* host_rows, void* stream);
+
 void gsmat_result_free(gsmat_result* r);
 
 /* ---- OPTIONAL, UNION and FILTER (Sec. 9) ---------------------------------

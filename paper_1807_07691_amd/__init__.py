@@ -43,7 +43,7 @@ EXPORTED = [
     "gsmat_autotune_batch", "gsmat_expand_strategy", "gsmat_set_batch_engine",
     "gsmat_set_batch_regions", "gsmat_batch_round_stats", "gsmat_join_noalloc",
     "gsmat_set_batch_tuning", "gsmat_get_batch_tuning", "gsmat_join_ext",
-    "gsmat_join_batch_bgp",
+    "gsmat_join_batch_bgp", "gsmat_fetch_bindings_many",
 ]
 
 
@@ -128,6 +128,8 @@ def _load():
     L.gsmat_result_info.argtypes = [vp, vp, vp, vp, vp, vp]
     L.gsmat_fetch_bindings.restype = i32
     L.gsmat_fetch_bindings.argtypes = [vp, i64, i64, vp, vp, vp]
+    L.gsmat_fetch_bindings_many.restype = i32
+    L.gsmat_fetch_bindings_many.argtypes = [vp, i32, vp, vp]
     L.gsmat_result_free.restype = None
     L.gsmat_result_free.argtypes = [vp]
     L.gsmat_last_error.restype = ctypes.c_char_p
@@ -818,6 +820,22 @@ def gsmat_fetch_bindings(result, row_offset=0, max_rows=None, stream=None):
     return out[:written.value]
 
 
+def gsmat_fetch_bindings_many(results, stream=None):
+    """All rows of several results (a list of Result): one (rows, n_vars) int32
+    array per result."""
+    n = len(results)
+    rows, nv = ctypes.c_int64(), ctypes.c_int32()
+    rp, vp_ = ctypes.byref(rows), ctypes.byref(nv)
+    out = []
+    for r in results:
+        _check(_lib.gsmat_result_info(r.h, rp, vp_, None, None, None))
+        out.append(np.empty((rows.value, nv.value), np.int32))
+    hs = (ctypes.c_void_p * max(n, 1))(*[r.h for r in results])
+    to = (ctypes.c_void_p * max(n, 1))(*[a.ctypes.data if a.size else None for a in out])
+    _check(_lib.gsmat_fetch_bindings_many(hs, n, to, _stream(stream)))
+    return out
+
+
 def gsmat_release_pools():
     _check(_lib.gsmat_release_pools())
 
@@ -850,7 +868,7 @@ def evaluate_batch(store, queries, mode=PLAN_ADAPTIVE, budget_bytes=0, max_rows=
     try:
         results, _ = gsmat_join_batch(store, plans, budget_bytes, max_rows, stream)
         try:
-            return [gsmat_fetch_bindings(r, stream=stream) for r in results]
+            return gsmat_fetch_bindings_many(results, stream)
         finally:
             for r in results:
                 r.close()

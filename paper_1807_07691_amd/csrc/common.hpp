@@ -304,11 +304,21 @@ void launch_cartesian(ColSet a, int ka, int64_t na, ColSet b, int kb, int64_t nb
 void launch_copy_cols(ColSet in, int k, int64_t n, OutSet out, hipStream_t s);
 // writes kSampleBlocks partial sums per candidate to part[cand * kSampleBlocks + b]
 void launch_sample_fanout(const SampleSet& ss, int64_t* part, hipStream_t s);
-// rows [row0, row0 + rows) of the k columns, row-major, to host memory `out`
-// (16-byte aligned); returns the number of workgroups, each of which writes
-// `report` to its word when its rows are there (at most kPackGroups)
+// Rows [row0, row0 + rows) of k columns, row-major, to host memory `out`
+// (16-byte aligned).
+struct PackTask {
+  ColSet cols;
+  int64_t row0, rows;
+  int32_t* out;
+  int32_t k, pad;
+};
+// Packs n tasks (host memory the device can reach; n = 1: passed by value);
+// returns the number of workgroups, each of which writes `report` to its word
+// when its rows are there: at most kPackGroups for each of up to kPackGroups
+// tasks, kPackWords in all.
 constexpr int kPackGroups = 256;
-int launch_pack_rows(ColSet cols, int k, int64_t row0, int64_t rows, int32_t* out,
-                     uint32_t* words, uint32_t report, hipStream_t s);
+constexpr int kPackWords = 4096;
+int launch_pack_rows(const PackTask* tasks, int n, uint32_t* words, uint32_t report,
+                     hipStream_t s);
 
 }  // namespace gsmat

@@ -11,22 +11,25 @@
 namespace gsmat {
 
 // Host memory that large transfers go through: two parts, one worked on by the
-// device while the host copies the other.  Per thread, 256 KiB until a fetch
-// needs more, then 8 MiB, given back at the thread's end.
+// device while the host copies the other, and the tasks and reports of each.
+// Per thread, 0.5 MiB until a transfer needs more, then 8.2 MiB, given back at
+// the thread's end.
 struct FetchArea {
   static constexpr size_t kSmall = 128 << 10, kLarge = 4 << 20;  // bytes per part
   char* p = nullptr;
   size_t part = 0;
-  uint32_t* words(int i) { return (uint32_t*)(p + 2 * part) + i * kPackGroups; }
+  uint32_t* words(int i) { return (uint32_t*)(p + 2 * part) + i * kPackWords; }
+  PackTask* tasks(int i) { return (PackTask*)(words(0) + 2 * kPackWords) + i * kPackGroups; }
   int32_t* rows(int i) { return (int32_t*)(p + i * part); }
   void reserve(size_t bytes) {
     const size_t want = bytes <= kSmall ? kSmall : kLarge;
     if (part >= want) return;
     release();
-    const size_t all = 2 * want + 2 * sizeof(uint32_t) * kPackGroups;
+    const size_t all =
+        2 * (want + sizeof(uint32_t) * kPackWords + sizeof(PackTask) * kPackGroups);
     GS_HIP(hipHostMalloc((void**)&p, all, hipHostMallocDefault));
     part = want;
-    std::memset(words(0), 0, 2 * sizeof(uint32_t) * kPackGroups);
+    std::memset(words(0), 0, 2 * sizeof(uint32_t) * kPackWords);
   }
   void release() {
     if (p) (void)hipHostFree(p);

@@ -616,17 +616,28 @@ __global__ __launch_bounds__(kBlock) void k_sample_fanout(SampleSet ss, int64_t*
 // wave makes to consecutive addresses.  Writing where the host reads takes
 // the device copy, the copy command and the wait for the stream out of a
 // fetch: of up to 100 rows 35 -> 16.5 us, of 3 million rows of 4 columns 5.2 -> 4.3 ms.
-__global__ __launch_bounds__(kBlock) void k_pack_rows(ColSet cols, int k, int64_t row0,
-                                                      int64_t rows, int32_t* __restrict__ out,
+// blockIdx.y is the task, the workgroups of a row stride over its tiles.
+__global__ __launch_bounds__(kBlock) void k_pack_rows(PackTask one,
+                                                      const PackTask* __restrict__ many,
                                                       uint32_t* words, uint32_t report) {
   __shared__ __align__(16) int32_t s[kBlock * kMaxCols];
+  __shared__ PackTask task;
+  static_assert(sizeof(PackTask) % 4 == 0 && sizeof(PackTask) / 4 <= kBlock, "one word a thread");
+  if (many) {
+    if (threadIdx.x < sizeof(PackTask) / 4)
+      ((uint32_t*)&task)[threadIdx.x] = ((const uint32_t*)(many + blockIdx.y))[threadIdx.x];
+    __syncthreads();
+  }
+  const int k = many ? task.k : one.k;
+  const int64_t row0 = many ? task.row0 : one.row0, rows = many ? task.rows : one.rows;
+  int32_t* const out = many ? task.out : one.out;
   const int64_t tiles = (rows + kBlock - 1) / kBlock;
   for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
     const int64_t r0 = t * kBlock;
     const int nr = (int)min((int64_t)kBlock, rows - r0);
     if ((int)threadIdx.x < nr)
       for (int c = 0; c < k; ++c) {
-        const int32_t* col = cols.c[c];  // no column: the variable is unbound
+        const int32_t* col = many ? task.cols.c[c] : one.cols.c[c];  // none: unbound
         s[threadIdx.x * k + c] = col ? col[row0 + r0 + threadIdx.x] : -1;
       }
     __syncthreads();
@@ -637,7 +648,7 @@ __global__ __launch_bounds__(kBlock) void k_pack_rows(ColSet cols, int k, int64_
     if ((int)threadIdx.x < (n & 3)) o[(n & ~3) + threadIdx.x] = s[(n & ~3) + threadIdx.x];
     __syncthreads();  // the next tile reuses the LDS
   }
-  report_done(words + blockIdx.x, report);
+  report_done(words + (int64_t)blockIdx.y * gridDim.x + blockIdx.x, report);
 }
 
 inline unsigned grid_for(int64_t n, int block = kBlock, int64_t cap = 65536) {
@@ -946,13 +957,19 @@ void launch_sample_fanout(const SampleSet& ss, int64_t* part, hipStream_t s) {
                                dim3(kBlock), 0, s, ss, part));
 }
 
-int launch_pack_rows(ColSet cols, int k, int64_t row0, int64_t rows, int32_t* out,
-                     uint32_t* words, uint32_t report, hipStream_t s) {
-  const int groups = (int)grid_for(rows, kBlock, kPackGroups);
-  GS_LAUNCH(GSMAT_K_OTHER, 8.0 * k * rows,
-            hipLaunchKernelGGL(k_pack_rows, dim3((unsigned)groups), dim3(kBlock), 0, s, cols, k,
-                               row0, rows, out, words, report));
-  return groups;
+int launch_pack_rows(const PackTask* tasks, int n, uint32_t* words, uint32_t report,
+                     hipStream_t s) {
+  int64_t most = 1;
+  double bytes = 0;
+  for (int i = 0; i < n; ++i) {
+    most = std::max(most, tasks[i].rows);
+    bytes += 8.0 * tasks[i].k * (double)tasks[i].rows;
+  }
+  const int gx = std::min((int)grid_for(most, kBlock, kPackGroups), kPackWords / n);
+  GS_LAUNCH(GSMAT_K_OTHER, bytes,
+            hipLaunchKernelGGL(k_pack_rows, dim3((unsigned)gx, (unsigned)n), dim3(kBlock), 0, s,
+                               tasks[0], n > 1 ? tasks : nullptr, words, report));
+  return gx * n;
 }
 
 }  // namespace gsmat

@@ -44,3 +44,32 @@ def test_fetch_edges(G, n):
         r.close()
         pl.close()
     st.close()
+
+
+@pytest.mark.parametrize("sizes", [[0], [1, 0, 7], [256] * 300, [SMALL // 2 + 1] * 5,
+                                   [3, LARGE + 5, 0, 12, 2 * LARGE + 1, 255, 40_000]])
+def test_fetch_many(G, sizes):
+    # vertex i has sizes[i] objects along predicate 0 and two along predicate 1
+    V = max(max(sizes), len(sizes)) + 2
+    s = np.repeat(np.arange(len(sizes)), sizes)
+    o = np.concatenate([np.arange(z) for z in sizes])
+    k = np.arange(len(sizes))
+    t = [np.concatenate([s, k, k]), np.concatenate([np.zeros(len(s)), np.ones(2 * len(k))]),
+         np.concatenate([o, k % 2, 1 + k])]
+    s, p, o = (np.asarray(x).astype(np.int32) for x in t)
+    st = G.gsmat_load_triples(s, p, o, V, 2)
+    G.gsmat_build_index(st)
+    print(f"[gpu] fetch many {len(sizes)} results", flush=True)
+    qs = [[[i, 0, -1]] for i in range(len(sizes))] + [[[0, 1, 0]], [[-1, 1, -2]]]
+    plans, _ = G.gsmat_plan_batch(st, qs)
+    res = [G.gsmat_join(st, pl) for pl in plans]
+    got = G.gsmat_fetch_bindings_many(res)
+    for i, z in enumerate(sizes):
+        assert np.array_equal(got[i], np.arange(z, dtype=np.int32)[:, None]), i
+    for a, r in zip(got, res):
+        assert a.shape == (G.gsmat_result_info(r)["rows"], G.gsmat_result_info(r)["n_vars"])
+        assert np.array_equal(a, G.gsmat_fetch_bindings(r))
+        r.close()
+    for pl in plans:
+        pl.close()
+    st.close()
