@@ -235,6 +235,10 @@ void launch_scan_tile_sums(int64_t* tile_sum, int64_t nt, int64_t* total, hipStr
 void launch_scan_tile_sums2(int64_t* ts, int64_t* ts2, int64_t nt, hipStream_t s);
 void launch_scan_add_i32(const int32_t* N, int64_t n, const int64_t* tile_off, int64_t* P,
                          hipStream_t s);
+// offsets P of the n counts N and their total, from tile sums that have not
+// been scanned; false (nothing launched) above kTile tiles
+bool launch_scan_rows(const int32_t* N, int64_t n, const int64_t* tile_sum, int64_t* P,
+                      int64_t* host_total, uint32_t* word, uint32_t report, hipStream_t s);
 void launch_tile_reduce_u32(const uint32_t* x, int64_t n, int64_t* tile_sum, hipStream_t s);
 void launch_scan_add_u32(const uint32_t* x, int64_t n, const int64_t* tile_off, uint32_t* out,
                          hipStream_t s);
@@ -303,7 +307,9 @@ void launch_cartesian(ColSet a, int ka, int64_t na, ColSet b, int kb, int64_t nb
 // out's columns = in's, n rows of k columns
 void launch_copy_cols(ColSet in, int k, int64_t n, OutSet out, hipStream_t s);
 // writes kSampleBlocks partial sums per candidate to part[cand * kSampleBlocks + b]
-void launch_sample_fanout(const SampleSet& ss, int64_t* part, hipStream_t s);
+// (words: a report per partial sum)
+void launch_sample_fanout(const SampleSet& ss, int64_t* part, hipStream_t s,
+                          uint32_t* words = nullptr, uint32_t report = 0);
 // Rows [row0, row0 + rows) of k columns, row-major, to host memory `out`
 // (16-byte aligned).
 struct PackTask {

@@ -130,8 +130,10 @@ struct DCtl {
   // per round: tasks counted, count tiles, post tiles, write tiles, tables
   // written, output bytes, candidates sampled, deferred tasks
   int64_t stats[kStatRounds][kStatFields];
-  int32_t out_slab, ncand, active, deferred, error, round;
+  int32_t out_slab, ncand, nbig, active, deferred, error, round, pad;
 };
+constexpr int kSampleWave = 256;  // rows of a candidate that one wave samples
+static_assert(kSampleWave <= kSampleRows, "every row is sampled");
 
 struct DRes {
   int32_t state, status, slab, pad;
@@ -156,6 +158,7 @@ struct DArgs {
   int64_t* sin;
   int64_t* sout;
   SCand* cands;
+  int32_t* big;  // the candidates of more than kSampleWave rows
   int64_t* part;
   CTask* ct;
   ListRef* lists;
@@ -490,7 +493,9 @@ __global__ void k_d_choose(DArgs A, int choose) {
         return;
       }
       Q.cand0 = c0;
+      const int b0 = Q.t.n > kSampleWave ? atomicAdd(&A.ctl->nbig, Q.nc) : 0;
       for (int i = 0; i < Q.nc; ++i) {
+        if (Q.t.n > kSampleWave) A.big[b0 + i] = c0 + i;  // b0 + nc <= all candidates
         const DPat q = pats[Q.cand_tp[i]];
         const bool from_s = Q.cand_or[i] == 0;
         const int c = tab_col(Q.t, d_var(from_s ? q.s : q.o));
@@ -514,18 +519,45 @@ __global__ void k_d_choose(DArgs A, int choose) {
   }
 }
 
-// Fan-out sample slices of every candidate (kSampleBlocks per candidate).
+// Fan-out samples of every candidate.  One of up to kSampleWave rows is a
+// wave's (most of a batch's are: 10 000 of them a round were 80 000 slices of a
+// workgroup, 35 us); the others, listed by the choice, are cut into
+// kSampleBlocks slices of a workgroup.
 // The tile kernels take their arrays as separate read-only, non-aliased
 // parameters, so that the descriptors are fetched with scalar loads.
 __global__ __launch_bounds__(kBlock) void k_d_sample(const SCand* __restrict__ cands,
+                                                     const int32_t* __restrict__ big,
                                                      int64_t* __restrict__ part,
                                                      const DCtl* __restrict__ ctl) {
-  const int64_t total = (int64_t)ctl->ncand * kSampleBlocks;
-  for (int64_t j = blockIdx.x; j < total; j += gridDim.x) {
-    const SCand& sc = cands[j / kSampleBlocks];
+  const int64_t slices = (int64_t)ctl->nbig * kSampleBlocks;
+  for (int64_t j = blockIdx.x; j < slices; j += gridDim.x) {
+    const int c = big[j / kSampleBlocks];
+    const SCand& sc = cands[c];
     const int64_t t = sample_fanout_slice((int)(j % kSampleBlocks), sc.col, sc.n, sc.pv);
-    if (threadIdx.x == 0) part[j] = t;
+    if (threadIdx.x == 0) part[(int64_t)c * kSampleBlocks + j % kSampleBlocks] = t;
     __syncthreads();
+  }
+  const int64_t nc = ctl->ncand;
+  for (int64_t c = (int64_t)blockIdx.x * kWaves + wave_id(); c < nc;
+       c += (int64_t)gridDim.x * kWaves) {
+    const SCand& sc = cands[__builtin_amdgcn_readfirstlane((int)c)];
+    const int n = sc.n > kSampleWave ? 0 : (int)sc.n;
+    if (n == 0) continue;  // a listed one
+    constexpr int kN = kSampleWave / 64;
+    int32_t v[kN], st[kN], len[kN];
+    bool ok[kN];
+#pragma unroll
+    for (int u = 0; u < kN; ++u) {
+      const int i = u * 64 + lane_id();
+      ok[u] = i < n;
+      v[u] = ok[u] ? sc.col[i] : 0;
+    }
+    row_lookup_n<kN>(sc.pv, v, ok, st, len);
+    int64_t loc = 0;
+#pragma unroll
+    for (int u = 0; u < kN; ++u) loc += len[u];
+    loc = wave_sum(loc);
+    if (lane_id() < kSampleBlocks) part[c * kSampleBlocks + lane_id()] = lane_id() == 0 ? loc : 0;
   }
 }
 
@@ -758,6 +790,7 @@ __device__ inline void d_layout_finish(DArgs& A, DCtl& C, const int64_t (&t1)[1]
     C.scr_used = t2[1] + 2 * d_a256(8 * (nt + 1));
     C.bytes_count += t2[2];
     C.ncand = 0;
+    C.nbig = 0;
     C.active = 0;
     C.deferred += s_defer;
     C.want_scr = max(C.want_scr, (int64_t)s_want);
@@ -1432,7 +1465,7 @@ void run_batch_packed(gsmat_store* st, PackedBatch& pb, int64_t budget, int64_t 
   const size_t up_bytes = L.bytes;
   const size_t o_lk = L.add(sizeof(LookupRes) * n * mp), o_q = L.add(sizeof(DQ) * n),
                o_cands = L.add(sizeof(SCand) * n * mp),
-               o_part = L.add(sizeof(int64_t) * n * mp * kSampleBlocks),
+               o_big = L.add(sizeof(int32_t) * n * mp), o_part = L.add(sizeof(int64_t) * n * mp * kSampleBlocks),
                o_ct = L.add(sizeof(CTask) * n), o_lists = L.add(sizeof(ListRef) * n * kMaxLists),
                o_wt = L.add(sizeof(WTask) * n), o_ne = L.add(sizeof(int64_t) * n),
                o_wc = L.add(sizeof(int64_t) * (n + 1)), o_wpo = L.add(sizeof(int64_t) * (n + 1)),
@@ -1496,6 +1529,7 @@ void run_batch_packed(gsmat_store* st, PackedBatch& pb, int64_t budget, int64_t 
   A.sin = (int64_t*)(dv + o_sin);
   A.sout = (int64_t*)(dv + o_sout);
   A.cands = (SCand*)(dv + o_cands);
+  A.big = (int32_t*)(dv + o_big);
   A.part = (int64_t*)(dv + o_part);
   A.ct = (CTask*)(dv + o_ct);
   A.lists = (ListRef*)(dv + o_lists);
@@ -1539,7 +1573,8 @@ void run_batch_packed(gsmat_store* st, PackedBatch& pb, int64_t budget, int64_t 
   for (int iter = 0;; ++iter) {
     for (int r = 0; r < rounds; ++r, ++gr) {
       GS_DLAUNCH(GSMAT_K_OTHER, k_d_choose, qgrid, kQBlock, A, 1);
-      GS_DLAUNCH(GSMAT_K_OTHER, k_d_sample, grids.sample, kBlock, A.cands, A.part, A.ctl);
+      GS_DLAUNCH(GSMAT_K_OTHER, k_d_sample, grids.sample, kBlock, A.cands, A.big, A.part,
+                 A.ctl);
       GS_DLAUNCH(GSMAT_K_OTHER, k_d_task, qgrid, kQBlock, A);
       if (nq <= kAllocRegs * kScanBlock) {
         GS_DLAUNCH(GSMAT_K_SCAN, k_d_layout<kAllocRegs>, 1, kScanBlock, A);

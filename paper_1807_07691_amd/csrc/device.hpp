@@ -30,6 +30,13 @@ __device__ inline void report_done(uint32_t* word, uint32_t report) {
     __hip_atomic_store(word, report, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// The same where thread 0 alone has written what is reported.
+__device__ inline void report_one(uint32_t* word, uint32_t report) {
+  if (!word || threadIdx.x != 0) return;
+  __threadfence_system();
+  __hip_atomic_store(word, report, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 __device__ inline int64_t wave_incl_scan(int64_t v) {
   const int lane = lane_id();
 #pragma unroll
@@ -408,15 +415,24 @@ constexpr int64_t kSampleRows = 16384;
 // `slice` (of kSampleBlocks) of it per workgroup.
 __device__ inline int64_t sample_fanout_slice(int slice, const int32_t* __restrict__ col,
                                               int64_t n, const PredView& pv) {
+  constexpr int kN = (int)(kSampleRows / (kSampleBlocks * kBlock));  // rows per thread
+  static_assert((int64_t)kN * kSampleBlocks * kBlock == kSampleRows, "every row in one thread");
   const int64_t S = n < kSampleRows ? n : kSampleRows;
   const int64_t stride = S > 0 ? n / S : 1;
-  int64_t loc = 0;
-  for (int64_t j = (int64_t)slice * kBlock + threadIdx.x; j < S;
-       j += (int64_t)kSampleBlocks * kBlock) {
-    int32_t st, len;
-    row_lookup(pv, col[j * stride], st, len);
-    loc += len;
+  int32_t v[kN], st[kN], len[kN];
+  bool ok[kN];
+  // a thread's lookups advance together: one chain of dependent loads, not
+  // kN of them
+#pragma unroll
+  for (int u = 0; u < kN; ++u) {
+    const int64_t j = ((int64_t)u * kSampleBlocks + slice) * kBlock + threadIdx.x;
+    ok[u] = j < S;
+    v[u] = ok[u] ? col[j * stride] : 0;
   }
+  row_lookup_n<kN>(pv, v, ok, st, len);
+  int64_t loc = 0;
+#pragma unroll
+  for (int u = 0; u < kN; ++u) loc += len[u];
   return block_sum(loc);
 }
 
@@ -759,6 +775,25 @@ __device__ inline int64_t mp_split(const int64_t* __restrict__ P, int64_t n, int
     const int64_t mid = (lo + hi) >> 1;
     if (P[mid + 1] <= J0 + (d - 1 - mid)) lo = mid + 1;
     else hi = mid;
+  }
+  return lo;
+}
+
+// The same by a whole wave (alike in every lane): 64 rows are looked at
+// together, 4 dependent loads instead of 20 over a million rows.
+__device__ inline int64_t mp_split_wave(const int64_t* __restrict__ P, int64_t n, int64_t J0,
+                                        int64_t J1, int64_t t) {
+  const int64_t nb = J1 - J0;
+  const int64_t d = min(t * (int64_t)kTile, n + nb);
+  int64_t lo = max((int64_t)0, d - nb), hi = min(d, n);
+  while (lo < hi) {
+    const int64_t step = (hi - lo + 63) / 64;
+    const int64_t i = lo + lane_id() * step;
+    // rows ascend, so the lanes whose row comes before the position are a prefix
+    const int c = (int)__popcll(__ballot(i < hi && P[i + 1] <= J0 + (d - 1 - i)));
+    if (c == 0) break;
+    hi = min(hi, lo + c * step);
+    lo += (c - 1) * step + 1;
   }
   return lo;
 }

@@ -51,6 +51,7 @@ struct PinnedArea {
   LookupRes res[kMaxLookups];
   int64_t part[kMaxPats * kSampleBlocks];
   uint32_t word;  // report of the launches that fill the other fields
+  uint32_t words[kMaxPats * kSampleBlocks];
   // a small join's query and report (host memory only)
   SmallReport small;
   SmallArgs query;
@@ -109,8 +110,6 @@ struct Exec {
   int64_t max_rows;
   gsmat_result* res;
   bool adaptive;
-
-  void sync_stream() { host_sync(s); }
 
   // table allocations not yet released or handed to the result
   std::vector<std::pair<void*, size_t>> live;
@@ -338,8 +337,9 @@ struct Exec {
       stage_back(part, dev_area->part, sizeof(int64_t) * c.nc * kSampleBlocks);
     } else {
       PinnedArea* h = pinned();
-      launch_sample_fanout(ss, h->part, s);
-      sync_stream();
+      const uint32_t report = next_report();
+      launch_sample_fanout(ss, h->part, s, h->words, report);
+      host_wait_words(h->words, c.nc * kSampleBlocks, report, s);
       std::copy(h->part, h->part + c.nc * kSampleBlocks, part);
     }
     int64_t sum[kMaxPats];
@@ -800,13 +800,23 @@ struct Exec {
     Tmp<int32_t> N(mem(), n, s), start(mem(), n, s);
     Tmp<int64_t> ts(mem(), nt + 1, s), P(mem(), n + 1, s);
     launch_count_expand(t.col[bc], n, pv, N.p, start.p, ts.p, s);
-    const int64_t m = scan_total(ts.p, nt, s);
+    int64_t m;
+    PinnedArea* h = dev_area ? nullptr : pinned();
+    const uint32_t report = next_report();
+    const bool scanned =
+        h && launch_scan_rows(N.p, n, ts.p, P.p, &h->total[0], &h->word, report, s);
+    if (scanned) {
+      host_wait_words(&h->word, 1, report, s);
+      m = h->total[0];
+    } else {
+      m = scan_total(ts.p, nt, s);
+    }
     add_out(si, m);
     if (m == 0) {
       release(t);
       return;
     }
-    launch_scan_add_i32(N.p, n, ts.p, P.p, s);
+    if (!scanned) launch_scan_add_i32(N.p, n, ts.p, P.p, s);
     expand_write(si, sp.tp, sp.orient, t, next, P.p, start.p, m);
   }
 

@@ -48,7 +48,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_tile_sums(int64_t* ts, int64_t 
     total[0] = carry;
     if (host_total) host_total[0] = carry;  // host memory, read after the report
   }
-  report_done(word, report);
+  report_one(word, report);
 }
 
 // Two tile-sum arrays (neither null) scanned in one pass (device.hpp).
@@ -64,6 +64,31 @@ __global__ __launch_bounds__(kBlock) void k_scan_add(const Tin* __restrict__ x, 
   const int64_t tot = scan_add_tile<Tin, Tout>(blockIdx.x, x, n, tile_off[blockIdx.x], out);
   if (write_total && threadIdx.x == 0 && blockIdx.x == gridDim.x - 1)
     out[n] = (Tout)(tile_off[blockIdx.x] + tot);
+}
+
+// The same with the tile sums not yet scanned, for at most kBlock * kItems
+// tiles: every workgroup adds up the sums before its own (a read of the sums
+// each, from the cache), and the last one reports the total.  A launch less
+// before the host knows the total, and one less in all.
+__global__ __launch_bounds__(kBlock) void k_scan_rows(const int32_t* __restrict__ x, int64_t n,
+                                                      const int64_t* __restrict__ ts,
+                                                      int64_t* __restrict__ out, int64_t* total,
+                                                      uint32_t* word, uint32_t report) {
+  const int b = (int)blockIdx.x;
+  int64_t before = 0;
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    const int i = j * kBlock + threadIdx.x;
+    if (i < b) before += ts[i];
+  }
+  const int64_t base = block_sum(before);
+  const bool last = blockIdx.x == gridDim.x - 1;
+  if (last) {
+    if (threadIdx.x == 0) total[0] = base + ts[b];
+    report_one(word, report);  // the host goes on while the offsets are written
+  }
+  const int64_t tot = scan_add_tile<int32_t, int64_t>(b, x, n, base, out);
+  if (threadIdx.x == 0 && last) out[n] = base + tot;
 }
 
 __global__ __launch_bounds__(kBlock) void k_tile_reduce_u32(const uint32_t* __restrict__ x,
@@ -571,6 +596,19 @@ __global__ void k_mp_partition(const int64_t* __restrict__ P, int64_t n, int64_t
   if (t > ntiles) return;
   split[t] = mp_split(P, n, J0, J1, t);
 }
+// A wave per split: for few splits, whose searches are one chain of loads
+// however many there are (7.3 -> 4.7 us for 500; of 137 000 splits a thread
+// each takes 9 us, a wave each 25 us).
+constexpr int64_t kWaveSplits = 8192;
+__global__ __launch_bounds__(kBlock) void k_mp_partition_wave(const int64_t* __restrict__ P,
+                                                              int64_t n, int64_t J0, int64_t J1,
+                                                              int64_t* __restrict__ split,
+                                                              int64_t ntiles) {
+  const int64_t t = (int64_t)blockIdx.x * kWaves + wave_id();
+  if (t > ntiles) return;
+  const int64_t a = mp_split_wave(P, n, J0, J1, t);
+  if (lane_id() == 0) split[t] = a;
+}
 
 template <int K>
 __global__ __launch_bounds__(kBlock) void k_write_expand(ColSet in, int kdyn,
@@ -605,10 +643,12 @@ __global__ __launch_bounds__(kBlock) void k_copy_cols(ColSet in, int64_t n, OutS
 
 // Sum of row lengths over a strided sample of the bound column; blockIdx.y
 // selects the candidate, blockIdx.x one of kSampleBlocks slices of the sample.
-__global__ __launch_bounds__(kBlock) void k_sample_fanout(SampleSet ss, int64_t* __restrict__ part) {
+__global__ __launch_bounds__(kBlock) void k_sample_fanout(SampleSet ss, int64_t* __restrict__ part,
+                                                          uint32_t* words, uint32_t report) {
   const int cand = blockIdx.y;
   const int64_t t = sample_fanout_slice(blockIdx.x, ss.col[cand], ss.n, ss.pv[cand]);
   if (threadIdx.x == 0) part[cand * kSampleBlocks + blockIdx.x] = t;
+  report_one(words ? words + cand * kSampleBlocks + blockIdx.x : nullptr, report);
 }
 
 // Rows to host memory, row-major.  The link (57 GB/s) is the bound, so a
@@ -687,6 +727,15 @@ void launch_scan_add_i32(const int32_t* N, int64_t n, const int64_t* tile_off, i
   GS_LAUNCH(GSMAT_K_SCAN, 12.0 * n,
             hipLaunchKernelGGL((k_scan_add<int32_t, int64_t>), dim3(tiles_for(n)), dim3(kBlock),
                                0, s, N, n, tile_off, P, 1));
+}
+
+bool launch_scan_rows(const int32_t* N, int64_t n, const int64_t* tile_sum, int64_t* P,
+                      int64_t* host_total, uint32_t* word, uint32_t report, hipStream_t s) {
+  if (ceil_div(n, kTile) > kTile) return false;
+  GS_LAUNCH(GSMAT_K_SCAN, 12.0 * n,
+            hipLaunchKernelGGL(k_scan_rows, dim3(tiles_for(n)), dim3(kBlock), 0, s, N, n, tile_sum,
+                               P, host_total, word, report));
+  return true;
 }
 
 void launch_tile_reduce_u32(const uint32_t* x, int64_t n, int64_t* tile_sum, hipStream_t s) {
@@ -903,6 +952,12 @@ void launch_compact_cols(ColSet in, int k, const uint8_t* flags, int64_t n,
 
 void launch_mp_partition(const int64_t* P, int64_t n, int64_t J0, int64_t J1, int64_t* split,
                          int64_t ntiles, hipStream_t s) {
+  if (ntiles < kWaveSplits) {
+    GS_LAUNCH(GSMAT_K_OTHER, 8.0 * (ntiles + 1),
+              hipLaunchKernelGGL(k_mp_partition_wave, dim3((unsigned)ceil_div(ntiles + 1, kWaves)),
+                                 dim3(kBlock), 0, s, P, n, J0, J1, split, ntiles));
+    return;
+  }
   GS_LAUNCH(GSMAT_K_OTHER, 8.0 * (ntiles + 1),
             hipLaunchKernelGGL(k_mp_partition, dim3((unsigned)ceil_div(ntiles + 1, kBlock)),
                                dim3(kBlock), 0, s, P, n, J0, J1, split, ntiles));
@@ -951,10 +1006,11 @@ void launch_copy_cols(ColSet in, int k, int64_t n, OutSet out, hipStream_t s) {
                                dim3(kBlock), 0, s, in, n, out));
 }
 
-void launch_sample_fanout(const SampleSet& ss, int64_t* part, hipStream_t s) {
+void launch_sample_fanout(const SampleSet& ss, int64_t* part, hipStream_t s, uint32_t* words,
+                          uint32_t report) {
   GS_LAUNCH(GSMAT_K_OTHER, 0.0,
             hipLaunchKernelGGL(k_sample_fanout, dim3(kSampleBlocks, (unsigned)ss.ncand),
-                               dim3(kBlock), 0, s, ss, part));
+                               dim3(kBlock), 0, s, ss, part, words, report));
 }
 
 int launch_pack_rows(const PackTask* tasks, int n, uint32_t* words, uint32_t report,
