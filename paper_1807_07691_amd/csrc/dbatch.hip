@@ -920,7 +920,7 @@ __global__ __launch_bounds__(kT) void k_d_count(const CTask* __restrict__ ct,
   int64_t* tsn = ctl->tsn;
   char* base = ctl->scr_base;
   for (int64_t b = blockIdx.x; b < nt; b += gridDim.x) {
-    const int qi = find_first_tile(w_cnt, nq, b);
+    const int qi = find_tile_wave(w_cnt, nq, b);
     const CTask& T = ct[qi];
     char* cb = base + cnt_off[qi];
     int64_t k;
@@ -1285,7 +1285,7 @@ __global__ __launch_bounds__(kBlock) void k_d_post(const WTask* __restrict__ wt,
   const int64_t* ts = ctl->ts;
   const int64_t* tsn = ctl->tsn;
   for (int64_t b = blockIdx.x; b < nt; b += gridDim.x) {
-    const int qi = find_first_tile(w_post, nq, b);
+    const int qi = find_tile_wave(w_post, nq, b);
     const WTask& T = wt[qi];
     const int64_t tile = b - w_post[qi];
     if (T.flags) b_compact_tile_any(T, tile, ts);
@@ -1311,13 +1311,13 @@ __global__ __launch_bounds__(kBlock) void k_d_partition(const WTask* __restrict_
 __global__ __launch_bounds__(kBlock) void k_d_write(const WTask* __restrict__ wt,
                                                     const int64_t* __restrict__ w_write, int nq,
                                                     const DCtl* __restrict__ ctl) {
-  __shared__ int32_t sE[kTile + 1];
-  __shared__ int32_t sRb[kTile + 1];
+  __shared__ int32_t sE[kTile];
+  __shared__ int32_t sRb[kTile];
   __shared__ uint16_t sRow[kTile];
-  const TileLds L{sE, sRb, sRow, nullptr};
+  const TileLds L{sE, sRb, sRow};
   const int64_t nt = ctl->n_write;
   for (int64_t b = blockIdx.x; b < nt; b += gridDim.x) {
-    const int qi = find_first_tile(w_write, nq, b);
+    const int qi = find_tile_wave(w_write, nq, b);
     const WTask& T = wt[qi];
     const int64_t t = b - w_write[qi];
     if (T.ridx) b_write_tile_any<true>(T, t, L);

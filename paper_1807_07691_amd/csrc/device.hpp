@@ -37,20 +37,33 @@ __device__ inline void report_one(uint32_t* word, uint32_t report) {
   __hip_atomic_store(word, report, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// v plus its value in the lane the DPP control names (zero where there is none
+// or the lane's row is not in the mask).
+template <int kCtrl, int kRows>
+__device__ inline int64_t dpp_add(int64_t v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)v, kCtrl, kRows, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), kCtrl, kRows, 0xf, false);
+  return v + (int64_t)((uint64_t)(uint32_t)hi << 32 | (uint32_t)lo);
+}
+
+// Inclusive scan and sum over a whole wave (all lanes active): moves within
+// rows of 16 lanes and row ends broadcast to the rows after, in registers; the
+// shuffles they replace went through LDS, two for each 64-bit value and step.
 __device__ inline int64_t wave_incl_scan(int64_t v) {
-  const int lane = lane_id();
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    int64_t t = __shfl_up(v, d, 64);
-    if (lane >= d) v += t;
-  }
+  v = dpp_add<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  v = dpp_add<0x118, 0xf>(v);
+  v = dpp_add<0x142, 0xa>(v);  // row_bcast 15: rows 0 and 2 to 1 and 3
+  v = dpp_add<0x143, 0xc>(v);  // row_bcast 31: rows 0 and 1 to 2 and 3
   return v;
 }
 
 __device__ inline int64_t wave_sum(int64_t v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-  return v;
+  v = wave_incl_scan(v);
+  const int lo = __builtin_amdgcn_readlane((int)v, 63);
+  const int hi = __builtin_amdgcn_readlane((int)(v >> 32), 63);
+  return (int64_t)((uint64_t)(uint32_t)hi << 32 | (uint32_t)lo);
 }
 
 // Exclusive scan of one value per thread over the workgroup.  Contains
@@ -814,16 +827,22 @@ __device__ inline int64_t mp_split_wave(const int64_t* __restrict__ P, int64_t n
 // 256-byte boundaries and the loop is shifted by the tile's offset modulo 64,
 // so every wave store covers whole 128-byte lines (unaligned tile starts
 // halved the store bandwidth); each thread handles U outputs per iteration
-// (four for up to three parent columns, else two) and issues all their loads
-// (neighbour ids, K parent values) before any store.  K is a compile-time
-// column count (-1: any count, in groups of 4).
-template <int K, class Out>
+// and issues all their loads (neighbour ids, K parent values) before any store.
+// K is a compile-time column count (-1: any count, in groups of 4).  A tile is
+// up to 33 wave stores of a column, 9 a wave, so U decides how many times a
+// wave waits for its loads: the kernels of one column count take the U that
+// keeps eight waves a SIMD, the batched write, whose registers are the largest
+// variant's, the one that keeps seven (fewer waves cost more than fewer waits:
+// 212 us a launch at U = 4 / 2, 203 at 5 / 3 / 2, 225 at 8 / 4 with five waves,
+// 250 with spills).
+template <int K, int U, class Out>
 __device__ inline void write_outputs(const ColSet& in, int kdyn, const int32_t* __restrict__ nbr,
                                      const uint16_t* sRow, const int32_t* sRb,
                                      const int32_t* sIdx, int64_t a0, int64_t ob, int nbt,
                                      const Out& out) {
-  constexpr int U = (K >= 0 && K <= 3) ? 4 : 2;
   const int k = K >= 0 ? K : kdyn;
+  // parent rows: consecutive from a0, or (compacted rows) their original indices
+  const int64_t row0 = sIdx ? 0 : a0;
   const int al = (int)(ob & 63);
   const int span = nbt + al;
   for (int q = threadIdx.x; q < span; q += U * kBlock) {
@@ -831,7 +850,7 @@ __device__ inline void write_outputs(const ColSet& in, int kdyn, const int32_t* 
     bool ok[U];
     int r[U];
     int32_t v[U];
-    int64_t row[U];
+    int32_t row[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       o[u] = q + u * kBlock - al;
@@ -841,15 +860,14 @@ __device__ inline void write_outputs(const ColSet& in, int kdyn, const int32_t* 
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       v[u] = ok[u] ? nbr[sRb[r[u]] + o[u]] : 0;
-      // parent rows: consecutive, or (compacted rows) their original indices
-      row[u] = sIdx ? (int64_t)sIdx[r[u]] : a0 + r[u];
+      row[u] = sIdx ? sIdx[r[u]] : r[u];
     }
     if (K >= 0) {
       int32_t x[U][K > 0 ? K : 1];
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int c = 0; c < K; ++c) x[u][c] = ok[u] ? in.c[c][row[u]] : 0;
+        for (int c = 0; c < K; ++c) x[u][c] = ok[u] ? (in.c[c] + row0)[row[u]] : 0;
 #pragma unroll
       for (int u = 0; u < U; ++u)
         if (ok[u]) {
@@ -862,7 +880,7 @@ __device__ inline void write_outputs(const ColSet& in, int kdyn, const int32_t* 
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
-          for (int c = 0; c < 4; ++c) x[u][c] = (ok[u] && c0 + c < k) ? in.c[c0 + c][row[u]] : 0;
+          for (int c = 0; c < 4; ++c) x[u][c] = (ok[u] && c0 + c < k) ? (in.c[c0 + c] + row0)[row[u]] : 0;
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -877,19 +895,19 @@ __device__ inline void write_outputs(const ColSet& in, int kdyn, const int32_t* 
 }
 
 // LDS staging of one path tile: each row's end offset and neighbour base
-// relative to the tile, the row of each output, and (compacted rows) each
-// row's input index.
+// relative to the tile, and the row of each output.  A tile with outputs
+// touches at most kTile rows, so the three arrays are 20 KiB exactly: eight
+// workgroups a CU.
 struct TileLds {
-  int32_t* sE;     // [kTile + 1]
-  int32_t* sRb;    // [kTile + 1]
+  int32_t* sE;     // [kTile]
+  int32_t* sRb;    // [kTile]
   uint16_t* sRow;  // [kTile]
-  int32_t* sIdx;   // [kTile + 1] with compacted rows (null: staged in sE after the walk)
 };
 
 // One path tile t of an expansion (all threads of the workgroup call it),
 // staged in L.  With ridx (kIdx), the rows are a compacted list: row i of
 // P/start is the input row ridx[i].
-template <int K, class Out, bool kIdx = false>
+template <int K, int U, class Out, bool kIdx = false>
 __device__ inline void write_expand_tile_in(const TileLds& L, int64_t t, const ColSet& in,
                                             int kdyn, const int64_t* __restrict__ P,
                                             const int32_t* __restrict__ start, int64_t n,
@@ -900,7 +918,6 @@ __device__ inline void write_expand_tile_in(const TileLds& L, int64_t t, const C
   int32_t* const sE = L.sE;
   int32_t* const sRb = L.sRb;
   uint16_t* const sRow = L.sRow;
-  int32_t* const sIdx = L.sIdx;
   const int64_t nb = J1 - J0;
   const int64_t total = n + nb;
   const int64_t d0 = t * (int64_t)kTile;
@@ -912,12 +929,26 @@ __device__ inline void write_expand_tile_in(const TileLds& L, int64_t t, const C
   const int64_t jb = J0 + b0;
   const int64_t rl = min(a1, n - 1);
   const int nr = (int)(rl - a0 + 1);
-  for (int i = threadIdx.x; i < nr; i += kBlock) {
-    const int64_t pb = P[a0 + i], pe = P[a0 + i + 1];
-    const int64_t er = pe - jb;
-    sE[i] = er > (int64_t)kTile + 1 ? kTile + 1 : (er < -1 ? -1 : (int32_t)er);
-    sRb[i] = (int32_t)((int64_t)start[a0 + i] + (jb - pb));
-    if (kIdx && sIdx) sIdx[i] = ridx[a0 + i];
+  // four rows per thread at a time, their loads in flight together
+  constexpr int kR = 4;
+  for (int i0 = threadIdx.x; i0 < nr; i0 += kR * kBlock) {
+    int64_t pb[kR], pe[kR];
+    int32_t st[kR];
+#pragma unroll
+    for (int u = 0; u < kR; ++u) {
+      const int i = min(i0 + u * kBlock, nr - 1);
+      pb[u] = P[a0 + i];
+      pe[u] = P[a0 + i + 1];
+      st[u] = start[a0 + i];
+    }
+#pragma unroll
+    for (int u = 0; u < kR; ++u) {
+      const int i = i0 + u * kBlock;
+      if (i >= nr) break;
+      const int64_t er = pe[u] - jb;
+      sE[i] = er > (int64_t)kTile + 1 ? kTile + 1 : (er < -1 ? -1 : (int32_t)er);
+      sRb[i] = (int32_t)((int64_t)st[u] + (jb - pb[u]));
+    }
   }
   __syncthreads();
   const int dl = min((int)threadIdx.x * kItems, nat + nbt);
@@ -939,30 +970,28 @@ __device__ inline void write_expand_tile_in(const TileLds& L, int64_t t, const C
     }
   }
   __syncthreads();
-  if (kIdx && !sIdx) {
-    // without an area of its own the row indices take the place of the row
-    // ends, which the walk no longer needs
+  if (kIdx) {
+    // the row indices take the place of the row ends, which the walk no longer
+    // needs
     for (int i = threadIdx.x; i < nr; i += kBlock) sE[i] = ridx[a0 + i];
     __syncthreads();
   }
-  write_outputs<K, Out>(in, kdyn, nbr, sRow, sRb, kIdx ? (sIdx ? sIdx : sE) : nullptr, a0,
-                        jb - J0, nbt, out);
+  write_outputs<K, U, Out>(in, kdyn, nbr, sRow, sRb, kIdx ? sE : nullptr, a0, jb - J0, nbt, out);
 }
 
 // write_expand_tile_in with the workgroup's own staging.
-template <int K, class Out, bool kIdx = false>
+template <int K, int U, class Out, bool kIdx = false>
 __device__ inline void write_expand_tile(int64_t t, const ColSet& in, int kdyn,
                                          const int64_t* __restrict__ P,
                                          const int32_t* __restrict__ start, int64_t n,
                                          const int32_t* __restrict__ nbr, int64_t J0, int64_t J1,
                                          const int64_t* __restrict__ split, const Out& out,
                                          const int32_t* __restrict__ ridx = nullptr) {
-  __shared__ int32_t sE[kTile + 1];
-  __shared__ int32_t sRb[kTile + 1];
+  __shared__ int32_t sE[kTile];
+  __shared__ int32_t sRb[kTile];
   __shared__ uint16_t sRow[kTile];
-  __shared__ int32_t sIdx[kIdx ? kTile + 1 : 1];
-  write_expand_tile_in<K, Out, kIdx>(TileLds{sE, sRb, sRow, sIdx}, t, in, kdyn, P, start, n, nbr,
-                                     J0, J1, split, out, ridx);
+  write_expand_tile_in<K, U, Out, kIdx>(TileLds{sE, sRb, sRow}, t, in, kdyn, P, start, n,
+                                        nbr, J0, J1, split, out, ridx);
 }
 
 }  // namespace dev

@@ -98,10 +98,10 @@ __global__ void k_b_partition(const WTask* __restrict__ tasks, const GItem* __re
 // occupancy of a single variant and no launch waits for another's tail.
 __global__ __launch_bounds__(kBlock) void k_b_write(const WTask* __restrict__ tasks,
                                                     const GItem* __restrict__ items, int nitems) {
-  __shared__ int32_t sE[kTile + 1];
-  __shared__ int32_t sRb[kTile + 1];
+  __shared__ int32_t sE[kTile];
+  __shared__ int32_t sRb[kTile];
   __shared__ uint16_t sRow[kTile];
-  const TileLds L{sE, sRb, sRow, nullptr};
+  const TileLds L{sE, sRb, sRow};
   const GItem& it = items[find_item(items, nitems, blockIdx.x)];
   const WTask& T = tasks[it.task];
   const int64_t t = (int64_t)blockIdx.x - it.w0;
@@ -115,10 +115,10 @@ __global__ __launch_bounds__(kBlock) void k_b_write_idx(const WTask* __restrict_
   const GItem& it = items[find_item(items, nitems, blockIdx.x)];
   const WTask& T = tasks[it.task];
   const int64_t t = (int64_t)blockIdx.x - it.w0;
-  __shared__ int32_t sE[kTile + 1];
-  __shared__ int32_t sRb[kTile + 1];
+  __shared__ int32_t sE[kTile];
+  __shared__ int32_t sRb[kTile];
   __shared__ uint16_t sRow[kTile];
-  b_write_tile<K, true>(T, t, TileLds{sE, sRb, sRow, nullptr});
+  b_write_tile<K, true>(T, t, TileLds{sE, sRb, sRow});
 }
 
 // Stable compaction of one tile of a filter or intersection task (K
