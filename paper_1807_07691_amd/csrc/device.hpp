@@ -90,6 +90,7 @@ __device__ inline int64_t block_excl_scan(int64_t v, int64_t* total) {
 template <int F>
 __device__ inline void block_excl_scan_n(const int64_t (&v)[F], int64_t (&ex)[F],
                                          int64_t (&tot)[F]) {
+  static_assert(F <= 16, "a row of 16 lanes of the workgroup's first waves per value");
   __shared__ int64_t ws[F][16];
   const int nw = (int)(blockDim.x >> 6);
   int64_t inc[F];
@@ -100,16 +101,23 @@ __device__ inline void block_excl_scan_n(const int64_t (&v)[F], int64_t (&ex)[F]
     for (int f = 0; f < F; ++f) ws[f][wave_id()] = inc[f];
   }
   __syncthreads();
+  // the waves' totals are scanned by a row of lanes per value, in place: every
+  // thread then reads two entries of a value instead of all sixteen
+  const int row = wave_id() * 4 + lane_id() / 16;
+  for (int f = row; f < (F + 3) / 4 * 4; f += nw * 4) {  // whole waves
+    const int q = lane_id() & 15;
+    int64_t a = f < F && q < nw ? ws[f][q] : 0;
+    a = dpp_add<0x111, 0xf>(a);
+    a = dpp_add<0x112, 0xf>(a);
+    a = dpp_add<0x114, 0xf>(a);
+    a = dpp_add<0x118, 0xf>(a);
+    if (f < F) ws[f][q] = a;
+  }
+  __syncthreads();
 #pragma unroll
   for (int f = 0; f < F; ++f) {
-    int64_t off = 0, t = 0;
-    for (int q = 0; q < nw; ++q) {
-      const int64_t a = ws[f][q];
-      if (q < wave_id()) off += a;
-      t += a;
-    }
-    ex[f] = off + inc[f] - v[f];
-    tot[f] = t;
+    ex[f] = (wave_id() ? ws[f][wave_id() - 1] : 0) + inc[f] - v[f];
+    tot[f] = ws[f][nw - 1];
   }
   __syncthreads();
 }
