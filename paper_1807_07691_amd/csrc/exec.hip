@@ -856,6 +856,11 @@ struct Exec {
 
 namespace gsmat {
 
+HostNote host_note() {
+  PinnedArea* h = pinned();
+  return HostNote{&h->total[0], &h->word};
+}
+
 Arena::Arena(DeviceMem* m, size_t b, hipStream_t st) : mem(m), bytes(b), s(st) {
   p = mem->alloc(bytes, s);
   if (!p) throw OomFail{bytes};

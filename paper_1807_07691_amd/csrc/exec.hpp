@@ -103,6 +103,14 @@ bool run_query(gsmat_store* st, const gsmat_query_plan* pl, int64_t budget_bytes
 void run_collect(gsmat_store* st, const gsmat_query_plan* pl, const Table* t0,
                  int64_t budget_bytes, hipStream_t s, std::vector<Table>* out);
 
+// Where the calling thread's launches leave one number for the host, and the
+// word that reports it (host_wait_words).
+struct HostNote {
+  int64_t* value;
+  uint32_t* word;
+};
+HostNote host_note();
+
 // Per-pattern statistics for the planner; lookups of constant endpoints go
 // to the device in one batch.
 std::vector<TpStat> pattern_stats(const gsmat_store* st, const gsmat_pattern* pats, int n,
