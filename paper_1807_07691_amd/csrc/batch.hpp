@@ -122,8 +122,6 @@ void run_batch_device_bgp(gsmat_store* st, const gsmat_pattern* pats, const int3
                           std::vector<gsmat_status>& status, std::vector<std::string>& msg,
                           std::vector<std::unique_ptr<gsmat_query_plan>>& fallback);
 
-// req and res may be host memory; each workgroup of kBlock requests writes
-// `report` to its word
 // Batches of at most kSmallBatch queries first run in one launch, a workgroup
 // per query (small.hip): out[i] as above, kDevFallback for the queries left to
 // the rounds.  512 workgroups of 16 waves are what the device holds at once;
@@ -136,6 +134,8 @@ void run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int3
                      int64_t budget, int64_t round_budget, int64_t max_rows, hipStream_t s,
                      std::vector<DevQueryOut>& out);
 
+// req and res may be host memory; each workgroup of kBlock requests writes
+// `report` to its word
 void launch_lookup_many(const LookupReq* req, int32_t n, const PredDesc* dout, const PredDesc* din,
                         OriPtrs out, OriPtrs in, LookupRes* res, uint32_t* words,
                         uint32_t report, hipStream_t s);

@@ -38,15 +38,6 @@ __device__ inline int find_tile_wave(const int64_t* __restrict__ w0, int n, int6
   }
   return __builtin_amdgcn_readfirstlane(lo);
 }
-__device__ inline int find_first_tile(const int64_t* __restrict__ w0, int n, int64_t b) {
-  int lo = 0, hi = n - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (w0[mid] <= b) lo = mid;
-    else hi = mid - 1;
-  }
-  return lo;
-}
 
 // Count / flag tile of one count-phase task, writing to N/start
 // (expansions) or flags; the tile sum is returned, and for expansions the

@@ -393,9 +393,10 @@ struct Exec {
   // most kSmallRows rows, and a first step does not list more (a scan of known
   // length is a view and needs no launch).  A table of so few rows costs the
   // general path 25 us to 60 us a step whatever its size; the launch takes 14 us
-  // for one or two steps and 30 us for four.  Sixteen queries, planned, joined
-  // and fetched, on 20 million triples: 4.49 -> 1.97 ms (3 to 5 patterns, 300 to
-  // 30 000 rows), 1.61 -> 1.10 ms (1 or 2 patterns, up to 100 rows).
+  // for one or two steps and 23 us for four.  Sixteen queries, planned, joined
+  // and fetched, on 20 million triples, with the fetch in reported packs: 4.6 -> 1.4
+  // ms (3 to 5 patterns, 300 to 30 000 rows), 1.65 -> 0.6 ms (1 or 2 patterns, up to
+  // 100 rows).
   bool small_fits(int si, const Table& t) const {
     if (t.n > kSmallRows) return false;
     if (!t.unit()) return true;

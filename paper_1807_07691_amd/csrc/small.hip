@@ -533,14 +533,19 @@ __global__ __launch_bounds__(kST) void k_small_join(SmallStore S,
           const int j = j0 + u * kST;
           v[u] = j < (int)m ? nbr[L.rb[r[u]] + j] : 0;
         }
-        for (int c = 0; c < k; ++c) {
-          const int32_t* src = L.col[c];
-          int32_t x[kSU];
+        for (int c0 = 0; c0 < k; c0 += 4) {  // four columns' loads in flight
+          int32_t x[4][kSU];
 #pragma unroll
-          for (int u = 0; u < kSU; ++u) x[u] = src[r[u]];
+          for (int c = 0; c < 4; ++c) {
+            const int32_t* src = L.col[min(c0 + c, k - 1)];
 #pragma unroll
-          for (int u = 0; u < kSU; ++u)
-            if (j0 + u * kST < (int)m) o[c * stride + j0 + u * kST] = x[u];
+            for (int u = 0; u < kSU; ++u) x[c][u] = src[r[u]];
+          }
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int u = 0; u < kSU; ++u)
+              if (c0 + c < k && j0 + u * kST < (int)m) o[(c0 + c) * stride + j0 + u * kST] = x[c][u];
         }
 #pragma unroll
         for (int u = 0; u < kSU; ++u)
@@ -567,9 +572,11 @@ __global__ __launch_bounds__(kST) void k_small_join(SmallStore S,
     __syncthreads();
   }
 
-  // The tables' stores have to be complete before the report can be seen;
-  // the report itself is one wave's, its last word after all others.
-  __threadfence();
+  // The tables' stores have to be complete before the report can be seen: each
+  // wave waits for its own to reach the L2, and the reporting wave's fence
+  // writes that back (a fence in all 16 waves cost 2 us).  The report itself is
+  // one wave's, its last word after all others.
+  __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's stores are in the L2
   __syncthreads();
   if (wave == 0) {
     if (lane < kMaxCols) {
