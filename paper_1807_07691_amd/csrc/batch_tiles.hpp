@@ -24,20 +24,6 @@ __device__ inline int find_item(const GItem* __restrict__ g, int n, int64_t b) {
   }
   return lo;
 }
-// The same for a tile of the whole workgroup: the wave looks at 64 entries
-// together, two dependent loads among 4096 queries instead of twelve (a tile of
-// the write spends about 10 us in all).  Called by whole waves; uniform.
-__device__ inline int find_tile_wave(const int64_t* __restrict__ w0, int n, int64_t b) {
-  int lo = 0, len = n;
-  while (len > 1) {
-    const int step = (len + 63) / 64;
-    const int i = lo + lane_id() * step;
-    const int c = (int)__popcll(__ballot(i < lo + len && w0[i] <= b));  // at least the first
-    lo += (c - 1) * step;
-    len = min(step, n - lo);
-  }
-  return __builtin_amdgcn_readfirstlane(lo);
-}
 
 // Count / flag tile of one count-phase task, writing to N/start
 // (expansions) or flags; the tile sum is returned, and for expansions the

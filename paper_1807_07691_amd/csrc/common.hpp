@@ -250,6 +250,10 @@ uint64_t* radix_sort_u64(uint64_t* keys, uint64_t* tmp, int64_t n, int lo_bit, i
                          int swap_vb, DeviceMem& mem, hipStream_t s);
 
 // build
+// Each of at most max_out workgroups writes the index of its first triple with an
+// id out of range (n: none) to out, which may be host memory; returns their number.
+int launch_check_ids(const int32_t* s, const int32_t* p, const int32_t* o, int64_t n, int32_t V,
+                     int32_t P, int64_t* out, int max_out, hipStream_t st);
 void launch_pack_keys(const int32_t* s, const int32_t* p, const int32_t* o, int64_t n, int vb,
                       uint64_t* k, hipStream_t st);
 void launch_flag_unique(const uint64_t* k, int64_t n, uint8_t* flags, int64_t* tile_sum,
@@ -266,8 +270,10 @@ void launch_row_fill(const uint64_t* k, int64_t n, int vb, const int64_t* pfe,
                      int32_t* ptr, int64_t* pfr, hipStream_t s);
 void launch_fill_i64(int64_t* p, int64_t n, int64_t v, hipStream_t s);
 // dense row pointers and bucket directories of every predicate that has them:
-// first[p] is predicate p's first tile of kTile entries (alike for predicates
-// without entries and their successor), tiles their number
+// first[p] is predicate p's first tile of kDenseTile (directories: kTile)
+// entries (alike for predicates without entries and their successor), tiles
+// their number
+constexpr int kDenseTile = 4096;
 void launch_dense_ptrs(const PredDesc* desc, const int64_t* first, int32_t P, int64_t tiles,
                        const int32_t* keys, const int32_t* ptr, int64_t V, int32_t* dense,
                        hipStream_t s);

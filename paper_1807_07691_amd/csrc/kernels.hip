@@ -246,6 +246,41 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(const uint64_t* __restric
 }
 
 // ---------------------------------------------------------------- index build
+// The first triple of the workgroup's with an id out of range.  Bound by the 12
+// bytes a triple it reads: 20 million triples 80 us, where the host's threads
+// need 1.6 ms to read them again.
+__global__ __launch_bounds__(kBlock) void k_check_ids(const int32_t* __restrict__ s,
+                                                      const int32_t* __restrict__ p,
+                                                      const int32_t* __restrict__ o, int64_t n,
+                                                      uint32_t V, uint32_t P,
+                                                      int64_t* __restrict__ out) {
+  constexpr int U = 4;
+  __shared__ int64_t wmin[kBlock / 64];
+  int64_t first = n;
+  const int64_t stride = (int64_t)gridDim.x * kBlock * U;
+  for (int64_t i0 = (int64_t)blockIdx.x * kBlock * U + threadIdx.x; i0 < n; i0 += stride) {
+    uint32_t a[U], b[U], c[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = min(i0 + (int64_t)u * kBlock, n - 1);
+      a[u] = (uint32_t)s[i];
+      b[u] = (uint32_t)p[i];
+      c[u] = (uint32_t)o[i];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (a[u] >= V || b[u] >= P || c[u] >= V)
+        first = min(first, min(i0 + (int64_t)u * kBlock, n - 1));
+  }
+  for (int d = 32; d > 0; d >>= 1) first = min(first, (int64_t)__shfl_xor((long long)first, d));
+  if (lane_id() == 0) wmin[wave_id()] = first;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kBlock / 64; ++w) first = min(first, wmin[w]);
+    out[blockIdx.x] = first;
+  }
+}
+
 __global__ void k_pack_keys(const int32_t* __restrict__ s, const int32_t* __restrict__ p,
                             const int32_t* __restrict__ o, int64_t n, int vb,
                             uint64_t* __restrict__ k) {
@@ -392,30 +427,29 @@ __global__ void k_fill_i64(int64_t* p, int64_t n, int64_t v) {
 }
 
 // Dense row pointers of every predicate that has them, one launch: tile b of
-// the launch is 2048 vertices of the predicate that owns it (first[p] its
+// the launch is kDenseTile vertices of the predicate that owns it (first[p] its
 // first tile).  dense[v] is the offset of the first row >= v.  The tile's rows
-// are found by one search and marked in LDS, and a scan of the marks gives
-// every vertex its row, so a pointer costs no search of its own (before: a
-// launch per predicate and 20 dependent loads per pointer).  89 predicates of
-// 2 million vertices: 2.82 -> 0.33 ms (2.2 TB/s written).
+// are found by one search and marked in a bit mask in LDS; a vertex's row is the
+// number of marks before it, so a pointer costs no search of its own.  The
+// offsets come from LDS too, where the lanes of a wave read few different
+// words: from memory a gather takes a clock per lane (8192 vertices a tile: 0.33
+// ms).  89 predicates of 2 million vertices: a mark per vertex and a scan over
+// them 0.32 ms, this 0.26 ms (2.7 TB/s written).
 __global__ __launch_bounds__(kBlock) void k_dense_ptrs(const PredDesc* __restrict__ desc,
                                                        const int64_t* __restrict__ first, int32_t P,
                                                        const int32_t* __restrict__ keys,
                                                        const int32_t* __restrict__ ptr, int64_t V,
                                                        int32_t* __restrict__ dense) {
-  __shared__ int32_t mark[kTile];      // rows with this id; then rows before the vertex
-  __shared__ int32_t off[kTile + 1];   // offsets of the tile's rows
+  constexpr int kWords = kDenseTile / 64, kPerWave = kWords / (kBlock / 64);
+  static_assert(kWords == 64, "a word a lane");
+  __shared__ unsigned long long mark[kWords];
+  __shared__ int32_t off[kDenseTile + 1];  // offsets of the tile's rows
   __shared__ int32_t lim[2];
   const int64_t b = blockIdx.x;
-  int lo = 0, hi = P - 1;  // the last predicate with first <= b
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (first[mid] <= b) lo = mid;
-    else hi = mid - 1;
-  }
+  const int lo = find_tile_wave(first, P, b);
   const PredDesc d = desc[lo];
-  const int64_t v0 = (b - first[lo]) * kTile;
-  const int nv = (int)min((int64_t)kTile, V + 1 - v0);
+  const int64_t v0 = (b - first[lo]) * kDenseTile;
+  const int nv = (int)min((int64_t)kDenseTile, V + 1 - v0);
   const int32_t* const pk = keys + d.row_base;
   const int32_t* const pp = ptr + d.ptr_base;
   if (wave_id() < 2) {
@@ -423,33 +457,35 @@ __global__ __launch_bounds__(kBlock) void k_dense_ptrs(const PredDesc* __restric
     const int32_t r = wave_lower_bound(pk, (int32_t)d.nr, (int32_t)min(v, (int64_t)INT32_MAX));
     if (lane_id() == 0) lim[wave_id()] = r;
   }
-  for (int i = threadIdx.x; i < kTile; i += kBlock) mark[i] = 0;
+  if (threadIdx.x < kWords) mark[threadIdx.x] = 0;
   __syncthreads();
   const int r0 = lim[0], nr = lim[1] - r0;  // ids in [v0, v0 + nv): at most nv rows
-  for (int i = threadIdx.x; i <= nr; i += kBlock) off[i] = pp[r0 + i];
-  for (int i = threadIdx.x; i < nr; i += kBlock) mark[pk[r0 + i] - v0] = 1;
-  __syncthreads();
-  int32_t m[kItems];
-  int64_t sum = 0;
-#pragma unroll
-  for (int j = 0; j < kItems; ++j) {
-    m[j] = mark[threadIdx.x * kItems + j];
-    sum += m[j];
-  }
-  int64_t tot;
-  int32_t ex = (int32_t)block_excl_scan(sum, &tot);
-#pragma unroll
-  for (int j = 0; j < kItems; ++j) {
-    mark[threadIdx.x * kItems + j] = ex;
-    ex += m[j];
+  for (int i = threadIdx.x; i <= nr; i += kBlock) {
+    off[i] = pp[r0 + i];
+    if (i == nr) break;
+    const int x = (int)(pk[r0 + i] - v0);
+    atomicOr(&mark[x >> 6], 1ull << (x & 63));
   }
   __syncthreads();
+  // rows before each word (every wave for itself)
+  const int c = (int)__popcll(mark[lane_id()]);
+  const int before = (int)wave_incl_scan(c) - c;
+  const int wave = __builtin_amdgcn_readfirstlane(wave_id());
   int32_t* const o = dense + d.dense_base + v0;
-  for (int i = threadIdx.x; i < nv; i += kBlock) o[i] = off[mark[i]];
+#pragma unroll 8
+  for (int j = 0; j < kPerWave; ++j) {
+    const int w = wave * kPerWave + j;
+    const unsigned long long m = mark[w];
+    const int at = __builtin_amdgcn_readlane(before, w);
+    const int r = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                                 __builtin_amdgcn_mbcnt_lo((unsigned)m, at));
+    const int i = w * 64 + lane_id();
+    if (i < nv) o[i] = off[r];
+  }
 }
 
 // Bucket directories of the other predicates, one launch (tiles as above, of
-// 2048 buckets): dir[b] is the first row with id >= b << shift, searched among
+// kTile buckets): dir[b] is the first row with id >= b << shift, searched among
 // the rows of the tile.
 __global__ __launch_bounds__(kBlock) void k_row_dirs(const PredDesc* __restrict__ desc,
                                                      const int64_t* __restrict__ first, int32_t P,
@@ -457,12 +493,7 @@ __global__ __launch_bounds__(kBlock) void k_row_dirs(const PredDesc* __restrict_
                                                      int32_t* __restrict__ dir) {
   __shared__ int32_t lim[2];
   const int64_t b = blockIdx.x;
-  int lo = 0, hi = P - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (first[mid] <= b) lo = mid;
-    else hi = mid - 1;
-  }
+  const int lo = find_tile_wave(first, P, b);
   const PredDesc d = desc[lo];
   const int64_t b0 = (b - first[lo]) * kTile;
   const int64_t nb = ((V - 1) >> d.dir_shift) + 2;  // entries
@@ -821,6 +852,16 @@ void launch_pack_keys(const int32_t* sv, const int32_t* p, const int32_t* o, int
                                vb, k));
 }
 
+int launch_check_ids(const int32_t* sv, const int32_t* p, const int32_t* o, int64_t n, int32_t V,
+                     int32_t P, int64_t* out, int max_out, hipStream_t s) {
+  if (n <= 0) return 0;
+  const unsigned g = (unsigned)std::min<int64_t>(max_out, ceil_div(n, 4 * kBlock));
+  GS_LAUNCH(GSMAT_K_OTHER, 12.0 * n,
+            hipLaunchKernelGGL(k_check_ids, dim3(g), dim3(kBlock), 0, s, sv, p, o, n, (uint32_t)V,
+                               (uint32_t)P, out));
+  return (int)g;
+}
+
 void launch_flag_unique(const uint64_t* k, int64_t n, uint8_t* flags, int64_t* tile_sum,
                         hipStream_t s) {
   GS_LAUNCH(GSMAT_K_OTHER, 9.0 * n,
@@ -860,7 +901,7 @@ void launch_dense_ptrs(const PredDesc* desc, const int64_t* first, int32_t P, in
                        const int32_t* keys, const int32_t* ptr, int64_t V, int32_t* dense,
                        hipStream_t s) {
   if (tiles <= 0) return;
-  GS_LAUNCH(GSMAT_K_OTHER, 4.0 * kTile * tiles,
+  GS_LAUNCH(GSMAT_K_OTHER, 4.0 * kDenseTile * tiles,
             hipLaunchKernelGGL(k_dense_ptrs, dim3((unsigned)tiles), dim3(kBlock), 0, s, desc, first,
                                P, keys, ptr, V, dense));
 }

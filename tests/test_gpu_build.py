@@ -67,3 +67,43 @@ def test_build_one_row_and_one_column(G):
     x = np.arange(n, dtype=np.int32)
     z = np.zeros(n, np.int32)
     check(G, np.concatenate([z, x]), np.concatenate([z, z + 1]), np.concatenate([x, z]), n, 2, 0)
+
+
+@pytest.mark.parametrize("n", [65_535, 65_536, 65_537, 1_050_001, 3_000_000])
+@pytest.mark.parametrize("which", ["s", "p", "o"])
+def test_bad_ids_on_the_device(G, n, which):
+    """The id check of loads around the size from which it runs on the device
+    (65536 triples): the first of several bad ids is named, at either end and
+    between; then the same arrays with good ids load."""
+    V, P = 50, 7
+    r = np.random.default_rng(n)
+    a = {"s": r.integers(0, V, n).astype(np.int32), "p": r.integers(0, P, n).astype(np.int32),
+         "o": r.integers(0, V, n).astype(np.int32)}
+    good = a[which].copy()
+    kind = "predicate" if which == "p" else "vertex"
+    for first in (0, 1023, n // 3, n - 1):
+        for bad in (-1, np.iinfo(np.int32).min, P if which == "p" else V):
+            a[which][:] = good
+            for i in {first, (first + n) // 2, n - 1}:
+                a[which][i] = bad
+            with pytest.raises(G.GsmatError) as e:
+                G.gsmat_load_triples(a["s"], a["p"], a["o"], V, P)
+            assert e.value.status == G.GSMAT_EINVAL
+            assert str(e.value).endswith(f"{kind} id out of range at triple {first}")
+    a[which][:] = good
+    st = G.gsmat_load_triples(a["s"], a["p"], a["o"], V, P)
+    G.gsmat_build_index(st)
+    d = np.unique(np.stack([a["s"], a["p"], a["o"]], 1), axis=0)
+    assert G.gsmat_store_stats(st)["n_triples"] == len(d)
+    st.close()
+
+
+@pytest.mark.parametrize("V", [63, 64, 4095, 4096, 4097, 8191, 8192])
+def test_dense_pointer_tiles(G, V):
+    """Dense pointers at the edges of their tiles (4096 vertices, V + 1 of them):
+    every row present, only the last, only the first of each 64."""
+    x = np.arange(V, dtype=np.int32)
+    parts = [x, x[-1:], x[::64]]
+    s = np.concatenate(parts)
+    p = np.concatenate([np.full(len(a), q, np.int32) for q, a in enumerate(parts)])
+    check(G, s, p, s[::-1].copy(), V, 3, 10 ** 6)
