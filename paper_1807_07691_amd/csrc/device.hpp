@@ -20,20 +20,34 @@ __device__ inline uint32_t mbcnt(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// The workgroup's report: every thread's stores to host memory, then the word.
+// Reports in host memory.  A wave's stores to host memory are seen by the host
+// before a later word only if that wave itself releases them: the wait for its
+// own stores is part of the release, and another wave's release does not wait
+// for them.  A release writes the whole L2 back, so a kernel whose workgroups
+// each report lets one wave make their stores.
+
+// The workgroup's report: every wave's stores to host memory, then the word.
 // Called by all threads; word null: nothing.
 __device__ inline void report_done(uint32_t* word, uint32_t report) {
   if (!word) return;
-  __threadfence_system();
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");  // system
   __syncthreads();
   if (threadIdx.x == 0)
     __hip_atomic_store(word, report, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// The same where thread 0 alone has written what is reported.
+// The same where one wave alone has written what is reported; called by its lanes.
+__device__ inline void report_wave(uint32_t* word, uint32_t report) {
+  if (!word) return;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
+  __builtin_amdgcn_wave_barrier();
+  if (lane_id() == 0)
+    __hip_atomic_store(word, report, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The same where thread 0 alone has.
 __device__ inline void report_one(uint32_t* word, uint32_t report) {
   if (!word || threadIdx.x != 0) return;
-  __threadfence_system();
   __hip_atomic_store(word, report, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 

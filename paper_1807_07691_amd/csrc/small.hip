@@ -573,9 +573,8 @@ __global__ __launch_bounds__(kST) void k_small_join(SmallStore S,
   }
 
   // The tables' stores have to be complete before the report can be seen: each
-  // wave waits for its own to reach the L2, and the reporting wave's fence
-  // writes that back (a fence in all 16 waves cost 2 us).  The report itself is
-  // one wave's, its last word after all others.
+  // wave waits for its own to reach the L2, and the reporting wave's release
+  // writes that back (a fence in all 16 waves cost 2 us).
   __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's stores are in the L2
   __syncthreads();
   if (wave == 0) {
@@ -599,8 +598,7 @@ __global__ __launch_bounds__(kST) void k_small_join(SmallStore S,
       rep->m = left_m;
       rep->start = left_start;
     }
-    __threadfence_system();
-    if (lane == 0) __hip_atomic_store(&rep->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    report_wave(&rep->seq, seq);
   }
 }
 
