@@ -40,6 +40,7 @@ struct Segment {
 // are views (into the store or an arena) or one owned allocation.
 struct Table {
   int64_t n = 0;
+  int64_t from = 0;  // rows of the table it was expanded from (0: none)
   int k = 0;
   const int32_t* col[kMaxCols] = {};
   int var[kMaxCols] = {};

@@ -77,3 +77,39 @@ def test_samples(G, n):
     one.close()
     pl.close()
     st.close()
+
+
+@pytest.mark.parametrize("fan", [1, 2, 3, 64])
+@pytest.mark.parametrize("n", [700, 6000])
+def test_filter_by_either_row(G, n, fan):
+    """Triangles whose last expansion binds the subject of the closing pattern,
+    below and above the run length (2) from which the pair is looked for in the
+    object's row; with a budget the runs are cut.  Rows against numpy."""
+    r = np.random.default_rng(n + fan)
+    x = np.arange(n)
+    y = n + x // 2  # two x for a y
+    z = 2 * n + r.integers(0, n, (n, fan))  # subjects of y's pairs
+    ys = n + np.arange(n)
+    close = r.random((n, fan)) < 0.3
+    cz, cx = z[x // 2][close], np.repeat(x, close.sum(1))  # (z, x) closes
+    hub = 2 * n + np.arange(n)  # a long row: every z meets x = 0
+    s = np.concatenate([x, z.ravel(), cz, hub])
+    p = np.concatenate([np.zeros(n), np.ones(n * fan), np.full(len(cz) + n, 2)])
+    o = np.concatenate([y, np.repeat(ys, fan), cx, np.zeros(n)])
+    t = np.unique(np.stack([s, p, o], 1).astype(np.int32), axis=0)
+    st = G.gsmat_load_triples(*(np.ascontiguousarray(t[:, i]) for i in range(3)), 3 * n, 3)
+    G.gsmat_build_index(st)
+    pairs = set(map(tuple, t[t[:, 1] == 2][:, [0, 2]].tolist()))
+    zy = np.unique(t[t[:, 1] == 1][:, [2, 0]], axis=0)
+    lo, hi = np.searchsorted(zy[:, 0], y), np.searchsorted(zy[:, 0], y, "right")
+    want = sorted((int(a), int(b), int(c)) for a, b, l, h in zip(x, y, lo, hi)
+                  for c in zy[l:h, 1] if (int(c), int(a)) in pairs)
+    for mode in (G.PLAN_ADAPTIVE, G.PLAN_DEFAULT, G.PLAN_PAPER):
+        for budget in (0, 20_000):
+            pl = G.gsmat_plan(st, [(-1, 0, -2), (-3, 1, -2), (-3, 2, -1)], mode)
+            res = G.gsmat_join(st, pl, budget)
+            print(f"[gpu] filter rows n={n} fan={fan} mode={mode} budget={budget}", flush=True)
+            assert sorted(map(tuple, G.gsmat_fetch_bindings(res).tolist())) == want
+            res.close()
+            pl.close()
+    st.close()
