@@ -126,7 +126,7 @@ void run_batch_device_bgp(gsmat_store* st, const gsmat_pattern* pats, const int3
 // per query (small.hip): out[i] as above, kDevFallback for the queries left to
 // the rounds.  512 workgroups of 16 waves are what the device holds at once;
 // above that a batch fills the rounds' launches, whose fixed cost (about 90 us
-// a round) it shares.  60 queries of up to 30 000 rows: 625 -> 270 us.
+// a round) it shares.  60 queries of up to 30 000 rows: 625 -> 235 us.
 constexpr int32_t kSmallBatch = 512;
 // round_budget > 0 bounds the bytes written for them in total (a query above
 // it is left).

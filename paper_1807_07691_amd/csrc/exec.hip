@@ -1462,7 +1462,7 @@ struct FetchSpan {
 // Fetches the spans through the calling thread's transfer area: pieces of at
 // most one part, in order, as many in a launch as fit the part, a part packed
 // by the device while the other is copied out.  Sixty answers of a batch, 4.1 MB:
-// 1.03 ms one by one, 0.67 ms together.
+// 1.0 ms one by one, 0.31 ms together.
 void fetch_spans(const FetchSpan* sp, int n, hipStream_t s) {
   uint64_t bytes = 0;
   for (int i = 0; i < n; ++i)

@@ -688,7 +688,7 @@ __global__ __launch_bounds__(kBlock) void k_sample_fanout(SampleSet ss, int64_t*
 // tile of kBlock rows is turned in LDS and leaves in 16-byte stores that a
 // wave makes to consecutive addresses.  Writing where the host reads takes
 // the device copy, the copy command and the wait for the stream out of a
-// fetch: of up to 100 rows 35 -> 16.5 us, of 3 million rows of 4 columns 5.2 -> 4.3 ms.
+// fetch: of up to 100 rows 35 -> 11.5 us, of 3 million rows of 4 columns 5.2 -> 4.3 ms.
 // One wave makes a workgroup's stores, so that its report needs one write-back
 // of the L2 and not one from every wave: 40 000 rows of 3 columns 21 -> 12.5 us
 // (8.4 at the link's rate), 350 000 rows 99 -> 84 us.
