@@ -270,6 +270,15 @@ gsmat_status gsmat_join_batch(gsmat_store* st, const gsmat_query_plan* const* pl
  * EINVAL for another value. */
 gsmat_status gsmat_set_batch_engine(gsmat_store* st, int32_t engine);
 
+/* 1 (default): what stays within a few thousand rows is run in one launch: the
+ * steps of a query over tables of at most 4096 rows by one workgroup
+ * (gsmat_join, gsmat_join_noalloc, the queries of a batch or of a served step,
+ * a workgroup each), and the selections of OPTIONAL and FILTER over as many.
+ * 0: everything takes the step-by-step launches and the batched rounds.  The
+ * rows, their order and the step counters are the same.  For timing one way
+ * against the other and for tests.  EINVAL for another value. */
+gsmat_status gsmat_set_small_joins(gsmat_store* st, int32_t on);
+
 /* Starting sizes, in bytes, of the device-driven batch's output slab and
  * scratch region for the next gsmat_join_batch on the store (0: 256 MiB and
  * 128 MiB).  After every batch the store keeps the sizes that batch needed

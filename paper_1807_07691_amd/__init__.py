@@ -43,7 +43,7 @@ EXPORTED = [
     "gsmat_autotune_batch", "gsmat_expand_strategy", "gsmat_set_batch_engine",
     "gsmat_set_batch_regions", "gsmat_batch_round_stats", "gsmat_join_noalloc",
     "gsmat_set_batch_tuning", "gsmat_get_batch_tuning", "gsmat_join_ext",
-    "gsmat_join_batch_bgp", "gsmat_fetch_bindings_many",
+    "gsmat_join_batch_bgp", "gsmat_fetch_bindings_many", "gsmat_set_small_joins",
 ]
 
 
@@ -84,6 +84,8 @@ def _load():
     L.gsmat_set_sparse_expand.argtypes = [vp, ctypes.c_double, i64]
     L.gsmat_set_batch_engine.restype = i32
     L.gsmat_set_batch_engine.argtypes = [vp, i32]
+    L.gsmat_set_small_joins.restype = i32
+    L.gsmat_set_small_joins.argtypes = [vp, i32]
     L.gsmat_set_batch_regions.restype = i32
     L.gsmat_set_batch_regions.argtypes = [vp, i64, i64]
     L.gsmat_batch_round_stats.restype = i32
@@ -716,6 +718,12 @@ def gsmat_set_batch_engine(store, engine):
     """gsmat_join_batch's rounds: ENGINE_DEVICE (default, device-driven) or
     ENGINE_HOST (host-driven)."""
     _check(_lib.gsmat_set_batch_engine(store.h, int(engine)))
+
+
+def gsmat_set_small_joins(store, on):
+    """True (default): what has few rows is run in one launch; False: by the
+    step-by-step launches and the batched rounds.  The rows do not change."""
+    _check(_lib.gsmat_set_small_joins(store.h, int(on)))
 
 
 def gsmat_set_batch_regions(store, out_bytes=0, scratch_bytes=0):

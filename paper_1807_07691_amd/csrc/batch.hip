@@ -1001,6 +1001,7 @@ struct gsmat_server {
   // The admitted queries that have not started, in one launch; what it does
   // not finish takes part in the rounds.
   void run_fresh() {
+    if (!st->small_joins) return;
     std::vector<const gsmat_query_plan*> plans;
     std::vector<size_t> at;
     for (size_t i = 0; i < bt.q.size() && plans.size() < (size_t)kSmallBatch; ++i) {
@@ -1176,7 +1177,7 @@ namespace {
 void run_batch_any(gsmat_store* st, const gsmat_query_plan* const* plans, int32_t n,
                    int64_t budget_bytes, int64_t max_rows, hipStream_t s,
                    std::vector<DevQueryOut>& out) {
-  if (n > kSmallBatch) {
+  if (n > kSmallBatch || !st->small_joins) {
     run_batch_device(st, plans, n, budget_bytes, max_rows, s, out);
     return;
   }
@@ -1265,7 +1266,7 @@ extern "C" gsmat_status gsmat_join_batch_bgp(gsmat_store* st, const gsmat_patter
     std::vector<gsmat_status> prc;
     std::vector<std::string> pmsg;
     std::vector<std::unique_ptr<gsmat_query_plan>> fb;
-    if (n_queries <= kSmallBatch) {
+    if (n_queries <= kSmallBatch && st->small_joins) {
       PlanPrep P;
       plan_prepare(st, pats, n_pats, n_queries, mode, s, &P);
       fb.resize(n_queries);
@@ -1576,6 +1577,15 @@ extern "C" gsmat_status gsmat_set_batch_engine(gsmat_store* st, int32_t engine) 
     if (!st) throw StatusFail{GSMAT_EINVAL, "store is NULL"};
     if (engine != 0 && engine != 1) throw StatusFail{GSMAT_EINVAL, "engine must be 0 or 1"};
     st->batch_engine = engine;
+    return GSMAT_OK;
+  });
+}
+
+extern "C" gsmat_status gsmat_set_small_joins(gsmat_store* st, int32_t on) {
+  return guarded([&]() -> gsmat_status {
+    if (!st) throw StatusFail{GSMAT_EINVAL, "store is NULL"};
+    if (on != 0 && on != 1) throw StatusFail{GSMAT_EINVAL, "on must be 0 or 1"};
+    st->small_joins = on;
     return GSMAT_OK;
   });
 }

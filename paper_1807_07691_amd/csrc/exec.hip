@@ -983,7 +983,7 @@ bool run_query(gsmat_store* st, const gsmat_query_plan* pl, int64_t budget_bytes
   }
   Exec ex{st, pl, s, budget_bytes, max_rows, res, pl->mode == GSMAT_PLAN_ADAPTIVE, {},
           mem, (PinnedArea*)dev_area};
-  ex.small = small;
+  ex.small = small && st->small_joins;
   Table unit;
   unit.n = 1;
   unit.k = 0;
@@ -1151,6 +1151,7 @@ void run_collect(gsmat_store* st, const gsmat_query_plan* pl, const Table* t0,
   counters.st = st;
   counters.stream = s;
   Exec ex{st, pl, s, budget_bytes, -1, &counters, true, {}, nullptr, nullptr, out};
+  ex.small = st->small_joins;
   Table t;
   if (t0) {
     if (t0->owned) throw StatusFail{GSMAT_EHIP, "internal: a starting table must not own memory"};

@@ -477,7 +477,7 @@ struct XRun {
       run_collect(st, pl.get(), &t0, budget, s, &tabs);
       std::vector<std::shared_ptr<Arena>> from = P.keep;
       from.push_back(rid);
-      if (P.n <= kXSmall && tabs.size() <= (size_t)kXTables) {
+      if (st->small_joins && P.n <= kXSmall && tabs.size() <= (size_t)kXTables) {
         XSelect x;
         x.filter = 0;
         x.tables = 0;
@@ -554,7 +554,7 @@ struct XRun {
       if (P.n == 0) continue;
       ColSet cols{};
       for (int c = 0; c < P.k; ++c) cols.c[P.var[c]] = P.col[c];
-      if (P.n <= kXSmall) {
+      if (st->small_joins && P.n <= kXSmall) {
         XSelect x;
         x.filter = 1;
         x.tables = 0;
