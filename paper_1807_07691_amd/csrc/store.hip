@@ -80,32 +80,15 @@ void copy_in(void* d, const void* h, size_t bytes, hipStream_t s) {
   }
 }
 
-// The first triple with an id out of range (n: none).  Three arrays read at
-// memory speed: one thread takes 8 ms for 20 million triples, as long as their
-// copy to the device, so the host pool shares them.
+// The first triple with an id out of range (n: none), by the host: of small
+// loads, and of those that did not reach the device.
 int64_t first_bad_triple(const int32_t* s, const int32_t* p, const int32_t* o, int64_t n, int32_t V,
                          int32_t P) {
-  const uint32_t v = (uint32_t)V, q = (uint32_t)P;
-  std::atomic<int64_t> first{n};
-  host_parallel_for(n, (int64_t)1 << 17, [&](int64_t lo, int64_t hi) {
-    constexpr int64_t kStep = 4096;
-    for (int64_t a = lo; a < hi && a < first.load(std::memory_order_relaxed); a += kStep) {
-      const int64_t b = std::min(hi, a + kStep);
-      uint32_t bad = 0;
-      for (int64_t i = a; i < b; ++i)
-        bad |= (uint32_t)((uint32_t)s[i] >= v) | (uint32_t)((uint32_t)o[i] >= v) |
-               (uint32_t)((uint32_t)p[i] >= q);
-      if (!bad) continue;
-      for (int64_t i = a; i < b; ++i)
-        if ((uint32_t)s[i] >= v || (uint32_t)o[i] >= v || (uint32_t)p[i] >= q) {
-          int64_t f = first.load();
-          while (i < f && !first.compare_exchange_weak(f, i)) {
-          }
-          return;
-        }
-    }
-  });
-  return first.load();
+  for (int64_t i = 0; i < n; ++i)
+    if ((uint32_t)s[i] >= (uint32_t)V || (uint32_t)o[i] >= (uint32_t)V ||
+        (uint32_t)p[i] >= (uint32_t)P)
+      return i;
+  return n;
 }
 
 int64_t read_i64(const int64_t* d, hipStream_t s) {
@@ -421,6 +404,8 @@ extern "C" gsmat_status gsmat_load_triples(const int32_t* s, const int32_t* p, c
       }
       GS_HIP(hipStreamSynchronize(hs));
     } catch (...) {
+      (void)hipStreamSynchronize(hs);  // nothing may still write them
+      free_raw();
       if (on_device) check_host();
       throw;
     }
