@@ -1020,7 +1020,7 @@ struct gsmat_server {
       if (out[j].state == kDevFallback) continue;
       b.state = out[j].state == kDevDone ? kDone : kFailed;
       b.status = out[j].status;
-      b.res.reset(out[j].res);
+      b.res = std::move(out[j].res);
       b.t = Table();
     }
   }
@@ -1190,14 +1190,9 @@ void run_batch_any(gsmat_store* st, const gsmat_query_plan* const* plans, int32_
       at.push_back(i);
     }
   if (rest.empty()) return;
-  try {
-    std::vector<DevQueryOut> dq;
-    run_batch_device(st, rest.data(), (int32_t)rest.size(), budget_bytes, max_rows, s, dq);
-    for (size_t j = 0; j < at.size(); ++j) out[at[j]] = dq[j];
-  } catch (...) {
-    for (DevQueryOut& o : out) gsmat_result_free(o.res);
-    throw;
-  }
+  std::vector<DevQueryOut> dq;
+  run_batch_device(st, rest.data(), (int32_t)rest.size(), budget_bytes, max_rows, s, dq);
+  for (size_t j = 0; j < at.size(); ++j) out[at[j]] = std::move(dq[j]);
 }
 
 // gsmat_join_batch with device-driven rounds: the queries that leave the
@@ -1227,7 +1222,7 @@ gsmat_status join_batch_device(gsmat_store* st, const gsmat_query_plan* const* p
       if (rc == GSMAT_OK) out[i] = r.release();
       else err = gsmat_last_error();
     } else if (dq[i].state == kDevDone) {
-      out[i] = dq[i].res;
+      out[i] = dq[i].res.release();
     } else if (rc == GSMAT_ETOOBIG) {
       err = "result exceeds max_rows (" + std::to_string(max_rows) + ")";
     } else {
@@ -1282,8 +1277,8 @@ extern "C" gsmat_status gsmat_join_batch_bgp(gsmat_store* st, const gsmat_patter
       }
       std::vector<DevQueryOut> vq;
       run_batch_any(st, valid.data(), (int32_t)valid.size(), budget_bytes, max_rows, s, vq);
-      dq.assign(n_queries, DevQueryOut{nullptr, kDevFailed, GSMAT_OK});
-      for (size_t j = 0; j < at.size(); ++j) dq[at[j]] = vq[j];
+      dq.resize(n_queries);
+      for (size_t j = 0; j < at.size(); ++j) dq[at[j]] = std::move(vq[j]);
       prc = P.rc;
       pmsg = P.msg;
     } else {
@@ -1312,7 +1307,7 @@ extern "C" gsmat_status gsmat_join_batch_bgp(gsmat_store* st, const gsmat_patter
           if (rc == GSMAT_OK) out[i] = r.release();
           else err = gsmat_last_error();
         } else if (dq[i].state == kDevDone) {
-          out[i] = dq[i].res;
+          out[i] = dq[i].res.release();
         } else if (rc == GSMAT_ETOOBIG) {
           err = "result exceeds max_rows (" + std::to_string(max_rows) + ")";
         } else {

@@ -79,16 +79,15 @@ __host__ __device__ inline bool sparse_expand(double theta, int64_t min_rows, in
 }
 
 // Device-driven batched join (dbatch.hip): every plan evaluated with its
-// state on the device.  out[i]: state kDevDone with res set (owned by the
-// caller), kDevFallback (the query left the batch: run it alone), or
+// state on the device.  out[i]: state kDevDone with res set, kDevFallback (the query left the batch: run it alone), or
 // kDevFailed with status.
 enum : int32_t { kDevDone = 0, kDevFallback = 1, kDevFailed = 2 };
 constexpr int kStatRounds = 64;  // rounds recorded per device-driven batch
 constexpr int kStatFields = 8;
 struct DevQueryOut {
-  gsmat_result* res;
-  int32_t state;
-  gsmat_status status;
+  std::unique_ptr<gsmat_result> res;
+  int32_t state = kDevFailed;
+  gsmat_status status = GSMAT_OK;
 };
 void run_batch_device(gsmat_store* st, const gsmat_query_plan* const* plans, int32_t n,
                       int64_t budget, int64_t max_rows, hipStream_t s,

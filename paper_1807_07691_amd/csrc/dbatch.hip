@@ -1488,7 +1488,8 @@ struct PackedBatch {
 void run_batch_packed(gsmat_store* st, PackedBatch& pb, int64_t budget, int64_t max_rows,
                       hipStream_t s, std::vector<DevQueryOut>& out) {
   const int32_t nq = pb.nq;
-  out.assign(nq, DevQueryOut{nullptr, kDevDone, GSMAT_OK});
+  out.clear();
+  out.resize(nq);
   if (nq == 0) return;
   DeviceMem* mem = st->mem.get();
   const int mp = pb.mp, ms = pb.ms, mv = pb.mv;
@@ -1719,7 +1720,7 @@ void run_batch_packed(gsmat_store* st, PackedBatch& pb, int64_t budget, int64_t 
       res->rows = r.rows;
       res->segs.push_back(seg);
     }
-    o.res = res.release();
+    o.res = std::move(res);
     o.state = kDevDone;
   }
 }
@@ -1831,18 +1832,18 @@ void run_batch_device_bgp(gsmat_store* st, const gsmat_pattern* pats, const int3
   };
   std::vector<DevQueryOut> dq;
   run_batch_packed(st, pb, budget, max_rows, s, dq);
-  out.assign(nq, DevQueryOut{nullptr, kDevFailed, GSMAT_OK});
+  out.clear();
+  out.resize(nq);
   fallback.clear();
   fallback.resize(nq);
   for (int32_t k = 0; k < pb.nq; ++k) {
     const int i = vi[k];
-    out[i] = dq[k];
     if (P.rc[i] != GSMAT_OK) {  // planning failed after all: drop any result
-      if (out[i].res) gsmat_result_free(out[i].res);
-      out[i] = DevQueryOut{nullptr, kDevFailed, P.rc[i]};
+      out[i].status = P.rc[i];
       continue;
     }
-    if (dq[k].state == kDevFallback) {  // runs alone: it needs its plan object
+    out[i] = std::move(dq[k]);
+    if (out[i].state == kDevFallback) {  // runs alone: it needs its plan object
       fallback[i].reset(new gsmat_query_plan);
       const gsmat_status rc = plan_build(st, pats, n_pats, mode, P, i, fallback[i].get());
       if (rc != GSMAT_OK) throw StatusFail{rc, P.msg[i]};

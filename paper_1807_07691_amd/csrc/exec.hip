@@ -999,7 +999,9 @@ bool run_query(gsmat_store* st, const gsmat_query_plan* pl, int64_t budget_bytes
 void run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int32_t nq,
                      int64_t budget, int64_t round_budget, int64_t max_rows, hipStream_t s,
                      std::vector<DevQueryOut>& out) {
-  out.assign(nq, DevQueryOut{nullptr, kDevFallback, GSMAT_OK});
+  out.clear();
+  out.resize(nq);
+  for (DevQueryOut& o : out) o.state = kDevFallback;
   struct One {
     int q;  // the query
     std::unique_ptr<gsmat_result> res;
@@ -1026,7 +1028,7 @@ void run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int3
     for (const gsmat_pattern& q : pl->pats)
       absent |= q.p >= st->P || (!is_var(q.s) && q.s >= st->V) || (!is_var(q.o) && q.o >= st->V);
     if (absent) {  // matches nothing
-      out[i] = DevQueryOut{o.res.release(), kDevDone, GSMAT_OK};
+      out[i] = DevQueryOut{std::move(o.res), kDevDone, GSMAT_OK};
       continue;
     }
     o.ex.reset(new Exec{st, pl, s, budget, max_rows, o.res.get(), pl->mode == GSMAT_PLAN_ADAPTIVE});
@@ -1128,16 +1130,10 @@ void run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int3
       return GSMAT_OK;
     });
     settled &= rc == GSMAT_OK && o.ex->settled;
-    out[o.q] = rc == GSMAT_OK ? DevQueryOut{o.res.release(), kDevDone, GSMAT_OK}
+    out[o.q] = rc == GSMAT_OK ? DevQueryOut{std::move(o.res), kDevDone, GSMAT_OK}
                               : DevQueryOut{nullptr, kDevFailed, rc};
   }
-  try {
-    if (!settled) host_sync(s);
-  } catch (...) {
-    for (DevQueryOut& o : out) delete o.res;
-    out.clear();
-    throw;
-  }
+  if (!settled) host_sync(s);
 }
 
 void run_collect(gsmat_store* st, const gsmat_query_plan* pl, const Table* t0,
