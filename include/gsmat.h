@@ -370,6 +370,8 @@ typedef struct gsmat_tune_report {
 /* Autotuner over the batched join's settings, one at a time in the order
  * theta, count_items, intersect: runs gsmat_join_batch on the plans once
  * untimed, then times each candidate of the setting with the others fixed
+ * (always by the rounds, as with gsmat_set_small_joins(st, 0): the settings are
+ * theirs)
  * and keeps the fastest (the store's current value stays unless another is
  * faster by more than 3 %) before tuning the next.  With the host-driven
  * engine only theta is tuned.  The rows of any later join do not depend on

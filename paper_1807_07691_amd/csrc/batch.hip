@@ -1694,6 +1694,13 @@ extern "C" gsmat_status gsmat_autotune_batch(gsmat_store* st,
     static const int32_t kItemsCand[3] = {4, 8, 16};
     static const int32_t kIsectCand[3] = {GSMAT_ISECT_SEARCH, GSMAT_ISECT_WINDOW,
                                           GSMAT_ISECT_MERGE};
+    // the settings are the rounds': a batch of few queries takes them too here
+    struct Rounds {
+      gsmat_store* st;
+      int32_t on;
+      explicit Rounds(gsmat_store* s_) : st(s_), on(s_->small_joins) { st->small_joins = 0; }
+      ~Rounds() { st->small_joins = on; }
+    } rounds(st);
     time_batch(true);  // allocator, caches and round hints warm
     tune([&](double v) { st->sparse_theta = v; }, [&] { return st->sparse_theta; }, kTheta,
          kTuneCandidates, r.theta_ms);

@@ -34,7 +34,7 @@ def _rounds(G, st, queries, mode):
     res, _ = G.gsmat_join_batch(st, plans, as_set=True)
     res.close()
     plans.close()
-    return sum(r[G.ROUND_STAT_FIELDS[0]] for r in G.gsmat_batch_round_stats(st))
+    return sum(r["tasks"] for r in G.gsmat_batch_round_stats(st))
 
 
 def test_small_batches_take_the_rounds(G, tiny):
@@ -147,3 +147,24 @@ def test_ext_both_ways(G, tiny):
         r = G.gsmat_join_ext(st, pats, filt, nv)
         assert np.array_equal(B._sorted(G.gsmat_fetch_bindings(r)), rows)
         r.close()
+
+
+def test_autotuner_times_the_rounds(G):
+    """Also of plans that a batch would finish in one small launch."""
+    rng = np.random.default_rng(5)
+    s, p, o = (rng.integers(0, hi, 3000).astype(np.int32) for hi in (400, 3, 400))
+    st = B._store(G, s, p, o, 400, 3)
+    G.gsmat_set_small_joins(st, 1)
+    plans, _ = G.gsmat_plan_batch(st, [[[7, 0, -1], [-1, 1, -2]]] * 20, G.PLAN_ADAPTIVE,
+                                  as_set=True)
+    G.gsmat_autotune_batch(st, plans)
+    assert sum(r["tasks"] for r in G.gsmat_batch_round_stats(st)) >= 20
+    pl = G.gsmat_plan(st, [[7, 0, -1], [-1, 1, -2]], G.PLAN_ADAPTIVE)
+    G.gsmat_prof_enable()
+    G.gsmat_join(st, pl).close()
+    n = sum(k["launches"] for k in G.gsmat_prof_read().values())
+    G.gsmat_prof_enable(0)
+    assert n <= 2, "the store's setting is as it was"
+    pl.close()
+    plans.close()
+    st.close()
