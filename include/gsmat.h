@@ -571,9 +571,9 @@ gsmat_status gsmat_release_pools(void);
 
 /* ---- instrumentation ----------------------------------------------------- */
 
-/* Rounds of the store's last device-driven gsmat_join_batch that took any (at
- * most 64 recorded): *n_rounds receives their number and out[8 * i + f] (for i <
- * cap) round i's f-th figure: tasks counted, count tiles, post tiles
+/* Rounds of the store's last device-driven gsmat_join_batch (at most 64
+ * recorded; none where every query finished without rounds): *n_rounds
+ * receives their number and out[8 * i + f] (for i < cap) round i's f-th figure: tasks counted, count tiles, post tiles
  * (row offsets, compacted rows, filter and intersection compactions), write
  * tiles, split entries, output bytes allocated, candidate expansions
  * sampled, tasks deferred for lack of memory.  Host only. */

@@ -1177,6 +1177,7 @@ namespace {
 void run_batch_any(gsmat_store* st, const gsmat_query_plan* const* plans, int32_t n,
                    int64_t budget_bytes, int64_t max_rows, hipStream_t s,
                    std::vector<DevQueryOut>& out) {
+  st->dbatch_rounds = false;
   if (n > kSmallBatch || !st->small_joins) {
     run_batch_device(st, plans, n, budget_bytes, max_rows, s, out);
     return;
@@ -1628,7 +1629,7 @@ extern "C" gsmat_status gsmat_batch_round_stats(const gsmat_store* st, int64_t* 
   return guarded([&]() -> gsmat_status {
     if (!st || !n_rounds) throw StatusFail{GSMAT_EINVAL, "store or n_rounds is NULL"};
     if (cap < 0 || (cap > 0 && !out)) throw StatusFail{GSMAT_EINVAL, "bad output array"};
-    const int32_t n = (int32_t)(st->dbatch_stats.size() / kStatFields);
+    const int32_t n = st->dbatch_rounds ? (int32_t)(st->dbatch_stats.size() / kStatFields) : 0;
     *n_rounds = n;
     for (int32_t i = 0; i < std::min(n, cap); ++i)
       for (int f = 0; f < kStatFields; ++f)

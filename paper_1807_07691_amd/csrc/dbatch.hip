@@ -1680,6 +1680,7 @@ void run_batch_packed(gsmat_store* st, PackedBatch& pb, int64_t budget, int64_t 
   // the pass's sizes are the next pass's starting regions
   st->dbatch_out_hint = std::max<int64_t>(round_up(out_total + out_total / 8, g), g);
   st->dbatch_scr_hint = std::max<int64_t>(round_up(hc->scr_need + hc->scr_need / 8, g), g);
+  st->dbatch_rounds = true;
   st->dbatch_stats.assign(&hc->stats[0][0],
                           &hc->stats[0][0] + (size_t)std::min(hc->round, kStatRounds) * kStatFields);
   prof_add_bytes(GSMAT_K_COUNT, (double)hc->bytes_count);

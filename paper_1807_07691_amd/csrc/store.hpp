@@ -58,7 +58,8 @@ struct gsmat_store {
   int32_t intersect = 0;          // ... sorted-list intersections: 0 search, 1 window, 2 merge
   int64_t dbatch_out_hint = 0;    // device-driven rounds: output slab and scratch sizes of
   int64_t dbatch_scr_hint = 0;    // the last batch (the next one starts with them)
-  std::vector<int64_t> dbatch_stats;  // the last device-driven batch's rounds
+  std::vector<int64_t> dbatch_stats;  // rounds of the last batch that took any
+  bool dbatch_rounds = false;     // ... and whether the last batch did
   int64_t hub_min_len = 1 << 14;  // rows this long get a bitmap ...
   int64_t hub_max_bytes = 0;      // ... within this many bytes per orientation (0: none)
   uint64_t uid = 0;        // distinct for every index build in the process

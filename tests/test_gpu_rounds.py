@@ -168,3 +168,15 @@ def test_autotuner_times_the_rounds(G):
     pl.close()
     plans.close()
     st.close()
+
+
+def test_round_stats_are_the_last_batchs(G, tiny):
+    """A batch that took no rounds reports none, not an earlier batch's."""
+    spec, s, p, o, qs, st, want = tiny
+    assert _rounds(G, st, [q.tps for q in qs], G.PLAN_ADAPTIVE) > 0
+    G.gsmat_set_small_joins(st, 1)
+    try:
+        assert _rounds(G, st, [[[int(s[0]), int(p[0]), -1]]] * 8, G.PLAN_ADAPTIVE) == 0
+    finally:
+        G.gsmat_set_small_joins(st, 0)
+    assert _rounds(G, st, [q.tps for q in qs], G.PLAN_ADAPTIVE) > 0
