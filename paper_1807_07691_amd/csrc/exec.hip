@@ -124,6 +124,7 @@ struct Exec {
   std::vector<Table>* collect = nullptr;
 
   bool small = true;     // tables of few rows run in one launch (small.hip)
+  size_t* small_bytes = nullptr;  // set: what those launches' areas took in all
   bool settled = true;   // everything launched so far has been waited for
 
   DeviceMem* mem() { return dm ? dm : st->mem.get(); }
@@ -359,7 +360,7 @@ struct Exec {
       emit(t);
       return;
     }
-    if (small && small_fits(si, t) && run_small(si, t, rem)) return;
+    if (small && small_fits(si, t, rem) && run_small(si, t, rem)) return;
     const gsmat_step_info sp =
         (adaptive && !t.unit()) ? choose(t, rem) : pl->steps[std::min<size_t>(si, pl->steps.size() - 1)];
     const uint32_t next = rem & ~completes(sp);
@@ -390,19 +391,33 @@ struct Exec {
   }
 
   // Whether the steps from si on are tried in one launch: the table has at
-  // most kSmallRows rows, and a first step does not list more (a scan of known
-  // length is a view and needs no launch).  A table of so few rows costs the
+  // most kSmallRows rows, and the next step is one the launch takes.  A first
+  // step must not list more rows, and one that the host answers from the plan's
+  // lookups needs no launch: a scan of known length is a view, a constant
+  // pattern known to hold or not to hold decides by itself (5 us against 15).
+  // From a bound table some pattern left must be connected to it: a Cartesian
+  // product only hands the table back (two constants' rows: 19 us against 34).
+  // A table of so few rows costs the
   // general path 25 us to 60 us a step whatever its size; the launch takes 14 us
   // for one or two steps and 23 us for four.  Sixteen queries, planned, joined
   // and fetched, on 20 million triples, with the fetch in reported packs: 4.6 -> 1.4
   // ms (3 to 5 patterns, 300 to 30 000 rows), 1.65 -> 0.6 ms (1 or 2 patterns, up to
   // 100 rows).
-  bool small_fits(int si, const Table& t) const {
+  bool small_fits(int si, const Table& t, uint32_t rem) const {
     if (t.n > kSmallRows) return false;
-    if (!t.unit()) return true;
-    const bool known = pl->lk_store == st->uid && pl->lk.size() == pl->pats.size();
     const gsmat_step_info& sp = pl->steps[std::min<size_t>(si, pl->steps.size() - 1)];
-    if (sp.kind == GSMAT_STEP_FILTER) return true;
+    if (!t.unit()) {
+      if (!adaptive) return sp.kind == GSMAT_STEP_EXPAND || sp.kind == GSMAT_STEP_FILTER;
+      for (int tp = 0; tp < (int)pl->pats.size(); ++tp) {
+        const gsmat_pattern& q = pl->pats[tp];
+        if (!(rem >> tp & 1)) continue;
+        if (is_var(q.s) ? t.col_of(var_of(q.s)) >= 0 : !is_var(q.o)) return true;
+        if (is_var(q.o) && t.col_of(var_of(q.o)) >= 0) return true;
+      }
+      return false;
+    }
+    const bool known = pl->lk_store == st->uid && pl->lk.size() == pl->pats.size();
+    if (sp.kind == GSMAT_STEP_FILTER) return !(known && pl->lk[sp.tp].valid);
     if (sp.kind == GSMAT_STEP_SCAN || sp.kind == GSMAT_STEP_CARTESIAN) {
       const gsmat_pattern& q = pl->pats[sp.tp];
       return !known && (!is_var(q.s) || !is_var(q.o));
@@ -427,7 +442,7 @@ struct Exec {
   bool small_first() const {
     Table unit;
     unit.n = 1;
-    if (small_fits(0, unit)) return true;
+    if (small_fits(0, unit, all_of(pl))) return true;
     const gsmat_step_info& sp = pl->steps[0];
     if (sp.kind != GSMAT_STEP_SCAN) return false;
     const gsmat_pattern& q = pl->pats[sp.tp];
@@ -505,6 +520,7 @@ struct Exec {
       return false;
     }
     live.push_back({sm.fin, (size_t)kSmallFin});
+    if (small_bytes) *small_bytes += sm.work_bytes + kSmallFin;
     fill_small(h->query, si, t, rem, l, sm);
     const uint32_t seq = next_report();
     launch_small(small_store(st), &h->query, &h->small, 1, seq, s);
@@ -974,7 +990,7 @@ gsmat_step_info step_pick(const gsmat_query_plan* pl, const StepChoice& c, const
 
 bool run_query(gsmat_store* st, const gsmat_query_plan* pl, int64_t budget_bytes,
                int64_t max_rows, hipStream_t s, gsmat_result* res, DeviceMem* mem,
-               void* dev_area, bool small) {
+               void* dev_area, bool small, size_t* small_bytes) {
   // a pattern over an absent predicate or vertex matches nothing
   for (const gsmat_pattern& q : pl->pats) {
     if (q.p >= st->P) return true;
@@ -984,6 +1000,7 @@ bool run_query(gsmat_store* st, const gsmat_query_plan* pl, int64_t budget_bytes
   Exec ex{st, pl, s, budget_bytes, max_rows, res, pl->mode == GSMAT_PLAN_ADAPTIVE, {},
           mem, (PinnedArea*)dev_area};
   ex.small = small && st->small_joins;
+  ex.small_bytes = small_bytes;
   Table unit;
   unit.n = 1;
   unit.k = 0;
@@ -1317,6 +1334,7 @@ struct ScratchStack {
   char* base = nullptr;
   size_t top = kStageBytes;
   size_t want = 0;  // largest request that did not fit
+  size_t over = 0;  // bytes the last of them was over
   std::vector<size_t> off, len;
   std::vector<char> freed;
 
@@ -1324,6 +1342,7 @@ struct ScratchStack {
     const size_t b = (std::max<size_t>(bytes, 1) + 255) / 256 * 256;
     if (b > kNoAllocBytes - top) {
       want = std::max(want, b);
+      over = b - (kNoAllocBytes - top);
       return nullptr;
     }
     off.push_back(top);
@@ -1390,11 +1409,13 @@ extern "C" gsmat_status gsmat_join_noalloc(gsmat_store* st, const gsmat_query_pl
         for (Segment& g : r.segs) g.owned = nullptr;
       }
     } drop{res};
+    size_t small_bytes = 0;
     try {
       try {
-        run_query(st, pl, 0, -1, s, &res, &mem, nd->base);
+        run_query(st, pl, 0, -1, s, &res, &mem, nd->base, true, &small_bytes);
       } catch (const OomFail&) {
-        // the small launch's areas may be what did not fit: once without it
+        // the small launches' areas may be what did not fit: once without them
+        if (stack.over > small_bytes) throw;
         (void)hipStreamSynchronize(s);
         stack = ScratchStack();
         stack.base = nd->base;

@@ -91,10 +91,10 @@ gsmat_step_info step_pick(const gsmat_query_plan* pl, const StepChoice& c, const
 // kernels leave the small results the host reads.
 constexpr size_t kStageBytes = 4096;
 // True: every launch has been waited for.  small unset: no one-launch run of
-// small tables.
+// small tables; small_bytes (may be null) grows by what their areas take.
 bool run_query(gsmat_store* st, const gsmat_query_plan* pl, int64_t budget_bytes,
                int64_t max_rows, hipStream_t s, gsmat_result* res, DeviceMem* mem = nullptr,
-               void* dev_area = nullptr, bool small = true);
+               void* dev_area = nullptr, bool small = true, size_t* small_bytes = nullptr);
 
 // Runs plan pl (adaptive step choice) from table t0, or from the unit table
 // when t0 is null, and appends the final tables to out instead of adding them

@@ -138,3 +138,54 @@ def test_small_batches(G, n, fan, count):
             if res[i] is not None:
                 res[i].close()
     st.close()
+
+
+def launches(G, f):
+    """Kernel launches of the library during f()."""
+    G.gsmat_prof_enable()
+    try:
+        f()
+        return sum(k["launches"] for k in G.gsmat_prof_read().values())
+    finally:
+        G.gsmat_prof_enable(0)
+
+
+def test_no_launch_for_what_it_cannot_take(G):
+    """A constant pattern the plan knows about, a product of two constants'
+    rows, and a join whose answer is far above the allocation-free array cost
+    the launches they cost without the small joins."""
+    import torch
+    s, p, o, V, P = graph(3000, 9, 3)
+    n = 3_000_000  # predicate 6: pairs whose square is above the array
+    big = np.stack([np.arange(n) % 1500, np.full(n, 6), np.arange(n) // 1500], 1).astype(np.int32)
+    a = np.concatenate([np.stack([s, p, o], 1), big])
+    st = G.gsmat_load_triples(a[:, 0].copy(), a[:, 1].copy(), a[:, 2].copy(), V, 7)
+    G.gsmat_build_index(st)
+    out = torch.empty(64, dtype=torch.int32, device="cuda")
+
+    def join(q, mode):
+        pl = G.gsmat_plan(st, q, mode)
+        return lambda: G.gsmat_join(st, pl).close()
+
+    def fails():
+        pl = G.gsmat_plan(st, [[5, 6, -1], [-2, 6, -1], [-2, 6, -3]], G.PLAN_ADAPTIVE)
+        n_rows = []
+
+        def f():
+            with pytest.raises(G.GsmatError) as e:
+                n_rows.append(G.gsmat_join_noalloc(st, pl, out.data_ptr(), 16, 16))
+            assert e.value.status == G.GSMAT_ENOMEM
+        return f
+
+    calls = [join([[0, 0, 1]], m) for m in (1, 2)]
+    calls += [join([[0, 0, -1], [1, 3, -2]], m) for m in (0, 1, 2)]
+    calls += [join([[0, 0, -1], [1, 3, -2], [-3, 4, 5]], m) for m in (1, 2)]
+    calls.append(fails())
+    for i, f in enumerate(calls):
+        got = []
+        for on in (0, 1):
+            G.gsmat_set_small_joins(st, on)
+            got.append(launches(G, f))
+        print(f"[gpu] call {i}: launches without {got[0]}, with {got[1]}", flush=True)
+        assert got[1] <= got[0] + (i == 7), i
+    st.close()
