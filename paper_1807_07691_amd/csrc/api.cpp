@@ -153,14 +153,16 @@ class BlockCache {
     return p;
   }
 
-  void free(void* p, hipStream_t s) {
+  void free(void* p, hipStream_t s, bool idle) {
     std::lock_guard<std::mutex> g(mu_);
     auto it = live_.find(p);
     if (it == live_.end()) return;
     const size_t size = it->second;
     live_.erase(it);
     hipEvent_t ev = nullptr;
-    if (!events_.empty()) {
+    if (idle) {
+      // nothing to wait for
+    } else if (!events_.empty()) {
       ev = events_.back();
       events_.pop_back();
     } else if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
@@ -238,7 +240,13 @@ void DeviceMem::free(void* p, size_t bytes, hipStream_t s) {
     user_.free(p, bytes, (void*)s, user_.ctx);
     return;
   }
-  static_cast<BlockCache*>(cache_)->free(p, s);
+  static_cast<BlockCache*>(cache_)->free(p, s, false);
+}
+
+void DeviceMem::free_idle(void* p, size_t bytes, hipStream_t s) {
+  if (!p || has_user_) return free(p, bytes, s);
+  HostTimer timer(&g_free_ms, nullptr);
+  static_cast<BlockCache*>(cache_)->free(p, s, true);
 }
 
 // ---------------------------------------------------------------- profiling

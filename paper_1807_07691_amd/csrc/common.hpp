@@ -148,6 +148,9 @@ class DeviceMem {
   ~DeviceMem();
   void* alloc(size_t bytes, hipStream_t s);  // nullptr on failure
   void free(void* p, size_t bytes, hipStream_t s);
+  // The same for a block whose work the host has waited for (or that had none):
+  // another stream may have it at once.
+  void free_idle(void* p, size_t bytes, hipStream_t s);
   int device() const { return dev_; }
 
  private:

@@ -455,7 +455,7 @@ struct Exec {
   struct SmallMem {
     void* work = nullptr;
     size_t work_bytes = 0;
-    void* fin = nullptr;
+    void* fin[kSmallFins] = {};
     std::shared_ptr<Arena> work_hold, fin_hold;
   };
 
@@ -478,7 +478,7 @@ struct Exec {
     a.starts = l.starts;
     a.lens = l.lens;
     a.offs = l.offs;
-    a.fin = (char*)sm.fin;
+    for (int f = 0; f < kSmallFins; ++f) a.fin[f] = (char*)sm.fin[f];
     a.lk_valid = 0;
     const bool known = pl->lk_store == st->uid && pl->lk.size() == pl->pats.size();
     for (int i = 0; i < a.np; ++i) {
@@ -514,13 +514,19 @@ struct Exec {
     sm.work = mem()->alloc(sm.work_bytes, s);
     if (!sm.work) return false;  // the general path may need less
     live.push_back({sm.work, sm.work_bytes});
-    sm.fin = mem()->alloc(kSmallFin, s);
-    if (!sm.fin) {
-      drop(sm.work, sm.work_bytes);
-      return false;
+    size_t fins = 0;
+    for (int f = 0; f < kSmallFins; ++f) {
+      if (dm && kFinBytes[f] < kSmallFin) continue;  // nothing is kept there
+      sm.fin[f] = mem()->alloc(kFinBytes[f], s);
+      if (!sm.fin[f]) {
+        drop_fins(sm);
+        drop(sm.work, sm.work_bytes);
+        return false;
+      }
+      live.push_back({sm.fin[f], (size_t)kFinBytes[f]});
+      fins += kFinBytes[f];
     }
-    live.push_back({sm.fin, (size_t)kSmallFin});
-    if (small_bytes) *small_bytes += sm.work_bytes + kSmallFin;
+    if (small_bytes) *small_bytes += sm.work_bytes + fins;
     fill_small(h->query, si, t, rem, l, sm);
     const uint32_t seq = next_report();
     launch_small(small_store(st), &h->query, &h->small, 1, seq, s);
@@ -530,9 +536,15 @@ struct Exec {
     return finish_small(r, (int64_t*)((char*)sm.work + l.offs), sm, si, t, rem);
   }
 
-  void drop(void* p, size_t bytes) {
+  // idle: all work on the block has been waited for
+  void drop(void* p, size_t bytes, bool idle = false) {
     forget(p);
-    mem()->free(p, bytes, s);
+    if (idle) mem()->free_idle(p, bytes, s);
+    else mem()->free(p, bytes, s);
+  }
+  void drop_fins(const SmallMem& sm, int but = -1) {
+    for (int f = 0; f < kSmallFins; ++f)
+      if (f != but && sm.fin[f]) drop(sm.fin[f], kFinBytes[f], true);
   }
 
   // The write of an expansion that a small join counted: its task and its
@@ -581,7 +593,8 @@ struct Exec {
     }
     si = r.si;
     rem = r.rem;
-    bool keep_work = false, keep_fin = false;
+    bool keep_work = false;
+    const int fin = r.n > 0 && r.place >= kAtFin ? r.place - kAtFin : -1;
     if (o.n == 0) {
     } else if (r.place == kAtWork && done) {
       // the answer leaves the work area for memory of its own size
@@ -602,12 +615,11 @@ struct Exec {
         o.owned = sm.work;
         o.owned_bytes = sm.work_bytes;
       }
-    } else if (r.place == kAtFin) {
-      keep_fin = true;
+    } else if (fin >= 0) {
       o.keep = sm.fin_hold;
       if (own) {
-        o.owned = sm.fin;
-        o.owned_bytes = kSmallFin;
+        o.owned = sm.fin[fin];
+        o.owned_bytes = kFinBytes[fin];
       }
     } else {  // t's own columns, or views into the store
       o.owned = t.owned;
@@ -615,9 +627,10 @@ struct Exec {
       o.keep = t.keep;
       t.owned = nullptr;
     }
-    if (own && !keep_fin) drop(sm.fin, kSmallFin);
+    if (own) drop_fins(sm, fin);
     const bool counted = r.status == kSmallWrite;
-    if (own && !keep_work && !counted) drop(sm.work, sm.work_bytes);
+    if (own && !keep_work && !counted)
+      drop(sm.work, sm.work_bytes, !done || r.place != kAtWork || r.n == 0);
     release(t);
     t = o;
     if (counted) {
@@ -1078,7 +1091,7 @@ void run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int3
     One& o = v[i];
     o.sm.work = (char*)work->p + (size_t)l.bytes * i;
     o.sm.work_bytes = (size_t)l.bytes;
-    o.sm.fin = (char*)fin->p + (size_t)kSmallFin * i;
+    o.sm.fin[kSmallFins - 1] = (char*)fin->p + (size_t)kSmallFin * i;
     o.sm.work_hold = work;
     o.sm.fin_hold = fin;
     o.ex->fill_small(args[i], 0, o.t, all_of(plans[o.q]), l, o.sm);

@@ -72,14 +72,17 @@ struct SmallLds {
 
 __device__ inline int64_t s_stride(int64_t n) { return (n + 63) / 64 * 64; }
 
-// Where the next table (of at most kSmallRows rows) goes: the final area when
-// it is the answer and fits, else the half of the work area the current table
-// is not in.
+// Where the next table (of at most kSmallRows rows) goes: the smallest final
+// block that holds it when it is the answer, else the half of the work area the
+// current table is not in.
 __device__ inline char* s_place(const SmallArgs& A, int64_t bytes, bool last, int half, int* place,
                                 int* next_half) {
   if (last && bytes <= kSmallFin) {
-    *place = kAtFin;
-    return A.fin;
+    for (int f = 0; f < kSmallFins; ++f)
+      if (bytes <= kFinBytes[f] && A.fin[f]) {
+        *place = kAtFin + f;
+        return A.fin[f];
+      }
   }
   *place = kAtWork;
   *next_half = half ^ 1;

@@ -8,6 +8,10 @@ namespace gsmat {
 
 constexpr int64_t kSmallRows = 4096;        // rows of a table inside the launch
 constexpr int64_t kSmallFin = 64 << 10;     // bytes of a final table of its own
+// Blocks the answer may be left in: it takes the smallest that holds it, so a
+// kept answer holds at most four times its bytes (or 1 KiB).
+constexpr int kSmallFins = 4;
+constexpr int64_t kFinBytes[kSmallFins] = {1 << 10, 4 << 10, 16 << 10, kSmallFin};
 
 // Offsets in a query's work area: two tables of up to `cols` columns (the
 // first at 0, the second at tab), the row starts and lengths of every
@@ -26,8 +30,8 @@ struct SmallLayout {
 
 enum : int32_t { kSmallDone = 1, kSmallMore = 2, kSmallWrite = 3 };
 // where a reported table's columns are: where they were at the start (or in
-// the store), in the final area, in the work area
-enum : int32_t { kAtStart = 0, kAtFin = 1, kAtWork = 2 };
+// the store), in the work area, in final block i
+enum : int32_t { kAtStart = 0, kAtWork = 1, kAtFin = 2 /* + i */ };
 
 struct SmallPat {
   int32_t s, p, o;
@@ -47,7 +51,7 @@ struct SmallArgs {
   int64_t budget;
   char* work;       // laid out by these (SmallLayout)
   int64_t tab, starts, lens, offs;
-  char* fin;        // kSmallFin bytes
+  char* fin[kSmallFins];  // kFinBytes[i] bytes (null: none)
   SmallPat pats[kMaxPats];
   SmallStep steps[kMaxPats + 1];
   LookupRes lk[kMaxPats];       // of the patterns with a constant ...

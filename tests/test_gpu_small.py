@@ -189,3 +189,53 @@ def test_no_launch_for_what_it_cannot_take(G):
         print(f"[gpu] call {i}: launches without {got[0]}, with {got[1]}", flush=True)
         assert got[1] <= got[0] + (i == 7), i
     st.close()
+
+
+class Counting:
+    """A store's allocator: torch memory, with the bytes held."""
+
+    def __init__(self, G):
+        import torch
+        self.held, self.bytes, self.peak = {}, 0, 0
+
+        def alloc(size, stream):
+            t = torch.empty(size, dtype=torch.uint8, device="cuda")
+            self.held[t.data_ptr()] = t
+            self.bytes += size
+            self.peak = max(self.peak, self.bytes)
+            return t.data_ptr()
+
+        def free(p, size, stream):
+            assert self.held.pop(p).numel() == size
+            self.bytes -= size
+
+        self.allocator = G.make_allocator(alloc, free)
+
+
+def test_kept_answers_hold_little(G):
+    """An answer of a small join holds at most four times its columns (which
+    start on 256-byte boundaries), or 1 KiB."""
+    s, p, o, V, P = graph(3000, 2, 5)
+    # predicate 6: vertex i has the objects 1 to 2 ** i
+    more = np.concatenate([np.stack([np.full(1 << i, i), np.full(1 << i, 6), 1 + np.arange(1 << i)], 1)
+                           for i in range(13)]).astype(np.int32)
+    a = np.concatenate([np.stack([s, p, o], 1), more])
+    mem = Counting(G)
+    st = G.gsmat_load_triples(*(a[:, i].copy() for i in range(3)), V, 7, allocator=mem.allocator)
+    G.gsmat_build_index(st)
+    for mode in (G.PLAN_DEFAULT, G.PLAN_ADAPTIVE):
+        for i in range(13):
+            pl = G.gsmat_plan(st, [[i, 6, -1], [-1, 3, -2], [-2, 3, -3]], mode)
+            before = mem.bytes
+            r = G.gsmat_join(st, pl)
+            info = G.gsmat_result_info(r)
+            n = info["rows"]
+            assert n > 0
+            held, own = mem.bytes - before, 4 * 3 * ((n + 63) // 64 * 64)
+            print(f"[gpu] kept answer rows={n} holds {held}", flush=True)
+            assert held <= max(1024, 4 * own), (n, held)
+            r.close()
+            assert mem.bytes == before
+            pl.close()
+    st.close()
+    assert mem.bytes == 0
