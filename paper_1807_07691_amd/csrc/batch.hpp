@@ -127,6 +127,9 @@ void run_batch_device_bgp(gsmat_store* st, const gsmat_pattern* pats, const int3
 // above that a batch fills the rounds' launches, whose fixed cost (about 90 us
 // a round) it shares.  60 queries of up to 30 000 rows: 625 -> 235 us.
 constexpr int32_t kSmallBatch = 512;
+// The queries' work areas (0.1 to 2.1 MB each, by patterns) stay within this;
+// the queries beyond it are left.
+constexpr int64_t kSmallBatchWork = (int64_t)256 << 20;
 // round_budget > 0 bounds the bytes written for them in total (a query above
 // it is left).
 void run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int32_t nq,

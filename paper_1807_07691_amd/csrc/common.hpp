@@ -313,8 +313,6 @@ void launch_write_expand(ColSet in, int k, const int64_t* P, const int32_t* star
                          int64_t ntiles, OutSet out, double alg_bytes, hipStream_t s);
 void launch_cartesian(ColSet a, int ka, int64_t na, ColSet b, int kb, int64_t nb, int64_t J0,
                       int64_t J1, OutSet out, hipStream_t s);
-// out's columns = in's, n rows of k columns
-void launch_copy_cols(ColSet in, int k, int64_t n, OutSet out, hipStream_t s);
 // writes kSampleBlocks partial sums per candidate to part[cand * kSampleBlocks + b]
 // (words: a report per partial sum)
 void launch_sample_fanout(const SampleSet& ss, int64_t* part, hipStream_t s,

@@ -547,27 +547,48 @@ struct Exec {
       if (f != but && sm.fin[f]) drop(sm.fin[f], kFinBytes[f], true);
   }
 
-  // The write of an expansion that a small join counted: its task and its
-  // output table.
-  void prepare_write(const SmallReport& r, const int64_t* offs, SmallWriteTask& w, Table& o) {
-    const gsmat_pattern& q = pl->pats[r.tp];
-    int vars[kMaxCols];
-    for (int c = 0; c < r.k; ++c) vars[c] = r.var[c];
-    vars[r.k] = r.orient == 0 ? var_of(q.o) : var_of(q.s);
-    o = alloc_table(r.m, vars, r.k + 1);
-    o.from = r.n;
-    w.offs = offs;
-    w.start = r.start;
-    w.nbr = r.orient == 0 ? st->out.view(q.p).nbr : st->in.view(q.p).nbr;
-    w.out = (int32_t*)o.owned;
-    w.m = r.m;
-    w.stride = col_stride(r.m);
+  // What a small join leaves to be written, the expansion it counted or an
+  // answer to be moved out of its work area: rows and columns.
+  static bool counted(const SmallReport& r) { return r.status == kSmallWrite; }
+  static int64_t out_rows(const SmallReport& r) { return counted(r) ? r.m : r.n; }
+  static int out_cols(const SmallReport& r) { return counted(r) ? r.k + 1 : r.k; }
+  static int64_t out_bytes(const SmallReport& r) {
+    return 4 * col_stride(out_rows(r)) * out_cols(r);
+  }
+  // Its task, and its table o, whose columns are at `to`.
+  void prepare_write(const SmallReport& r, const int64_t* offs, int32_t* to, SmallWriteTask& w,
+                     Table& o) {
+    o.n = out_rows(r);
+    o.k = out_cols(r);
+    for (int c = 0; c < r.k; ++c) o.var[c] = r.var[c];
+    w.offs = nullptr;
+    if (counted(r)) {
+      const gsmat_pattern& q = pl->pats[r.tp];
+      o.from = r.n;
+      o.var[r.k] = r.orient == 0 ? var_of(q.o) : var_of(q.s);
+      w.offs = offs;
+      w.start = r.start;
+      w.nbr = r.orient == 0 ? st->out.view(q.p).nbr : st->in.view(q.p).nbr;
+    }
+    w.out = to;
+    w.m = o.n;
+    w.stride = col_stride(o.n);
     w.n = (int32_t)r.n;
     w.k = r.k;
     for (int c = 0; c < r.k; ++c) w.col[c] = r.col[c];
+    for (int c = 0; c < o.k; ++c) o.col[c] = to + c * w.stride;
   }
   static double write_bytes(const SmallReport& r) {
+    if (!counted(r)) return 8.0 * (double)r.n * r.k;
     return 4.0 * (double)r.m * (r.k + 2) + (double)r.n * (4.0 * r.k + 12.0);
+  }
+  // The same written at once, into memory of its own.
+  Table write_own(const SmallReport& r, const int64_t* offs) {
+    Table o = alloc_table(out_rows(r), r.var, out_cols(r));
+    SmallWriteTask w;
+    prepare_write(r, offs, (int32_t*)o.owned, w, o);
+    launch_small_write(&w, 1, o.n, write_bytes(r), s);
+    return o;
   }
   // Whether the write is one piece within the step budget.
   bool one_piece(const SmallReport& r) const {
@@ -575,7 +596,7 @@ struct Exec {
   }
 
   // Takes over what a small join reports (as run_small); written: the table
-  // of its counted expansion, where that has been written.
+  // of its counted expansion or of its answer, where that has been written.
   bool finish_small(const SmallReport& r, const int64_t* offs, const SmallMem& sm, int& si,
                     Table& t, uint32_t& rem, Table* written = nullptr) {
     for (int i = 0; i < res->n_steps && i <= kMaxPats; ++i) {
@@ -598,16 +619,8 @@ struct Exec {
     if (o.n == 0) {
     } else if (r.place == kAtWork && done) {
       // the answer leaves the work area for memory of its own size
-      Table x = alloc_table(o.n, o.var, o.k);
-      ColSet in{};
-      OutSet out{};
-      for (int c = 0; c < o.k; ++c) {
-        in.c[c] = o.col[c];
-        out.c[c] = const_cast<int32_t*>(x.col[c]);
-      }
-      launch_copy_cols(in, o.k, o.n, out, s);
+      o = written ? *written : write_own(r, offs);
       settled = false;
-      o = x;
     } else if (r.place == kAtWork) {
       keep_work = true;
       o.keep = sm.work_hold;
@@ -628,26 +641,18 @@ struct Exec {
       t.owned = nullptr;
     }
     if (own) drop_fins(sm, fin);
-    const bool counted = r.status == kSmallWrite;
-    if (own && !keep_work && !counted)
+    if (own && !keep_work && !counted(r))
       drop(sm.work, sm.work_bytes, !done || r.place != kAtWork || r.n == 0);
     release(t);
     t = o;
-    if (counted) {
+    if (counted(r)) {
       // the step is counted: its outputs are written as any expansion's
       settled = false;
       if (si < res->n_steps) res->step_in[si] += t.n;
       add_out(si, r.m);
       const uint32_t next = rem & ~(1u << r.tp);
       if (written || one_piece(r)) {
-        Table x;
-        if (written) {
-          x = *written;
-        } else {
-          SmallWriteTask w;
-          prepare_write(r, offs, w, x);
-          launch_small_write(&w, 1, r.m, write_bytes(r), s);
-        }
+        Table x = written ? *written : write_own(r, offs);
         run(si + 1, x, next);
         release(t);
       } else {
@@ -1034,21 +1039,23 @@ void run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int3
   for (DevQueryOut& o : out) o.state = kDevFallback;
   struct One {
     int q;  // the query
+    SmallLayout l;
     std::unique_ptr<gsmat_result> res;
     std::unique_ptr<Exec> ex;
     Table t;
     Exec::SmallMem sm;
-    Table w;            // its counted expansion's table ...
-    bool made = false;  // ... when that is written by the batch's launch
+    int64_t at = -1;    // its table's place in the batch's outputs (-1: none)
+    Table w;            // that table
     bool skip = false;  // left to the rounds
   };
   std::vector<One> v;
   v.reserve(nq);
-  int mp = 1;
+  constexpr int kFin = 1;  // every query's own final block: of 4 KiB
+  int64_t work_bytes = 0;
   for (int i = 0; i < nq; ++i) {
     const gsmat_query_plan* pl = plans[i];
-    One o;
-    o.q = i;
+    // a pattern after the first adds one variable at most
+    One o{i, SmallLayout((int)pl->pats.size(), (int)pl->pats.size() + 1)};
     o.res.reset(new gsmat_result);
     o.res->st = st;
     o.res->stream = s;
@@ -1065,21 +1072,17 @@ void run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int3
     o.t.n = 1;
     o.t.k = 0;
     if (!o.ex->small_first()) continue;
-    mp = std::max(mp, (int)pl->pats.size());
+    if (work_bytes + o.l.bytes > kSmallBatchWork) continue;
+    work_bytes += o.l.bytes;
     v.push_back(std::move(o));
   }
   if (v.empty()) return;
   const int n = (int)v.size();
-  // a pattern after the first adds one variable at most; sizes in steps, so that
-  // batches of about one size share the allocator's blocks
-  mp = (mp + 7) / 8 * 8;
-  const SmallLayout l(mp, mp + 1);
   DeviceMem* mem = st->mem.get();
-  std::shared_ptr<Arena> work, fin;
+  std::shared_ptr<Arena> work, fin, outs;
   try {
-    const size_t slots = (size_t)(n + 63) / 64 * 64;
-    work = std::make_shared<Arena>(mem, (size_t)l.bytes * slots, s);
-    fin = std::make_shared<Arena>(mem, (size_t)kSmallFin * slots, s);
+    work = std::make_shared<Arena>(mem, (size_t)work_bytes, s);
+    fin = std::make_shared<Arena>(mem, (size_t)kFinBytes[kFin] * n, s);
   } catch (const OomFail&) {
     return;  // the rounds may need less
   }
@@ -1087,14 +1090,16 @@ void run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int3
       (SmallReport*)query_area().get((sizeof(SmallArgs) + sizeof(SmallReport) +
                                       sizeof(SmallWriteTask)) * (size_t)n);
   SmallArgs* args = (SmallArgs*)(reps + n);
+  char* at = (char*)work->p;
   for (int i = 0; i < n; ++i) {
     One& o = v[i];
-    o.sm.work = (char*)work->p + (size_t)l.bytes * i;
-    o.sm.work_bytes = (size_t)l.bytes;
-    o.sm.fin[kSmallFins - 1] = (char*)fin->p + (size_t)kSmallFin * i;
+    o.sm.work = at;
+    o.sm.work_bytes = (size_t)o.l.bytes;
+    at += o.l.bytes;
+    o.sm.fin[kFin] = (char*)fin->p + kFinBytes[kFin] * i;
     o.sm.work_hold = work;
     o.sm.fin_hold = fin;
-    o.ex->fill_small(args[i], 0, o.t, all_of(plans[o.q]), l, o.sm);
+    o.ex->fill_small(args[i], 0, o.t, all_of(plans[o.q]), o.l, o.sm);
     reps[i].seq = 0;
   }
   const uint32_t seq = next_report();
@@ -1109,38 +1114,44 @@ void run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int3
     return r.status == kSmallMore || (r.status == kSmallWrite && (r.rem & ~(1u << r.tp)) != 0);
   };
   for (int i = 0; i < n; ++i) unfinished += left(reps[i]);
-  // every write in one launch
-  int64_t written = 0, most = 0;
+  // everything to be written goes out in one launch, into one block, as the
+  // outputs of a round do
+  int64_t written = 0, total = 0, most = 0;
   double alg = 0;
   int nw = 0;
   SmallWriteTask* tasks = (SmallWriteTask*)(args + n);
-  try {
-    for (int i = 0; i < n; ++i) {
-      One& o = v[i];
-      const SmallReport& r = reps[i];
-      const int64_t bytes = r.status == kSmallWrite ? 4 * col_stride(r.m) * (r.k + 1)
-                                                    : 4 * col_stride(r.n) * r.k;
-      o.skip = (left(r) && (unfinished > 4 || round_budget > 0)) ||
-               (round_budget > 0 && written + bytes > round_budget);
-      if (o.skip) continue;
-      written += bytes;
-      if (r.status != kSmallWrite || !o.ex->one_piece(r)) continue;
-      try {
-        o.ex->prepare_write(r, (const int64_t*)((char*)o.sm.work + l.offs), tasks[nw], o.w);
-      } catch (const OomFail&) {
-        o.skip = true;
-        continue;
-      }
-      o.made = true;
-      most = std::max(most, r.m);
-      alg += Exec::write_bytes(r);
-      ++nw;
-    }
-    launch_small_write(tasks, nw, most, alg, s);
-  } catch (...) {
-    for (One& o : v) o.ex->release_all();
-    throw;
+  for (int i = 0; i < n; ++i) {
+    One& o = v[i];
+    const SmallReport& r = reps[i];
+    const int64_t bytes = Exec::out_bytes(r);
+    o.skip = (left(r) && (unfinished > 4 || round_budget > 0)) ||
+             (round_budget > 0 && written + bytes > round_budget);
+    if (o.skip) continue;
+    written += bytes;
+    const bool move = r.status == kSmallDone && r.n > 0 && r.place == kAtWork;
+    if (!move && !(r.status == kSmallWrite && o.ex->one_piece(r))) continue;
+    o.at = total;
+    total += bytes;
   }
+  try {
+    if (total > 0) outs = std::make_shared<Arena>(mem, (size_t)total, s);
+  } catch (const OomFail&) {  // the rounds may need less
+  }
+  for (int i = 0; i < n; ++i) {
+    One& o = v[i];
+    const SmallReport& r = reps[i];
+    if (o.at < 0) continue;
+    if (!outs) {
+      o.skip = true;
+      continue;
+    }
+    o.ex->prepare_write(r, (const int64_t*)((char*)o.sm.work + o.l.offs),
+                        (int32_t*)((char*)outs->p + o.at), tasks[nw++], o.w);
+    o.w.keep = outs;
+    most = std::max(most, o.w.n);
+    alg += Exec::write_bytes(r);
+  }
+  launch_small_write(tasks, nw, most, alg, s);
   bool settled = nw == 0;
   for (int i = 0; i < n; ++i) {
     One& o = v[i];
@@ -1150,8 +1161,8 @@ void run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int3
     uint32_t rem = 0;
     const gsmat_status rc = guarded([&]() -> gsmat_status {
       try {
-        if (!o.ex->finish_small(r, (const int64_t*)((char*)o.sm.work + l.offs), o.sm, si, o.t, rem,
-                                o.made ? &o.w : nullptr))
+        if (!o.ex->finish_small(r, (const int64_t*)((char*)o.sm.work + o.l.offs), o.sm, si, o.t,
+                                rem, o.at >= 0 ? &o.w : nullptr))
           o.ex->run(si, o.t, rem);
       } catch (...) {
         o.ex->release_all();

@@ -666,14 +666,6 @@ __global__ void k_cartesian(ColSet a, int ka, ColSet b, int kb, int64_t nb, int6
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_copy_cols(ColSet in, int64_t n, OutSet out) {
-  const int32_t* __restrict__ src = in.c[blockIdx.y];
-  int32_t* __restrict__ dst = out.c[blockIdx.y];
-  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * kBlock)
-    dst[i] = src[i];
-}
-
 // Sum of row lengths over a strided sample of the bound column; blockIdx.y
 // selects the candidate, blockIdx.x one of kSampleBlocks slices of the sample.
 __global__ __launch_bounds__(kBlock) void k_sample_fanout(SampleSet ss, int64_t* __restrict__ part,
@@ -1045,13 +1037,6 @@ void launch_cartesian(ColSet a, int ka, int64_t na, ColSet b, int kb, int64_t nb
   GS_LAUNCH(GSMAT_K_OTHER, 4.0 * (ka + kb) * 2.0 * (J1 - J0),
             hipLaunchKernelGGL(k_cartesian, dim3(grid_for(J1 - J0)), dim3(kBlock), 0, s, a, ka, b,
                                kb, nb, J0, J1, out));
-}
-
-void launch_copy_cols(ColSet in, int k, int64_t n, OutSet out, hipStream_t s) {
-  if (n <= 0 || k <= 0) return;
-  GS_LAUNCH(GSMAT_K_OTHER, 8.0 * k * n,
-            hipLaunchKernelGGL(k_copy_cols, dim3(grid_for(n, kBlock, 1024), (unsigned)k),
-                               dim3(kBlock), 0, s, in, n, out));
 }
 
 void launch_sample_fanout(const SampleSet& ss, int64_t* part, hipStream_t s, uint32_t* words,

@@ -634,6 +634,11 @@ __global__ __launch_bounds__(kBlock) void k_small_write(SmallWriteTask one,
   const int64_t m = L.t.m, stride = L.t.stride;
   const int64_t* const offs = L.t.offs;
   const int32_t* const nbr = L.t.nbr;
+  if (!offs) {  // an answer moved out of its work area
+    for (int64_t j = (int64_t)blockIdx.x * kBlock + tid; j < m; j += (int64_t)gridDim.x * kBlock)
+      for (int c = 0; c < k; ++c) L.t.out[c * stride + j] = L.t.col[c][j];
+    return;
+  }
   for (int64_t j0 = (int64_t)blockIdx.x * kTile; j0 < m; j0 += (int64_t)gridDim.x * kTile) {
     const int nj = (int)min((int64_t)kTile, m - j0);
     if (wave < 2) {  // the rows of the tile's first and last output

@@ -95,7 +95,7 @@ void launch_small(const SmallStore& st, const SmallArgs* args, SmallReport* reps
 
 // An expansion counted by a small join: output j < m belongs to the last of
 // the n <= kSmallRows rows whose offset is at most j.  Column c of the output
-// is at out + c * stride.
+// is at out + c * stride.  offs null: the m = n rows as they are, k columns.
 struct SmallWriteTask {
   const int64_t* offs;
   const int32_t* start;

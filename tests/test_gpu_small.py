@@ -239,3 +239,37 @@ def test_kept_answers_hold_little(G):
             pl.close()
     st.close()
     assert mem.bytes == 0
+
+
+def test_batch_areas_stay_small(G):
+    """What a batch's small launch takes follows each query's own patterns and
+    stays within 256 MiB, and one kept answer holds the batch's answers and 4
+    KiB a query, not every query's largest possible answer."""
+    s, p, o, V, P = graph(700, 7, 5)
+    mem = Counting(G)
+    st = G.gsmat_load_triples(s, p, o, V, P, allocator=mem.allocator)
+    G.gsmat_build_index(st)
+    chain = [[1, 3, -1]] + [[-i, 3, -i - 1] for i in range(1, 25)]
+    tiny = [[[i + 1, 1, -1], [-1, 3, -2]] for i in range(300)]
+    for queries, most in [(tiny[:60], 24 << 20), (tiny + [chain], 128 << 20),
+                          ([chain] * 300, 256 << 20)]:
+        want = [G.evaluate(st, q) for q in queries]
+        plans, _ = G.gsmat_plan_batch(st, queries, G.PLAN_ADAPTIVE)
+        before = mem.peak = mem.bytes
+        G.gsmat_set_batch_regions(st, 1 << 20, 1 << 20)
+        res, _ = G.gsmat_join_batch(st, plans)
+        print(f"[gpu] batch of {len(queries)}: peak {mem.peak - before}", flush=True)
+        assert mem.peak - before <= most + (8 << 20)
+        for r, w in zip(res, want):
+            assert np.array_equal(G.gsmat_fetch_bindings(r), w)
+        answers = sum(4 * w.shape[1] * ((len(w) + 63) // 64 * 64) for w in want)
+        for r in res[1:]:
+            r.close()
+        if len(queries) == 60:
+            assert mem.bytes - before <= answers + 4096 * len(queries)
+        res[0].close()
+        assert mem.bytes == before
+        for pl in plans:
+            pl.close()
+    st.close()
+    assert mem.bytes == 0
