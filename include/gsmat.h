@@ -263,8 +263,10 @@ gsmat_status gsmat_join_batch(gsmat_store* st, const gsmat_query_plan* const* pl
  *     task that does not fit the regions waits a round; at the wait the host
  *     adds larger regions and runs the remaining rounds.  The batch's
  *     intermediate tables stay in device memory until its results are freed.
- *     A batch of at most 512 queries first runs in one launch, a workgroup per
- *     query, and only the queries whose tables outgrow it take the rounds.
+ *     A batch of at most 512 queries, of which few have first relations of
+ *     more than 4096 rows and at most 64 three patterns or more, first runs in
+ *     one launch, a workgroup per query; the queries whose tables outgrow it
+ *     take the rounds, or go on alone where few of their steps are left.
  *   0 host-driven: the host builds every round's tasks and allocations from
  *     sizes read back twice per round (the serving loop always runs so).
  * EINVAL for another value. */

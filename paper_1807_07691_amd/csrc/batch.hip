@@ -1012,8 +1012,9 @@ struct gsmat_server {
     }
     if (plans.size() < 4) return;  // a round or two of so few is as fast
     std::vector<DevQueryOut> out;
-    run_small_batch(st, plans.data(), (int32_t)plans.size(), bt.budget, mem_budget, bt.max_rows, s,
-                    out);
+    const SmallBatchEnd e = run_small_batch(st, plans.data(), (int32_t)plans.size(), bt.budget,
+                                            mem_budget, bt.max_rows, true, s, out);
+    if (!e.settled) host_sync(s);
     for (size_t j = 0; j < at.size(); ++j) {
       BQ& b = bt.q[at[j]];
       b.tried = true;
@@ -1182,7 +1183,7 @@ void run_batch_any(gsmat_store* st, const gsmat_query_plan* const* plans, int32_
     run_batch_device(st, plans, n, budget_bytes, max_rows, s, out);
     return;
   }
-  run_small_batch(st, plans, n, budget_bytes, 0, max_rows, s, out);
+  const SmallBatchEnd e = run_small_batch(st, plans, n, budget_bytes, 0, max_rows, false, s, out);
   std::vector<const gsmat_query_plan*> rest;
   std::vector<int32_t> at;
   for (int32_t i = 0; i < n; ++i)
@@ -1190,10 +1191,17 @@ void run_batch_any(gsmat_store* st, const gsmat_query_plan* const* plans, int32_
       rest.push_back(plans[i]);
       at.push_back(i);
     }
-  if (rest.empty()) return;
-  std::vector<DevQueryOut> dq;
-  run_batch_device(st, rest.data(), (int32_t)rest.size(), budget_bytes, max_rows, s, dq);
-  for (size_t j = 0; j < at.size(); ++j) out[at[j]] = std::move(dq[j]);
+  if (!rest.empty() && !e.alone) {
+    std::vector<DevQueryOut> dq;
+    try {
+      run_batch_device(st, rest.data(), (int32_t)rest.size(), budget_bytes, max_rows, s, dq);
+    } catch (...) {
+      (void)hipStreamSynchronize(s);
+      throw;
+    }
+    for (size_t j = 0; j < at.size(); ++j) out[at[j]] = std::move(dq[j]);
+  }
+  if (!e.settled) host_sync(s);
 }
 
 // gsmat_join_batch with device-driven rounds: the queries that leave the

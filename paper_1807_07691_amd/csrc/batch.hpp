@@ -121,20 +121,38 @@ void run_batch_device_bgp(gsmat_store* st, const gsmat_pattern* pats, const int3
                           std::vector<gsmat_status>& status, std::vector<std::string>& msg,
                           std::vector<std::unique_ptr<gsmat_query_plan>>& fallback);
 
-// Batches of at most kSmallBatch queries first run in one launch, a workgroup
-// per query (small.hip): out[i] as above, kDevFallback for the queries left to
-// the rounds.  512 workgroups of 16 waves are what the device holds at once;
-// above that a batch fills the rounds' launches, whose fixed cost (about 90 us
-// a round) it shares.  60 queries of up to 30 000 rows: 625 -> 235 us.
+// A batch of at most kSmallBatch queries may first run in one launch, a
+// workgroup per query (small.hip): out[i] as above, kDevFallback for the queries
+// left.  Two things decide whether that pays.
+//   * The rounds cost about 80 us each whatever the batch holds, so the launch
+//     wins only if no round is needed after it.  A query whose first relation has
+//     more than 4096 rows does not start in it, and one whose tables outgrow it
+//     is left on the way; both may go on alone, at about 45 us a step, while
+//     their steps number at most two more than the longest query's (the rounds
+//     there would be).  With more of the first kind it is not tried.
+//   * A query of three patterns or more cannot be told to stay small: of those
+//     with up to 30 000 rows one in 25 outgrows it, of those with up to 10^6
+//     rows one in 7.  With more than kSmallUnsure of them it is not tried.
+// By the launch and by the rounds, us: 60 queries of 1 or 2 patterns and up to
+// 100 rows 47 and 167, 512 of them 215 and 239; 96 queries of 1 to 6 patterns and
+// up to 30 000 rows, where few enough are left, 203 and 498; where not, 60
+// queries 552 and 521, 512 queries 802 and 663.
 constexpr int32_t kSmallBatch = 512;
+constexpr int32_t kSmallUnsure = 64;
 // The queries' work areas (0.1 to 2.1 MB each, by patterns) stay within this;
 // the queries beyond it are left.
 constexpr int64_t kSmallBatchWork = (int64_t)256 << 20;
 // round_budget > 0 bounds the bytes written for them in total (a query above
-// it is left).
-void run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int32_t nq,
-                     int64_t budget, int64_t round_budget, int64_t max_rows, hipStream_t s,
-                     std::vector<DevQueryOut>& out);
+// it is left).  server: rounds follow at once, which also take the queries
+// left; the launch is then made unless one that cannot start in it has as many
+// patterns as any that can.
+struct SmallBatchEnd {
+  bool alone;    // the queries left are few, to be run alone
+  bool settled;  // else the stream is to be waited for before the next such call
+};
+SmallBatchEnd run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int32_t nq,
+                              int64_t budget, int64_t round_budget, int64_t max_rows, bool server,
+                              hipStream_t s, std::vector<DevQueryOut>& out);
 
 // req and res may be host memory; each workgroup of kBlock requests writes
 // `report` to its word

@@ -437,6 +437,15 @@ struct Exec {
     return false;
   }
 
+  // Whether the query's answer is a relation of the store, or nothing, as far as
+  // is known without a launch.
+  bool is_view() const {
+    if (pl->pats.size() != 1) return false;
+    const gsmat_pattern& q = pl->pats[0];
+    if (is_var(q.s) && is_var(q.o)) return q.s != q.o;
+    return pl->lk_store == st->uid && pl->lk.size() == 1 && pl->lk[0].valid;
+  }
+
   // Whether a batch tries the whole query in one launch: its first relation
   // has at most kSmallRows rows, as far as is known without a lookup.
   bool small_first() const {
@@ -1031,9 +1040,9 @@ bool run_query(gsmat_store* st, const gsmat_query_plan* pl, int64_t budget_bytes
   return ex.settled;
 }
 
-void run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int32_t nq,
-                     int64_t budget, int64_t round_budget, int64_t max_rows, hipStream_t s,
-                     std::vector<DevQueryOut>& out) {
+SmallBatchEnd run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int32_t nq,
+                              int64_t budget, int64_t round_budget, int64_t max_rows, bool server,
+                              hipStream_t s, std::vector<DevQueryOut>& out) {
   out.clear();
   out.resize(nq);
   for (DevQueryOut& o : out) o.state = kDevFallback;
@@ -1048,43 +1057,79 @@ void run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int3
     Table w;            // that table
     bool skip = false;  // left to the rounds
   };
-  std::vector<One> v;
-  v.reserve(nq);
+  // How each query starts, and whether the launch is made.
+  enum : char { kAbsent, kView, kIn, kRest };
+  std::vector<char> how(nq);
   constexpr int kFin = 1;  // every query's own final block: of 4 KiB
   int64_t work_bytes = 0;
+  int n = 0, most_pats = 0, rest_pats = 0, rest_steps = 0, unsure = 0;
+  auto adaptive = [&](int i) { return plans[i]->mode == GSMAT_PLAN_ADAPTIVE; };
+  // a pattern after the first adds one variable at most
+  auto layout = [&](int i) {
+    const int np = (int)plans[i]->pats.size();
+    return SmallLayout(np, np + 1);
+  };
   for (int i = 0; i < nq; ++i) {
     const gsmat_query_plan* pl = plans[i];
-    // a pattern after the first adds one variable at most
-    One o{i, SmallLayout((int)pl->pats.size(), (int)pl->pats.size() + 1)};
-    o.res.reset(new gsmat_result);
-    o.res->st = st;
-    o.res->stream = s;
-    o.res->n_vars = pl->n_vars;
-    o.res->reset_steps(pl->steps.size());
+    const Exec ex{st, pl, s, budget, max_rows, nullptr, adaptive(i)};
+    const int np = (int)pl->pats.size();
     bool absent = false;
     for (const gsmat_pattern& q : pl->pats)
       absent |= q.p >= st->P || (!is_var(q.s) && q.s >= st->V) || (!is_var(q.o) && q.o >= st->V);
-    if (absent) {  // matches nothing
-      out[i] = DevQueryOut{std::move(o.res), kDevDone, GSMAT_OK};
-      continue;
+    how[i] = absent ? kAbsent
+             : ex.is_view() ? kView
+             : ex.small_first() && work_bytes + layout(i).bytes <= kSmallBatchWork ? kIn : kRest;
+    if (how[i] == kIn) {
+      work_bytes += layout(i).bytes;
+      most_pats = std::max(most_pats, np);
+      unsure += np >= 3;
+      ++n;
+    } else if (how[i] == kRest) {
+      rest_pats = std::max(rest_pats, np);
+      rest_steps += np;
     }
-    o.ex.reset(new Exec{st, pl, s, budget, max_rows, o.res.get(), pl->mode == GSMAT_PLAN_ADAPTIVE});
+  }
+  const int alone = std::max(most_pats, rest_pats) + 2;  // steps that may be taken alone
+  if (server ? rest_pats >= most_pats : rest_steps > alone || unsure > kSmallUnsure)
+    return {false, true};
+  std::vector<One> v;
+  v.reserve(n);
+  auto finish = [&](One& o, auto&& f) {
+    const gsmat_status rc = guarded([&]() -> gsmat_status {
+      try {
+        f();
+      } catch (...) {
+        o.ex->release_all();
+        throw;
+      }
+      return GSMAT_OK;
+    });
+    out[o.q] = rc == GSMAT_OK ? DevQueryOut{std::move(o.res), kDevDone, GSMAT_OK}
+                              : DevQueryOut{nullptr, kDevFailed, rc};
+    return rc == GSMAT_OK && o.ex->settled;
+  };
+  for (int i = 0; i < nq; ++i) {
+    if (how[i] == kRest) continue;
+    One o{i, layout(i)};
+    o.res.reset(new gsmat_result);
+    o.res->st = st;
+    o.res->stream = s;
+    o.res->n_vars = plans[i]->n_vars;
+    o.res->reset_steps(plans[i]->steps.size());
+    o.ex.reset(new Exec{st, plans[i], s, budget, max_rows, o.res.get(), adaptive(i)});
     o.t.n = 1;
     o.t.k = 0;
-    if (!o.ex->small_first()) continue;
-    if (work_bytes + o.l.bytes > kSmallBatchWork) continue;
-    work_bytes += o.l.bytes;
-    v.push_back(std::move(o));
+    if (how[i] == kIn) v.push_back(std::move(o));
+    else finish(o, [&] { if (how[i] == kView) o.ex->run(0, o.t, all_of(plans[i])); });
   }
-  if (v.empty()) return;
-  const int n = (int)v.size();
+  if (n == 0) return {!server, true};
   DeviceMem* mem = st->mem.get();
   std::shared_ptr<Arena> work, fin, outs;
   try {
     work = std::make_shared<Arena>(mem, (size_t)work_bytes, s);
     fin = std::make_shared<Arena>(mem, (size_t)kFinBytes[kFin] * n, s);
   } catch (const OomFail&) {
-    return;  // the rounds may need less
+    return {false, true};  // the rounds may need less
   }
   SmallReport* reps =
       (SmallReport*)query_area().get((sizeof(SmallArgs) + sizeof(SmallReport) +
@@ -1105,15 +1150,15 @@ void run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int3
   const uint32_t seq = next_report();
   launch_small(small_store(st), args, reps, n, seq, s);
   for (int i = 0; i < n; ++i) host_wait_words(&reps[i].seq, 1, seq, s);
-  // Finished here: what is done, and what only has to be written (10 us of
-  // launches each, no wait).  A query left on the way costs the general path
-  // 50 us to 200 us, the rounds about 600 us for any number of them: up to four
-  // go on alone, more go to the rounds together, from the start.
-  int unfinished = 0;
+  // Finished here: what is done, what only has to be written, and with few
+  // steps left in all the queries left on the way.
   auto left = [&](const SmallReport& r) {
     return r.status == kSmallMore || (r.status == kSmallWrite && (r.rem & ~(1u << r.tp)) != 0);
   };
-  for (int i = 0; i < n; ++i) unfinished += left(reps[i]);
+  for (int i = 0; i < n; ++i)
+    if (left(reps[i]))
+      rest_steps += __builtin_popcount(reps[i].rem) - (reps[i].status == kSmallWrite);
+  bool go_alone = !server && rest_steps <= alone;
   // everything to be written goes out in one launch, into one block, as the
   // outputs of a round do
   int64_t written = 0, total = 0, most = 0;
@@ -1124,9 +1169,13 @@ void run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int3
     One& o = v[i];
     const SmallReport& r = reps[i];
     const int64_t bytes = Exec::out_bytes(r);
-    o.skip = (left(r) && (unfinished > 4 || round_budget > 0)) ||
-             (round_budget > 0 && written + bytes > round_budget);
+    o.skip = left(r) && !go_alone;
     if (o.skip) continue;
+    if (round_budget > 0 && written + bytes > round_budget) {
+      o.skip = true;
+      go_alone = false;  // the rounds take it, and what is found left from here on
+      continue;
+    }
     written += bytes;
     const bool move = r.status == kSmallDone && r.n > 0 && r.place == kAtWork;
     if (!move && !(r.status == kSmallWrite && o.ex->one_piece(r))) continue;
@@ -1143,6 +1192,7 @@ void run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int3
     if (o.at < 0) continue;
     if (!outs) {
       o.skip = true;
+      go_alone = false;
       continue;
     }
     o.ex->prepare_write(r, (const int64_t*)((char*)o.sm.work + o.l.offs),
@@ -1157,24 +1207,15 @@ void run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int3
     One& o = v[i];
     const SmallReport& r = reps[i];
     if (o.skip) continue;
-    int si = 0;
-    uint32_t rem = 0;
-    const gsmat_status rc = guarded([&]() -> gsmat_status {
-      try {
-        if (!o.ex->finish_small(r, (const int64_t*)((char*)o.sm.work + o.l.offs), o.sm, si, o.t,
-                                rem, o.at >= 0 ? &o.w : nullptr))
-          o.ex->run(si, o.t, rem);
-      } catch (...) {
-        o.ex->release_all();
-        throw;
-      }
-      return GSMAT_OK;
+    settled &= finish(o, [&] {
+      int si = 0;
+      uint32_t rem = 0;
+      if (!o.ex->finish_small(r, (const int64_t*)((char*)o.sm.work + o.l.offs), o.sm, si, o.t, rem,
+                              o.at >= 0 ? &o.w : nullptr))
+        o.ex->run(si, o.t, rem);
     });
-    settled &= rc == GSMAT_OK && o.ex->settled;
-    out[o.q] = rc == GSMAT_OK ? DevQueryOut{std::move(o.res), kDevDone, GSMAT_OK}
-                              : DevQueryOut{nullptr, kDevFailed, rc};
   }
-  if (!settled) host_sync(s);
+  return {go_alone, settled};
 }
 
 void run_collect(gsmat_store* st, const gsmat_query_plan* pl, const Table* t0,

@@ -273,3 +273,58 @@ def test_batch_areas_stay_small(G):
             pl.close()
     st.close()
     assert mem.bytes == 0
+
+
+def test_batch_routes(G):
+    """Which batches take the small launch, the rounds, or neither: rounds only
+    where too many queries cannot start in the launch, may outgrow it or have;
+    the rows are those of the queries alone, in the same order."""
+    s, p, o, V, P = graph(5000, 3, 8)
+    st = G.gsmat_load_triples(s, p, o, V, P)
+    G.gsmat_build_index(st)
+    view = [[0, 0, -1]]
+    two = [[1, 1, -1], [-1, 3, -2]]
+    three = [[1, 1, -1], [-1, 3, -2], [-2, 3, -3]]
+    wide = [[0, 0, -1], [-1, 3, -2]]                 # starts from 5000 rows
+    grows = [[-1, 4, 5], [-1, 1, -2], [-2, 3, -3]]   # 3000 rows, then 7700
+    for name, queries, rounds in [
+            ("views", [view] * 7 + [[[-1, 4, 5]], [[3, 4, 5]], [[-1, 7, -2]]], False),
+            ("two patterns", [two] * 300, False),
+            ("two patterns, one wide", [two] * 30 + [wide], False),
+            ("two patterns, many wide", [two] * 30 + [wide] * 9, True),
+            ("three patterns", [three] * 64, False),
+            ("more of three patterns", [three] * 65, True),
+            ("two grow", [three] * 20 + [grows] * 2, False),
+            ("many grow", [three] * 20 + [grows] * 20, True),
+            ("one wide alone", [wide], False)]:
+        plans, _ = G.gsmat_plan_batch(st, queries, G.PLAN_DEFAULT)
+        res = []
+        n = launches(G, lambda: res.extend(G.gsmat_join_batch(st, plans)[0]))
+        took = sum(r["tasks"] for r in G.gsmat_batch_round_stats(st)) > 0
+        print(f"[gpu] routes: {name}, {n} launches, rounds {took}", flush=True)
+        assert took == rounds, name
+        assert name != "views" or n == 0
+        alone = {}
+        for q, pl, r in zip(queries, plans, res):
+            key = str(q)
+            if key not in alone:
+                one = G.gsmat_join(st, pl)
+                alone[key] = G.gsmat_fetch_bindings(one), G.gsmat_result_info(one)
+                one.close()
+            assert np.array_equal(G.gsmat_fetch_bindings(r), alone[key][0]), name
+            assert G.gsmat_result_info(r) == alone[key][1], name
+            r.close()
+            pl.close()
+    sv = G.gsmat_server_new(st)
+    plans, _ = G.gsmat_plan_batch(st, [view] * 6, G.PLAN_ADAPTIVE)
+    for i, pl in enumerate(plans):
+        G.gsmat_server_submit(sv, pl, i)
+    assert launches(G, lambda: G.gsmat_server_step(sv)) == 0
+    done = G.gsmat_server_poll(sv)
+    assert len(done) == 6 and all(G.gsmat_result_info(r)["rows"] == 5000 for _, r, _ in done)
+    for _, r, _ in done:
+        r.close()
+    sv.close()
+    for pl in plans:
+        pl.close()
+    st.close()
