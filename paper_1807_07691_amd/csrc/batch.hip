@@ -1183,7 +1183,8 @@ void run_batch_any(gsmat_store* st, const gsmat_query_plan* const* plans, int32_
     run_batch_device(st, plans, n, budget_bytes, max_rows, s, out);
     return;
   }
-  const SmallBatchEnd e = run_small_batch(st, plans, n, budget_bytes, 0, max_rows, false, s, out);
+  const SmallBatchEnd e = run_small_batch(st, plans, n, budget_bytes, budget_bytes, max_rows, false, s,
+                                          out);
   std::vector<const gsmat_query_plan*> rest;
   std::vector<int32_t> at;
   for (int32_t i = 0; i < n; ++i)

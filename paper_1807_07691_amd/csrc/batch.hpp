@@ -143,7 +143,7 @@ constexpr int32_t kSmallUnsure = 64;
 // the queries beyond it are left.
 constexpr int64_t kSmallBatchWork = (int64_t)256 << 20;
 // round_budget > 0 bounds the bytes written for them in total (a query above
-// it is left).  server: rounds follow at once, which also take the queries
+// it is left, but not the first).  server: rounds follow at once, which also take the queries
 // left; the launch is then made unless one that cannot start in it has as many
 // patterns as any that can.
 struct SmallBatchEnd {

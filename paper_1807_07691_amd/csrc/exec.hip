@@ -1171,14 +1171,16 @@ SmallBatchEnd run_small_batch(gsmat_store* st, const gsmat_query_plan* const* pl
     const int64_t bytes = Exec::out_bytes(r);
     o.skip = left(r) && !go_alone;
     if (o.skip) continue;
-    if (round_budget > 0 && written + bytes > round_budget) {
+    const bool pieces = Exec::counted(r) && !o.ex->one_piece(r);
+    if (pieces) continue;  // each within the step budget
+    if (round_budget > 0 && written > 0 && written + bytes > round_budget) {
       o.skip = true;
       go_alone = false;  // the rounds take it, and what is found left from here on
       continue;
     }
     written += bytes;
     const bool move = r.status == kSmallDone && r.n > 0 && r.place == kAtWork;
-    if (!move && !(r.status == kSmallWrite && o.ex->one_piece(r))) continue;
+    if (!move && !Exec::counted(r)) continue;
     o.at = total;
     total += bytes;
   }

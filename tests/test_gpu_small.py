@@ -328,3 +328,29 @@ def test_batch_routes(G):
     for pl in plans:
         pl.close()
     st.close()
+
+
+def test_batch_outputs_within_the_budget(G):
+    """Outputs that fit the budget each but not together: what is above it is
+    left to the rounds, which take it a round at a time; the rows are the same."""
+    s, p, o, V, P = graph(5000, 3, 8)
+    st = G.gsmat_load_triples(s, p, o, V, P)
+    G.gsmat_build_index(st)
+    q = [[-1, 4, 5], [-1, 1, -2]]
+    want = G.evaluate(st, q)
+    one = 4 * 2 * ((len(want) + 63) // 64 * 64)
+    assert len(want) > ROWS
+    for n in (1, 3, 20):
+        for budget, rounds in ((0, False), (n * one, False), (n * one - 1, n > 1),
+                               (one, n > 1), (one // 3, False)):
+            plans, _ = G.gsmat_plan_batch(st, [q] * n, G.PLAN_ADAPTIVE)
+            res, _ = G.gsmat_join_batch(st, plans, budget)
+            took = sum(r["tasks"] for r in G.gsmat_batch_round_stats(st)) > 0
+            print(f"[gpu] {n} outputs of {one}, budget {budget}: rounds {took}", flush=True)
+            assert took == rounds, (n, budget)
+            for r in res:
+                assert np.array_equal(G.gsmat_fetch_bindings(r), want)
+                r.close()
+            for pl in plans:
+                pl.close()
+    st.close()
