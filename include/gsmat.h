@@ -528,9 +528,9 @@ gsmat_status gsmat_parse_bgp(const gsmat_dict* d, const char* text, size_t len,
  * length of its predicate, capped by the Theorem 1 bound (Sec. 6.2).  Each
  * gsmat_server_step admits what fits and runs one step of every admitted
  * query as one batched round (as in gsmat_join_batch with host-driven
- * rounds; four or more that have not started first run in one launch, which
- * finishes those of few rows), so queries that arrive while others run join them at the next
- * round; when the server holds at most two queries, none started and none
+ * rounds; four or more that have not started may first run in one launch, which
+ * finishes those of few rows and whose work areas count as bytes held), so
+ * queries that arrive while others run join them at the next round; when the server holds at most two queries, none started and none
  * waiting, the step instead runs the oldest to completion with the
  * single-query executor (the other waits for the next step; later arrivals
  * are admitted at the next step).  A round whose

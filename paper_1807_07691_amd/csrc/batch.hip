@@ -954,16 +954,20 @@ struct gsmat_server {
     for (Finished& f : done) delete f.res;
   }
 
-  // Bytes the admitted queries hold or are expected to need, and those of
-  // finished results not yet polled.
-  int64_t committed() const {
+  // Bytes the admitted queries hold (or with `expected`, are expected to need),
+  // and those of finished results not yet polled.
+  int64_t committed(bool expected = true) const {
     int64_t c = 0;
     for (const BQ& b : bt.q) {
       const int64_t held = b.t.keep ? 4 * col_stride(b.t.n) * (int64_t)b.t.k : 0;
-      c += std::max(held, b.est_bytes);
+      c += expected ? std::max(held, b.est_bytes) : held;
     }
-    for (const Finished& f : done)
-      if (f.res) c += 4 * col_stride(f.res->rows) * (int64_t)std::max(f.res->n_vars, 1);
+    for (const Finished& f : done) {
+      if (!f.res) continue;
+      int64_t own = 0;  // blocks of its own may be larger than its rows
+      for (const Segment& g : f.res->segs) own += (int64_t)g.owned_bytes;
+      c += std::max(own, 4 * col_stride(f.res->rows) * (int64_t)std::max(f.res->n_vars, 1));
+    }
     return c;
   }
 
@@ -1012,8 +1016,11 @@ struct gsmat_server {
     }
     if (plans.size() < 4) return;  // a round or two of so few is as fast
     std::vector<DevQueryOut> out;
-    const SmallBatchEnd e = run_small_batch(st, plans.data(), (int32_t)plans.size(), bt.budget,
-                                            mem_budget, bt.max_rows, true, s, out);
+    SmallBatchRun run{bt.budget, bt.max_rows};
+    run.server = true;
+    if (mem_budget > 0) run.room = mem_budget - committed(false);
+    const SmallBatchEnd e =
+        run_small_batch(st, plans.data(), (int32_t)plans.size(), run, s, out);
     if (!e.settled) host_sync(s);
     for (size_t j = 0; j < at.size(); ++j) {
       BQ& b = bt.q[at[j]];
@@ -1183,8 +1190,8 @@ void run_batch_any(gsmat_store* st, const gsmat_query_plan* const* plans, int32_
     run_batch_device(st, plans, n, budget_bytes, max_rows, s, out);
     return;
   }
-  const SmallBatchEnd e = run_small_batch(st, plans, n, budget_bytes, budget_bytes, max_rows, false, s,
-                                          out);
+  const SmallBatchEnd e =
+      run_small_batch(st, plans, n, SmallBatchRun{budget_bytes, max_rows, budget_bytes}, s, out);
   std::vector<const gsmat_query_plan*> rest;
   std::vector<int32_t> at;
   for (int32_t i = 0; i < n; ++i)

@@ -142,17 +142,24 @@ constexpr int32_t kSmallUnsure = 64;
 // The queries' work areas (0.1 to 2.1 MB each, by patterns) stay within this;
 // the queries beyond it are left.
 constexpr int64_t kSmallBatchWork = (int64_t)256 << 20;
-// round_budget > 0 bounds the bytes written for them in total (a query above
-// it is left, but not the first).  server: rounds follow at once, which also take the queries
-// left; the launch is then made unless one that cannot start in it has as many
-// patterns as any that can.
+struct SmallBatchRun {
+  int64_t budget, max_rows;  // of each query, as in gsmat_join
+  // > 0: bytes written for all of them (a query above that is left, but not the
+  // first)
+  int64_t outputs = 0;
+  // Rounds follow at once, which also take the queries left: the launch is made
+  // unless one that cannot start in it has as many patterns as any that can.
+  // The areas and what is written stay within `room`.
+  bool server = false;
+  int64_t room = INT64_MAX;
+};
 struct SmallBatchEnd {
   bool alone;    // the queries left are few, to be run alone
   bool settled;  // else the stream is to be waited for before the next such call
 };
 SmallBatchEnd run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int32_t nq,
-                              int64_t budget, int64_t round_budget, int64_t max_rows, bool server,
-                              hipStream_t s, std::vector<DevQueryOut>& out);
+                              const SmallBatchRun& run, hipStream_t s,
+                              std::vector<DevQueryOut>& out);
 
 // req and res may be host memory; each workgroup of kBlock requests writes
 // `report` to its word

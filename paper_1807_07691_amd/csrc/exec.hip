@@ -639,10 +639,8 @@ struct Exec {
       }
     } else if (fin >= 0) {
       o.keep = sm.fin_hold;
-      if (own) {
-        o.owned = sm.fin[fin];
-        o.owned_bytes = kFinBytes[fin];
-      }
+      o.owned_bytes = kFinBytes[fin];
+      if (own) o.owned = sm.fin[fin];
     } else {  // t's own columns, or views into the store
       o.owned = t.owned;
       o.owned_bytes = t.owned_bytes;
@@ -1041,8 +1039,10 @@ bool run_query(gsmat_store* st, const gsmat_query_plan* pl, int64_t budget_bytes
 }
 
 SmallBatchEnd run_small_batch(gsmat_store* st, const gsmat_query_plan* const* plans, int32_t nq,
-                              int64_t budget, int64_t round_budget, int64_t max_rows, bool server,
-                              hipStream_t s, std::vector<DevQueryOut>& out) {
+                              const SmallBatchRun& run, hipStream_t s,
+                              std::vector<DevQueryOut>& out) {
+  const int64_t budget = run.budget, max_rows = run.max_rows;
+  const bool server = run.server;
   out.clear();
   out.resize(nq);
   for (DevQueryOut& o : out) o.state = kDevFallback;
@@ -1061,7 +1061,8 @@ SmallBatchEnd run_small_batch(gsmat_store* st, const gsmat_query_plan* const* pl
   enum : char { kAbsent, kView, kIn, kRest };
   std::vector<char> how(nq);
   constexpr int kFin = 1;  // every query's own final block: of 4 KiB
-  int64_t work_bytes = 0;
+  const int64_t work_most = std::min(kSmallBatchWork, run.room);
+  int64_t work_bytes = 0, room = run.room;
   int n = 0, most_pats = 0, rest_pats = 0, rest_steps = 0, unsure = 0;
   auto adaptive = [&](int i) { return plans[i]->mode == GSMAT_PLAN_ADAPTIVE; };
   // a pattern after the first adds one variable at most
@@ -1078,9 +1079,11 @@ SmallBatchEnd run_small_batch(gsmat_store* st, const gsmat_query_plan* const* pl
       absent |= q.p >= st->P || (!is_var(q.s) && q.s >= st->V) || (!is_var(q.o) && q.o >= st->V);
     how[i] = absent ? kAbsent
              : ex.is_view() ? kView
-             : ex.small_first() && work_bytes + layout(i).bytes <= kSmallBatchWork ? kIn : kRest;
+             : ex.small_first() && work_bytes + layout(i).bytes + kFinBytes[kFin] <= work_most
+                 ? kIn : kRest;
     if (how[i] == kIn) {
       work_bytes += layout(i).bytes;
+      room -= layout(i).bytes + kFinBytes[kFin];
       most_pats = std::max(most_pats, np);
       unsure += np >= 3;
       ++n;
@@ -1172,8 +1175,11 @@ SmallBatchEnd run_small_batch(gsmat_store* st, const gsmat_query_plan* const* pl
     o.skip = left(r) && !go_alone;
     if (o.skip) continue;
     const bool pieces = Exec::counted(r) && !o.ex->one_piece(r);
-    if (pieces) continue;  // each within the step budget
-    if (round_budget > 0 && written > 0 && written + bytes > round_budget) {
+    if (pieces) {  // each within the step budget
+      o.skip = bytes > room - total;
+      continue;
+    }
+    if (run.outputs > 0 && written > 0 && written + bytes > run.outputs) {
       o.skip = true;
       go_alone = false;  // the rounds take it, and what is found left from here on
       continue;
@@ -1181,6 +1187,11 @@ SmallBatchEnd run_small_batch(gsmat_store* st, const gsmat_query_plan* const* pl
     written += bytes;
     const bool move = r.status == kSmallDone && r.n > 0 && r.place == kAtWork;
     if (!move && !Exec::counted(r)) continue;
+    if (bytes > room - total) {
+      o.skip = true;
+      go_alone = false;
+      continue;
+    }
     o.at = total;
     total += bytes;
   }

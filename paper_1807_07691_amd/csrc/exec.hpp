@@ -31,7 +31,7 @@ struct Segment {
   int64_t rows = 0;
   const int32_t* col[kMaxCols] = {};  // variable order
   void* owned = nullptr;
-  size_t owned_bytes = 0;
+  size_t owned_bytes = 0;             // (without owned: its own part of keep)
   std::shared_ptr<Arena> keep;        // arena holding the columns, if any
   std::shared_ptr<void> hold;         // anything else the columns live in
 };

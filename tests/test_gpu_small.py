@@ -354,3 +354,33 @@ def test_batch_outputs_within_the_budget(G):
             for pl in plans:
                 pl.close()
     st.close()
+
+
+@pytest.mark.parametrize("budget", [1 << 20, 8 << 20, 64 << 20])
+def test_server_areas_within_its_budget(G, budget):
+    """The small launch's areas count as memory the admitted queries hold."""
+    s, p, o, V, P = graph(700, 7, 5)
+    mem = Counting(G)
+    st = G.gsmat_load_triples(s, p, o, V, P, allocator=mem.allocator)
+    G.gsmat_build_index(st)
+    queries = [[[i + 1, 1, -1], [-1, 3, -2], [-2, 3, -3]] for i in range(128)]
+    want = [G.evaluate(st, q) for q in queries]
+    plans, _ = G.gsmat_plan_batch(st, queries, G.PLAN_ADAPTIVE)
+    before = mem.peak = mem.bytes
+    sv = G.gsmat_server_new(st, budget)
+    for i, pl in enumerate(plans):
+        G.gsmat_server_submit(sv, pl, i)
+    left = len(plans)
+    while left:
+        G.gsmat_server_step(sv)
+        for tag, r, status in G.gsmat_server_poll(sv):
+            assert status == 0 and np.array_equal(G.gsmat_fetch_bindings(r), want[tag])
+            r.close()
+            left -= 1
+    print(f"[gpu] server budget {budget}: peak {mem.peak - before}", flush=True)
+    assert mem.peak - before <= budget
+    sv.close()
+    for pl in plans:
+        pl.close()
+    st.close()
+    assert mem.bytes == 0
