@@ -226,8 +226,11 @@ gsmat_status gsmat_join(gsmat_store* st, const gsmat_query_plan* pl, int64_t bud
  * array of the library (one per GPU, held until the process ends), and the
  * result copied into the caller's device buffer: variable v's column at
  * out + v * out_stride, rows [0, *n_rows), in the row order gsmat_join gives.
- * No device memory is allocated or freed.  *n_rows always receives the row
- * count when it is known.  EINVAL for a NULL store, plan or n_rows, a NULL
+ * No device memory is allocated or freed.  Queries of few rows run in one
+ * launch, as under gsmat_join, on a thread that has planned a query before
+ * (gsmat_plan, gsmat_plan_batch: the launch reports through host memory that the
+ * thread takes there); on other threads step by step.  *n_rows always receives
+ * the row count when it is known.  EINVAL for a NULL store, plan or n_rows, a NULL
  * out with out_cap > 0, out_cap < 0 or out_stride < out_cap; ENOMEM (message
  * names the limit) when the intermediates and the result do not fit the
  * 64 MiB array; ETOOBIG when the result has more than out_cap rows.  Calls on

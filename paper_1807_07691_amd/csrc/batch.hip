@@ -1517,6 +1517,7 @@ extern "C" gsmat_status gsmat_plan_batch(const gsmat_store* st, const gsmat_patt
     if (!st->built) throw StatusFail{GSMAT_ESTATE, "index not built"};
     if (mode != GSMAT_PLAN_PAPER && mode != GSMAT_PLAN_DEFAULT && mode != GSMAT_PLAN_ADAPTIVE)
       throw StatusFail{GSMAT_EINVAL, "unknown plan mode " + std::to_string(mode)};
+    (void)host_note();  // the thread's area: here, not in a join that must not allocate
     PlanPrep P;
     plan_prepare(st, pats, n_pats, n_queries, mode, (hipStream_t)stream, &P);
     // the plans are independent: built on the host pool's threads

@@ -97,3 +97,35 @@ def test_noalloc_errors_then_correct(G, tiny):
     pl.close()
     print(f"[gpu] noalloc after errors: rows={n}", flush=True)
     assert n == q.count and np.array_equal(got, want)
+
+
+def test_noalloc_launches_of_a_thread(G, tiny):
+    """A thread that planned its queries, one by one or as a batch, runs a small
+    one in one launch; a thread that planned none takes the general path."""
+    import threading
+
+    import torch
+    qs, st = tiny
+    q = next(q.tps for q in sorted(qs, key=lambda q: q.count)
+             if len(q.tps) >= 2 and 1 <= q.count <= 2000)
+    out = torch.empty((8, 4096), dtype=torch.int32, device="cuda")
+    mine = G.gsmat_plan(st, q, G.PLAN_ADAPTIVE)
+    got = {}
+
+    def run(how, make):
+        pl = make()
+        G.gsmat_prof_enable()
+        got[how, "rows"] = G.gsmat_join_noalloc(st, pl, out.data_ptr(), 4096, 4096)
+        got[how] = sum(k["launches"] for k in G.gsmat_prof_read().values())
+        G.gsmat_prof_enable(0)
+
+    for how, make in [("plan", lambda: G.gsmat_plan(st, q, G.PLAN_ADAPTIVE)),
+                      ("batch", lambda: G.gsmat_plan_batch(st, [q], G.PLAN_ADAPTIVE)[0][0]),
+                      ("other", lambda: mine)]:
+        t = threading.Thread(target=run, args=(how, make))
+        t.start()
+        t.join()
+    print(f"[gpu] noalloc launches by thread: {got}", flush=True)
+    assert got["plan", "rows"] == got["batch", "rows"] == got["other", "rows"] > 0
+    assert got["batch"] == got["plan"] < got["other"]
+    mine.close()
