@@ -921,7 +921,8 @@ Arena::Arena(DeviceMem* m, size_t b, hipStream_t st) : mem(m), bytes(b), s(st) {
   if (!p) throw OomFail{bytes};
 }
 Arena::~Arena() {
-  if (p) mem->free(p, bytes, s);
+  if (idle) mem->free_idle(p, bytes, s);
+  else mem->free(p, bytes, s);
 }
 
 uint32_t step_completes(const gsmat_query_plan* pl, const gsmat_step_info& sp) {

@@ -19,6 +19,7 @@ struct Arena {
   void* p = nullptr;
   size_t bytes = 0;
   hipStream_t s = nullptr;
+  bool idle = false;  // no work on it is left to wait for
   Arena(DeviceMem* m, size_t b, hipStream_t st);
   // takes over an allocation of b bytes at p made from m
   Arena(DeviceMem* m, void* p_, size_t b, hipStream_t st) : mem(m), p(p_), bytes(b), s(st) {}

@@ -130,6 +130,17 @@ constexpr int64_t kXSmall = 4096;
 constexpr int kXThreads = 1024;
 constexpr int kXRows = (int)kXSmall / kXThreads;  // rows per thread
 constexpr int kXTables = 4;                       // matched tables of a left join
+// Blocks the rows may be put in, the smallest that holds them: kept rows hold at
+// most four times their bytes (or 1 KiB), not the part's.
+constexpr int kXBlocks = 6;
+constexpr int64_t x_block_bytes(int f) { return (int64_t)1024 << (2 * f); }
+static_assert(x_block_bytes(kXBlocks - 1) >= 4 * kXSmall * kMaxCols, "a whole part fits");
+__host__ __device__ inline int x_block_of(int64_t rows, int k) {
+  const int64_t bytes = 4 * ((rows + 63) / 64 * 64) * k;
+  int f = 0;
+  while (f < kXBlocks - 1 && bytes > x_block_bytes(f)) ++f;
+  return f;
+}
 
 struct XSelect {
   ColSet in;    // the part's columns
@@ -138,8 +149,7 @@ struct XSelect {
   const int32_t* rid[kXTables];  // left join: row ids of the matched tables
   int64_t rn[kXTables];
   int32_t n, k, tables, filter;
-  int32_t* out;
-  int64_t stride;
+  int32_t* out[kXBlocks];
 };
 
 __global__ __launch_bounds__(kXThreads) void k_x_select(XSelect X, int64_t* total, uint32_t* word,
@@ -182,14 +192,17 @@ __global__ __launch_bounds__(kXThreads) void k_x_select(XSelect X, int64_t* tota
     if (w < wave) base += cnt[w];
     m += cnt[w];
   }
-  if (m > 0 && m < X.n)
+  if (m > 0 && m < X.n) {
+    int32_t* const out = X.out[x_block_of(m, X.k)];
+    const int stride = (m + 63) / 64 * 64;
     for (int col = 0; col < X.k; ++col) {
       const int32_t* src = X.in.c[col];
-      int32_t* dst = X.out + col * X.stride;
+      int32_t* dst = out + col * stride;
 #pragma unroll
       for (int u = 0; u < kXRows; ++u)
         if (keep[u]) dst[base + pos[u]] = src[wave * (64 * kXRows) + u * 64 + lane];
     }
+  }
   if (tid == 0) total[0] = m;
   dev::report_one(word, report);
 }
@@ -383,20 +396,25 @@ struct XRun {
     std::copy(P.var, P.var + P.k, o.var);
     x.n = (int32_t)P.n;
     x.k = P.k;
-    x.stride = col_stride(P.n);
-    auto a = arena(sizeof(int32_t) * (size_t)x.stride * (size_t)std::max(P.k, 1));
-    x.out = (int32_t*)a->p;
-    for (int c = 0; c < P.k; ++c) {
-      x.in.c[c] = P.col[c];
-      o.col[c] = x.out + c * x.stride;
+    std::shared_ptr<Arena> block[kXBlocks];
+    for (int f = P.k > 0 ? x_block_of(P.n, P.k) : -1; f >= 0; --f) {
+      block[f] = arena((size_t)x_block_bytes(f));
+      x.out[f] = (int32_t*)block[f]->p;
     }
-    o.keep.push_back(a);
+    for (int c = 0; c < P.k; ++c) x.in.c[c] = P.col[c];
     const HostNote h = host_note();
     const uint32_t report = next_report();
     hipLaunchKernelGGL(k_x_select, dim3(1), dim3(kXThreads), 0, s, x, h.value, h.word, report);
     GS_HIP(hipGetLastError());
     host_wait_words(h.word, 1, report, s);
     o.n = *h.value;
+    const int used = o.n > 0 && o.n < P.n && P.k > 0 ? x_block_of(o.n, P.k) : -1;
+    for (int f = 0; f < kXBlocks; ++f)
+      if (block[f] && f != used) block[f]->idle = true;  // not written
+    if (used >= 0) {
+      for (int c = 0; c < P.k; ++c) o.col[c] = x.out[used] + c * col_stride(o.n);
+      o.keep.push_back(block[used]);
+    }
     if (o.n == P.n) out.push_back(std::move(P));
     else if (o.n > 0) out.push_back(std::move(o));
   }

@@ -384,3 +384,24 @@ def test_server_areas_within_its_budget(G, budget):
         pl.close()
     st.close()
     assert mem.bytes == 0
+
+
+def test_kept_selections_hold_little(G):
+    """The rows an OPTIONAL or FILTER over a small part keeps hold at most four
+    times their columns, or 1 KiB, and not the whole part."""
+    s, p, o, V, P = graph(4000, 1, 5)
+    mem = Counting(G)
+    st = G.gsmat_load_triples(s, p, o, V, P, allocator=mem.allocator)
+    G.gsmat_build_index(st)
+    for keep in (1, 64, 65, 1000, 3999, 4000):
+        before = mem.bytes
+        r = G.gsmat_join_ext(st, [[0, 0, -1, 0, 0]], [[G.F_LE, -1, keep, 0]])
+        n, held = G.gsmat_result_info(r)["rows"], mem.bytes - before
+        print(f"[gpu] kept selection rows={n} holds {held}", flush=True)
+        assert n == keep
+        assert held <= max(1024, 4 * 4 * ((n + 63) // 64 * 64))
+        assert np.array_equal(np.sort(G.gsmat_fetch_bindings(r)[:, 0]), np.arange(1, keep + 1))
+        r.close()
+        assert mem.bytes == before
+    st.close()
+    assert mem.bytes == 0
