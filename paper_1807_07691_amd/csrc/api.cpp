@@ -55,20 +55,20 @@ void host_sync(hipStream_t s) {
 // stream's completion is signalled and seen.  The looking ends after 200 us,
 // so a long queue does not hold a core, and a failed or capturing stream is
 // reported by the wait that follows.
-void host_wait_words(const uint32_t* p, int n, uint32_t want, hipStream_t s) {
+void host_wait_words(const uint32_t* p, int n, uint32_t want, hipStream_t s, int64_t stride) {
   HostTimer t(&g_sync_ms, &g_syncs);
   const double t0 = now_ms();
   int at = 0;
   do {
     for (int i = 0; i < 64; ++i) {
-      while (at < n && __atomic_load_n(p + at, __ATOMIC_ACQUIRE) == want) ++at;
+      while (at < n && __atomic_load_n(p + at * stride, __ATOMIC_ACQUIRE) == want) ++at;
       if (at == n) return;
       __builtin_ia32_pause();
     }
   } while (now_ms() - t0 < 0.2);
   GS_HIP(hipStreamSynchronize(s));
   for (; at < n; ++at)
-    if (__atomic_load_n(p + at, __ATOMIC_ACQUIRE) != want)
+    if (__atomic_load_n(p + at * stride, __ATOMIC_ACQUIRE) != want)
       throw StatusFail{GSMAT_EHIP, "internal: a kernel ended without its report"};
 }
 

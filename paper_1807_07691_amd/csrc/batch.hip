@@ -1278,7 +1278,10 @@ extern "C" gsmat_status gsmat_join_batch_bgp(gsmat_store* st, const gsmat_patter
     std::vector<gsmat_status> prc;
     std::vector<std::string> pmsg;
     std::vector<std::unique_ptr<gsmat_query_plan>> fb;
-    if (n_queries <= kSmallBatch && st->small_joins) {
+    // so many that may outgrow the small launch take the rounds anyway
+    int unsure = 0;
+    for (int i = 0; i < n_queries; ++i) unsure += n_pats[i] >= 3;
+    if (n_queries <= kSmallBatch && unsure <= kSmallUnsure && st->small_joins) {
       PlanPrep P;
       plan_prepare(st, pats, n_pats, n_queries, mode, s, &P);
       fb.resize(n_queries);

@@ -124,24 +124,28 @@ void run_batch_device_bgp(gsmat_store* st, const gsmat_pattern* pats, const int3
 // A batch of at most kSmallBatch queries may first run in one launch, a
 // workgroup per query (small.hip): out[i] as above, kDevFallback for the queries
 // left.  Two things decide whether that pays.
-//   * The rounds cost about 80 us each whatever the batch holds, so the launch
-//     wins only if no round is needed after it.  A query whose first relation has
+//   * The rounds cost about 75 us each whatever the batch holds, so the launch
+//     wins only if few are needed after it.  A query whose first relation has
 //     more than 4096 rows does not start in it, and one whose tables outgrow it
-//     is left on the way; both may go on alone, at about 45 us a step, while
-//     their steps number at most two more than the longest query's (the rounds
-//     there would be).  With more of the first kind it is not tried.
+//     is left on the way; both go on alone, at about 55 us a step, while their
+//     steps number at most a third more than the longest query's.  With more of
+//     the first kind the launch is not made, with more of both the rounds take
+//     what is left (60 queries of up to 30 000 rows, 9 steps left: alone 655 to
+//     680 us, by rounds 558 to 647, all by rounds 521 to 576).
 //   * A query of three patterns or more cannot be told to stay small: of those
 //     with up to 30 000 rows one in 25 outgrows it, of those with up to 10^6
 //     rows one in 7.  With more than kSmallUnsure of them it is not tried.
 // By the launch and by the rounds, us: 60 queries of 1 or 2 patterns and up to
-// 100 rows 47 and 167, 512 of them 215 and 239; 96 queries of 1 to 6 patterns and
-// up to 30 000 rows, where few enough are left, 203 and 498; where not, 60
-// queries 552 and 521, 512 queries 802 and 663.
+// 100 rows 40 and 187, 512 of them 151 and 290; 60 queries of 1 to 6 patterns and
+// up to 30 000 rows, where few enough are left, 89 to 295 and 550.
 constexpr int32_t kSmallBatch = 512;
 constexpr int32_t kSmallUnsure = 64;
 // The queries' work areas (0.1 to 2.1 MB each, by patterns) stay within this;
 // the queries beyond it are left.
 constexpr int64_t kSmallBatchWork = (int64_t)256 << 20;
+// One kept answer keeps the blocks of its batch's small answers: 64 KiB a query
+// for up to 32 queries, 4 KiB for 512.
+constexpr int64_t kSmallBatchFins = (int64_t)2 << 20;
 struct SmallBatchRun {
   int64_t budget, max_rows;  // of each query, as in gsmat_join
   // > 0: bytes written for all of them (a query above that is left, but not the

@@ -214,9 +214,9 @@ void host_sync(hipStream_t s);  // hipStreamSynchronize, timed for instrumentati
 // launch's number to a word of it last (one word per workgroup).
 // next_report: a number the calling thread's earlier launches did not have.
 uint32_t next_report();
-// Waits until each of the n words is `want`: looks at them for a short while,
-// then waits for the stream.
-void host_wait_words(const uint32_t* p, int n, uint32_t want, hipStream_t s);
+// Waits until each of the n words, stride apart, is `want`: looks at them for a
+// short while, then waits for the stream.
+void host_wait_words(const uint32_t* p, int n, uint32_t want, hipStream_t s, int64_t stride = 1);
 void host_event_sync(hipEvent_t e);  // hipEventSynchronize, timed likewise
 void prof_end(hipStream_t s, int cls, double bytes);
 bool prof_on(int cls);

@@ -1061,7 +1061,11 @@ SmallBatchEnd run_small_batch(gsmat_store* st, const gsmat_query_plan* const* pl
   // How each query starts, and whether the launch is made.
   enum : char { kAbsent, kView, kIn, kRest };
   std::vector<char> how(nq);
-  constexpr int kFin = 1;  // every query's own final block: of 4 KiB
+  // Every query's own final block, of a size that keeps the batch's within
+  // kSmallBatchFins (an answer in its block needs no write of its own: 17 queries of
+  // 137 to 2192 rows 195 us with 4 KiB, 176 with 64).
+  int tier = kSmallFins - 1;
+  while (tier > 0 && nq * kFinBytes[tier] > kSmallBatchFins) --tier;
   const int64_t work_most = std::min(kSmallBatchWork, run.room);
   int64_t work_bytes = 0, room = run.room;
   int n = 0, most_pats = 0, rest_pats = 0, rest_steps = 0, unsure = 0;
@@ -1080,11 +1084,11 @@ SmallBatchEnd run_small_batch(gsmat_store* st, const gsmat_query_plan* const* pl
       absent |= q.p >= st->P || (!is_var(q.s) && q.s >= st->V) || (!is_var(q.o) && q.o >= st->V);
     how[i] = absent ? kAbsent
              : ex.is_view() ? kView
-             : ex.small_first() && work_bytes + layout(i).bytes + kFinBytes[kFin] <= work_most
+             : ex.small_first() && work_bytes + layout(i).bytes + kFinBytes[tier] <= work_most
                  ? kIn : kRest;
     if (how[i] == kIn) {
       work_bytes += layout(i).bytes;
-      room -= layout(i).bytes + kFinBytes[kFin];
+      room -= layout(i).bytes + kFinBytes[tier];
       most_pats = std::max(most_pats, np);
       unsure += np >= 3;
       ++n;
@@ -1093,7 +1097,9 @@ SmallBatchEnd run_small_batch(gsmat_store* st, const gsmat_query_plan* const* pl
       rest_steps += np;
     }
   }
-  const int alone = std::max(most_pats, rest_pats) + 2;  // steps that may be taken alone
+  // Steps that may be taken alone: a third more than the rounds the longest
+  // query takes, which cost a third more each; two more if there is no launch.
+  const int alone = 4 * std::max(most_pats, rest_pats) / 3 + (n > 0 ? 0 : 2);
   if (server ? rest_pats >= most_pats : rest_steps > alone || unsure > kSmallUnsure)
     return {false, true};
   std::vector<One> v;
@@ -1131,7 +1137,7 @@ SmallBatchEnd run_small_batch(gsmat_store* st, const gsmat_query_plan* const* pl
   std::shared_ptr<Arena> work, fin, outs;
   try {
     work = std::make_shared<Arena>(mem, (size_t)work_bytes, s);
-    fin = std::make_shared<Arena>(mem, (size_t)kFinBytes[kFin] * n, s);
+    fin = std::make_shared<Arena>(mem, (size_t)kFinBytes[tier] * n, s);
   } catch (const OomFail&) {
     return {false, true};  // the rounds may need less
   }
@@ -1145,7 +1151,7 @@ SmallBatchEnd run_small_batch(gsmat_store* st, const gsmat_query_plan* const* pl
     o.sm.work = at;
     o.sm.work_bytes = (size_t)o.l.bytes;
     at += o.l.bytes;
-    o.sm.fin[kFin] = (char*)fin->p + kFinBytes[kFin] * i;
+    o.sm.fin[tier] = (char*)fin->p + kFinBytes[tier] * i;
     o.sm.work_hold = work;
     o.sm.fin_hold = fin;
     o.ex->fill_small(args[i], 0, o.t, all_of(plans[o.q]), o.l, o.sm);
@@ -1153,7 +1159,7 @@ SmallBatchEnd run_small_batch(gsmat_store* st, const gsmat_query_plan* const* pl
   }
   const uint32_t seq = next_report();
   launch_small(small_store(st), args, reps, n, seq, s);
-  for (int i = 0; i < n; ++i) host_wait_words(&reps[i].seq, 1, seq, s);
+  host_wait_words(&reps[0].seq, n, seq, s, sizeof(SmallReport) / sizeof(uint32_t));
   // Finished here: what is done, what only has to be written, and with few
   // steps left in all the queries left on the way.
   auto left = [&](const SmallReport& r) {

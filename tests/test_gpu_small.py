@@ -243,8 +243,8 @@ def test_kept_answers_hold_little(G):
 
 def test_batch_areas_stay_small(G):
     """What a batch's small launch takes follows each query's own patterns and
-    stays within 256 MiB, and one kept answer holds the batch's answers and 4
-    KiB a query, not every query's largest possible answer."""
+    stays within 256 MiB, and one kept answer holds the batch's answers and 2
+    MiB at most, not every query's largest possible answer."""
     s, p, o, V, P = graph(700, 7, 5)
     mem = Counting(G)
     st = G.gsmat_load_triples(s, p, o, V, P, allocator=mem.allocator)
@@ -265,8 +265,8 @@ def test_batch_areas_stay_small(G):
         answers = sum(4 * w.shape[1] * ((len(w) + 63) // 64 * 64) for w in want)
         for r in res[1:]:
             r.close()
-        if len(queries) == 60:
-            assert mem.bytes - before <= answers + 4096 * len(queries)
+        if queries[0] != chain:  # those take the rounds
+            assert mem.bytes - before <= answers + (2 << 20)
         res[0].close()
         assert mem.bytes == before
         for pl in plans:
