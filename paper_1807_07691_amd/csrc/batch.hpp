@@ -136,7 +136,7 @@ void run_batch_device_bgp(gsmat_store* st, const gsmat_pattern* pats, const int3
 //     with up to 30 000 rows one in 25 outgrows it, of those with up to 10^6
 //     rows one in 7.  With more than kSmallUnsure of them it is not tried.
 // By the launch and by the rounds, us: 60 queries of 1 or 2 patterns and up to
-// 100 rows 40 and 187, 512 of them 151 and 290; 60 queries of 1 to 6 patterns and
+// 100 rows 39 and 182, 512 of them 143 and 278; 60 queries of 1 to 6 patterns and
 // up to 30 000 rows, where few enough are left, 89 to 295 and 550.
 constexpr int32_t kSmallBatch = 512;
 constexpr int32_t kSmallUnsure = 64;
