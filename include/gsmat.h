@@ -39,9 +39,9 @@
  *     unless an allocator is given to gsmat_load_triples.
  *   - The store's index is immutable after gsmat_build_index; concurrent
  *     gsmat_join calls on different streams (and different results) are
- *     allowed.  gsmat_set_sparse_expand, gsmat_set_batch_tuning and
- *     gsmat_autotune_batch change tuning settings of the store and must not
- *     overlap other calls on it.
+ *     allowed.  gsmat_set_sparse_expand, gsmat_set_batch_tuning,
+ *     gsmat_set_small_joins and gsmat_autotune_batch change tuning settings of
+ *     the store and must not overlap other calls on it.
  *   - A result's (and a server's) memory is returned to the allocator on the
  *     stream it was made on: that stream must outlive them.
  *   - A gsmat_server_step whose round fails (device allocation, HIP error)

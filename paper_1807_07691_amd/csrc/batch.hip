@@ -1278,6 +1278,7 @@ extern "C" gsmat_status gsmat_join_batch_bgp(gsmat_store* st, const gsmat_patter
     std::vector<gsmat_status> prc;
     std::vector<std::string> pmsg;
     std::vector<std::unique_ptr<gsmat_query_plan>> fb;
+    st->dbatch_rounds = false;
     // so many that may outgrow the small launch take the rounds anyway
     int unsure = 0;
     for (int i = 0; i < n_queries; ++i) unsure += n_pats[i] >= 3;

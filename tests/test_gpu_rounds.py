@@ -180,3 +180,6 @@ def test_round_stats_are_the_last_batchs(G, tiny):
     finally:
         G.gsmat_set_small_joins(st, 0)
     assert _rounds(G, st, [q.tps for q in qs], G.PLAN_ADAPTIVE) > 0
+    # a fused batch of which no query can be planned
+    _, stat = G.gsmat_join_batch_bgp(st, [[[-1, -1, -2]]] * 600, raise_on_error=False)
+    assert stat == [G.GSMAT_EUNSUPPORTED] * 600 and G.gsmat_batch_round_stats(st) == []
